@@ -131,6 +131,7 @@ Layout make_layout(const gcamps_config& c) {
   L.off_perm = take(L.mcap * sizeof(int));
   L.off_eigG = take(3 * L.m_pad * L.m_pad * sizeof(z64));  // two matrix buffers and the accumulator
   L.off_eigV = take((L.m_pad / 64 + 1) * 64 * 64 * sizeof(z64));
+  L.off_eigD = take((L.m_pad / 64 + 1) * 64 * 64 * sizeof(z64));
   L.off_flags = take(4096);
   L.off_s2 = take(L.ncand * sizeof(double));
   L.off_s2w = take(L.ncand * sizeof(double));
@@ -252,6 +253,7 @@ int32_t gcamps_init(const gcamps_config* cfg, void* dev_workspace, size_t bytes,
     c->perm = reinterpret_cast<int*>(w + lay.off_perm);
     c->eig.G = reinterpret_cast<z64*>(w + lay.off_eigG);
     c->eig.V = reinterpret_cast<z64*>(w + lay.off_eigV);
+    c->eig.D = reinterpret_cast<z64*>(w + lay.off_eigD);
     c->eig.flags = reinterpret_cast<int*>(w + lay.off_flags);
     c->eig.m_pad = (int)lay.m_pad;
     c->s2 = reinterpret_cast<double*>(w + lay.off_s2);

@@ -29,11 +29,35 @@ void launch_zgemm(hipStream_t s, int opa, int opb, int M, int N, int K, const z6
 // eigenvectors, lam the eigenvalues (unsorted).  rel: relative-accuracy criterion.
 struct EigWork {
   z64* G;      // three padded m_pad x m_pad planes: matrix, accumulator, second matrix buffer
-  z64* V;      // block rotations
+  z64* V;      // block rotations (two rounds)
+  z64* D;      // solved sub-problems (two rounds)
   int* flags;  // device flags
   int m_pad;
   double* host_rb = nullptr;  // pinned host read-back slots (2 doubles); pageable locals when null
 };
+// Criteria of the sweeps.  Absolute criterion 2e-15 of the trace: what stays off the diagonal tilts a
+// factor's columns by up to 2e-15 trace / lambda (1.1e-12 at 4e-15 on a Gaussian 300 x 97); half the
+// bound takes no further sweep.
+struct JacobiCrit {
+  double tol, skip_rel, floor_rel;
+  int max_sweeps;
+};
+inline JacobiCrit jacobi_crit(int m, int rel) {
+  // Relative pass: pairs whose diagonal entries are both below 1e-28 lambda_max (lambda_max >=
+  // trace / m) are left alone.  They lie two decades below the rank floor (sigma^2 = 1e-26
+  // sigma_0^2), so no decision depends on them, and exact null directions sit at the rounding
+  // level (~1e-32 of the trace), where a relative criterion cannot be met.
+  // An off-diagonal entry of at most 1e-29 trace / m (<= 1e-29 lambda_max) counts as converged
+  // there.  On exactly rank-deficient matrices the rounding of the rotations keeps entries of that
+  // size alive between directions at the rounding level, where a relative criterion is never met
+  // (the pass then ran out of sweeps); an eigenvalue at or above the rank floor (1e-26 lambda_max)
+  // moves by at most 1e-3 of itself because of such an entry.
+  // Sweeps grow with m on these Grams: up to ~20 at m = 768, 19-26 at m = 3072, where one
+  // decomposition needed more than 40 (every sub-problem still rotating for the first ~20
+  // sweeps, then a steady decay).
+  return JacobiCrit{rel ? 1e-14 : 2e-15, rel ? 1e-28 / (double)m : 0.0, rel ? 1e-29 / (double)m : 0.0,
+                    m > 1024 ? 100 : 40};
+}
 // Offsets in a context's pinned read-back block: device status, Cholesky state, eigensolver
 // slots, conjugated Weyl string and its error flag.
 constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbEig = 512, kRbWeyl = 1024, kRbWeylErr = 2560, kRbBytes = 4096;

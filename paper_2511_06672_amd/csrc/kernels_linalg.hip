@@ -11,11 +11,10 @@
 #include <cfloat>
 #include <cstring>
 
+#include "jacobi.h"
 #include "kernels.h"
 
 namespace gc {
-
-typedef double d4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -210,436 +209,35 @@ __global__ __launch_bounds__(512) void k_zgemm_ks(int M, int N, int K, const z64
 }
 
 // ===================================================================================== Jacobi
-// Round-robin (circle) pairing: step s of mp-1 steps pairs positions k and mp-1-k; position 0
-// is fixed, position i >= 1 holds element ((i - 1 + s) mod (mp - 1)) + 1.  Every unordered pair
-// of the mp indices meets exactly once per sweep.
-__device__ __forceinline__ void rr_pair(int k, int s, int mp, int& p, int& q) {
-  // k < mp / 2 and 0 <= s < mp - 1 keep both circle positions below 2 (mp - 1): one conditional
-  // subtraction reduces them
-  const int n1 = mp - 1, i0 = k, i1 = mp - 1 - k;
-  const int x0 = i0 - 1 + s, x1 = i1 - 1 + s;
-  int e0 = (i0 == 0) ? 0 : (x0 >= n1 ? x0 - n1 : x0) + 1;
-  int e1 = (x1 >= n1 ? x1 - n1 : x1) + 1;
-  p = e0 < e1 ? e0 : e1;
-  q = e0 < e1 ? e1 : e0;
-}
-
-// tab[(s * half + k) * 2 + {0, 1}] = (p, q) for every step s and pair k.
-__device__ void build_pair_table(unsigned char* tab, int mp) {
-  const int half = mp / 2;
-  for (int e = threadIdx.x; e < (mp - 1) * half; e += blockDim.x) {
-    int s = e / half, k = e - s * half, p, q;
-    rr_pair(k, s, mp, p, q);
-    tab[2 * e] = (unsigned char)p;
-    tab[2 * e + 1] = (unsigned char)q;
-  }
-}
-
-struct JacobiArgs {
-  double thr;   // absolute threshold on |g| (abs mode)
-  double tol;   // relative threshold |g| <= tol sqrt(|a b|) (rel mode)
-  double skip;  // rel mode: pairs whose diagonal entries are both below skip are left alone
-  int rel;
-  double floor2;  // rel mode: pairs with |g|^2 <= floor2 count as converged
-};
-
-// 1/sqrt(x) and 1/x from the hardware estimates refined by two Newton steps (the estimates
-// carry about 23 correct bits; each step doubles them).
-__device__ __forceinline__ double rsqrt_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = y * (1.5 - 0.5 * x * y * y);
-  return y * (1.5 - 0.5 * x * y * y);
-}
-__device__ __forceinline__ double rcp_nr(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = y * (2.0 - x * y);
-  return y * (2.0 - x * y);
-}
-
-// Whether the pair with diagonal (a, b) and off-diagonal g = gr + i gi is rotated.
-__device__ __forceinline__ bool rot_needed(double a, double b, double gr, double gi, const JacobiArgs& ja) {
-  const double h2 = gr * gr + gi * gi;
-  if (ja.rel)
-    return h2 > 1e-290 && h2 > ja.floor2 && h2 > ja.tol * ja.tol * fabs(a) * fabs(b) && fmax(fabs(a), fabs(b)) > ja.skip;
-  return h2 > 1e-290 && h2 > ja.thr * ja.thr;
-}
-
-// Rotation J = [[c, -sp], [conj(sp), c]] (c real, |sp|^2 = 1 - c^2) for the Hermitian 2x2
-// [[a, g], [conj g, b]]: J H J^H is diagonal with entries (a - t|g|, b + t|g|), where
-// t = sign(b - a) 2|g| / (|b - a| + R), R = sqrt((b - a)^2 + 4|g|^2) (the smaller root of
-// |g| t^2 - (a - b) t - |g| = 0), c = 1/sqrt(1 + t^2) and sp = c t g/|g|.  With
-// den = |b - a| + R these are c = den / sqrt(den^2 + 4|g|^2), sp = sign 2 g / sqrt(den^2 + 4|g|^2),
-// t|g| = sign 2|g|^2 / den: two reciprocal square roots in sequence.
-__device__ __forceinline__ bool rot_params(double a, double b, double gr, double gi, const JacobiArgs& ja, double& c,
-                                           double& spr, double& spi, double& na, double& nb) {
-  if (!rot_needed(a, b, gr, gi, ja)) return false;
-  const double h2 = gr * gr + gi * gi;
-  const double dlt = b - a;
-  const double sg = dlt < 0.0 ? -1.0 : 1.0;
-  const double r2 = dlt * dlt + 4.0 * h2;
-  const double den = fabs(dlt) + r2 * rsqrt_nr(r2);
-  const double q = rsqrt_nr(den * den + 4.0 * h2);
-  c = den * q;
-  const double f = 2.0 * sg * q;
-  spr = f * gr;
-  spi = f * gi;
-  const double th = 2.0 * sg * h2 * rcp_nr(den);
-  na = a - th;
-  nb = b + th;
-  return true;
-}
-
-// One rotation of a parallel step: the pair's (c, sp) and new diagonal entries, and whether it
-// rotates at all.
-struct Rot {
-  double c, spr, spi, na, nb;
-  bool f;
-};
-
-// The rotation of pair (p, q) of the Hermitian matrix in planes (hr, hi) (leading dimension ld).
-__device__ __forceinline__ Rot pair_rot(const double* __restrict__ hr, const double* __restrict__ hi, int ld, int p,
-                                        int q, const JacobiArgs& ja) {
-  Rot r;
-  r.f = rot_params(hr[p * ld + p], hr[q * ld + q], hr[p * ld + q], hi[p * ld + q], ja, r.c, r.spr, r.spi, r.na, r.nb);
-  return r;
-}
-
-// The 2x2 block (a b; c d) of rows (p1, q1) and columns (p2, q2) of H, rotated in place into
-// the block of J H J^H: rotation r1 on the rows, r2 on the columns; diag marks the block of the
-// pair itself (r1 = r2), whose result is diagonal.
-__device__ __forceinline__ void rotate_vals(double& ar, double& ai, double& br, double& bi, double& cr, double& ci,
-                                            double& dr, double& di, const Rot& r1, const Rot& r2, bool diag,
-                                            int* any) {
-  if (r1.f) {  // rows: r_p' = c r_p - sp r_q ; r_q' = conj(sp) r_p + c r_q
-    const double c1 = r1.c, sp1r = r1.spr, sp1i = r1.spi;
-    const double nar = c1 * ar - (sp1r * cr - sp1i * ci), nai = c1 * ai - (sp1r * ci + sp1i * cr);
-    const double nbr = c1 * br - (sp1r * dr - sp1i * di), nbi = c1 * bi - (sp1r * di + sp1i * dr);
-    const double ncr = c1 * cr + (sp1r * ar + sp1i * ai), nci = c1 * ci + (sp1r * ai - sp1i * ar);
-    const double ndr = c1 * dr + (sp1r * br + sp1i * bi), ndi = c1 * di + (sp1r * bi - sp1i * br);
-    ar = nar;
-    ai = nai;
-    br = nbr;
-    bi = nbi;
-    cr = ncr;
-    ci = nci;
-    dr = ndr;
-    di = ndi;
-  }
-  if (r2.f) {  // cols: c_p' = c c_p - conj(sp) c_q ; c_q' = sp c_p + c c_q
-    const double c2 = r2.c, sp2r = r2.spr, sp2i = r2.spi;
-    const double nar = c2 * ar - (sp2r * br + sp2i * bi), nai = c2 * ai - (sp2r * bi - sp2i * br);
-    const double ncr = c2 * cr - (sp2r * dr + sp2i * di), nci = c2 * ci - (sp2r * di - sp2i * dr);
-    const double nbr = c2 * br + (sp2r * ar - sp2i * ai), nbi = c2 * bi + (sp2r * ai + sp2i * ar);
-    const double ndr = c2 * dr + (sp2r * cr - sp2i * ci), ndi = c2 * di + (sp2r * ci + sp2i * cr);
-    ar = nar;
-    ai = nai;
-    br = nbr;
-    bi = nbi;
-    cr = ncr;
-    ci = nci;
-    dr = ndr;
-    di = ndi;
-  }
-  if (diag && r1.f) {
-    ar = r1.na;
-    dr = r1.nb;
-    ai = di = br = bi = cr = ci = 0.0;
-  }
-  if (r1.f || r2.f) *any = 1;
-}
-
-// The same block read from the old planes (ir, ii) (leading dimension ld) and written to the new
-// ones (orr, oi).
-__device__ __forceinline__ void rotate_block(const double* __restrict__ ir, const double* __restrict__ ii,
-                                             double* __restrict__ orr, double* __restrict__ oi, int ld, int p1,
-                                             int q1, int p2, int q2, const Rot& r1, const Rot& r2, bool diag,
-                                             int* any) {
-  double ar = ir[p1 * ld + p2], ai = ii[p1 * ld + p2];
-  double br = ir[p1 * ld + q2], bi = ii[p1 * ld + q2];
-  double cr = ir[q1 * ld + p2], ci = ii[q1 * ld + p2];
-  double dr = ir[q1 * ld + q2], di = ii[q1 * ld + q2];
-  rotate_vals(ar, ai, br, bi, cr, ci, dr, di, r1, r2, diag, any);
-  orr[p1 * ld + p2] = ar;
-  oi[p1 * ld + p2] = ai;
-  orr[p1 * ld + q2] = br;
-  oi[p1 * ld + q2] = bi;
-  orr[q1 * ld + p2] = cr;
-  oi[q1 * ld + p2] = ci;
-  orr[q1 * ld + q2] = dr;
-  oi[q1 * ld + q2] = di;
-}
-
-// Rotation r (pair (p, q)) applied to rows v0 and v1 of the eigenvector accumulator, in place:
-// v_p' = c v_p - conj(sp) v_q ; v_q' = sp v_p + c v_q.
-__device__ __forceinline__ void rotate_vrows(double* __restrict__ vr, double* __restrict__ vi, int ld, int v0, int v1,
-                                             int p, int q, const Rot& r) {
-  const double c1 = r.c, sp1r = r.spr, sp1i = r.spi;
-  const double w0pr = vr[v0 * ld + p], w0pi = vi[v0 * ld + p];
-  const double w0qr = vr[v0 * ld + q], w0qi = vi[v0 * ld + q];
-  const double w1pr = vr[v1 * ld + p], w1pi = vi[v1 * ld + p];
-  const double w1qr = vr[v1 * ld + q], w1qi = vi[v1 * ld + q];
-  vr[v0 * ld + p] = c1 * w0pr - (sp1r * w0qr + sp1i * w0qi);
-  vi[v0 * ld + p] = c1 * w0pi - (sp1r * w0qi - sp1i * w0qr);
-  vr[v0 * ld + q] = c1 * w0qr + (sp1r * w0pr - sp1i * w0pi);
-  vi[v0 * ld + q] = c1 * w0qi + (sp1r * w0pi + sp1i * w0pr);
-  vr[v1 * ld + p] = c1 * w1pr - (sp1r * w1qr + sp1i * w1qi);
-  vi[v1 * ld + p] = c1 * w1pi - (sp1r * w1qi - sp1i * w1qr);
-  vr[v1 * ld + q] = c1 * w1qr + (sp1r * w1pr - sp1i * w1pi);
-  vi[v1 * ld + q] = c1 * w1qi + (sp1r * w1pi + sp1i * w1pr);
-}
-
-// rot_params without branches: every lane computes the rotation and the result is selected at the
-// end (the identity and the unchanged diagonal when the pair is not rotated), so that the
-// scheduler can interleave two rotations of one thread.
-__device__ __forceinline__ Rot rot_select(double a, double b, double gr, double gi, const JacobiArgs& ja) {
-  const bool need = rot_needed(a, b, gr, gi, ja);
-  const double h2 = gr * gr + gi * gi;
-  const double dlt = b - a;
-  const double sg = dlt < 0.0 ? -1.0 : 1.0;
-  const double r2 = dlt * dlt + 4.0 * h2;
-  const double den = fabs(dlt) + r2 * rsqrt_nr(r2);
-  const double q = rsqrt_nr(den * den + 4.0 * h2);
-  const double f = 2.0 * sg * q;
-  const double th = 2.0 * sg * h2 * rcp_nr(den);
-  Rot r;
-  r.f = need;
-  r.c = need ? den * q : 1.0;
-  r.spr = need ? f * gr : 0.0;
-  r.spi = need ? f * gi : 0.0;
-  r.na = need ? a - th : a;
-  r.nb = need ? b + th : b;
-  return r;
-}
-
-// A sequence of parallel Jacobi steps on the Hermitian H (2*half indices, half <= 16) held as
-// two re/im plane pairs in LDS (double buffer).  Step s uses the pairs tab[s][k] = (p, q).
-// Item (k1, k2) (k1, k2 < half) is the 2x2 block of rows (p_k1, q_k1) and columns
-// (p_k2, q_k2): it needs rotations k1 and k2, computed from the old buffer, and its rotated block
-// goes to the new buffer.  Rotation k1 is also applied to two rows of the eigenvector
-// accumulator (V planes, in place; 2 * half rows in total).  With at least 2 half^2 threads the
-// block update and the V update of an item run on different threads (each computes the
-// rotations it needs), otherwise one thread does both; items are dealt round-robin.  On that
-// split, V threads take k1 as the fast index and rows k2 and k2 + half (with a leading
-// dimension of 16 mod 32 doubles the V accesses of 32 consecutive lanes fall in distinct
-// banks); otherwise k2 is the fast index and the rows are 2 k2 and 2 k2 + 1.  One barrier per
-// step.  Returns the index (0/1) of the buffer holding the result; *any is set when a rotation
-// happened.
-__device__ int jacobi_steps(double* __restrict__ h0r, double* __restrict__ h0i, double* __restrict__ h1r,
-                            double* __restrict__ h1i, int ldh, int half, const unsigned char* __restrict__ tab,
-                            int nsteps, double* __restrict__ vr, double* __restrict__ vi, int ldv,
-                            const JacobiArgs& ja, int* any) {
-  const int t = threadIdx.x, nt = blockDim.x;
-  const int nitems = half * half;
-  const bool split = nt >= 2 * nitems;
-  const int nwork = split ? 2 * nitems : nitems;
-  int cur = 0;
-  for (int step = 0; step < nsteps; ++step) {
-    const unsigned char* pt = tab + step * 2 * half;
-    const double* __restrict__ ir = cur ? h1r : h0r;
-    const double* __restrict__ ii = cur ? h1i : h0i;
-    double* __restrict__ orr = cur ? h0r : h1r;
-    double* __restrict__ oi = cur ? h0i : h1i;
-    for (int e0 = t; e0 < nwork; e0 += nt) {
-      const bool vsplit = split && e0 >= nitems;
-      const bool do_v = !split || vsplit;
-      const bool do_h = !split || e0 < nitems;
-      const int e = vsplit ? e0 - nitems : e0;
-      int k1, k2;
-      if (vsplit) {
-        k2 = (int)(((float)e + 0.5f) / (float)half);
-        k1 = e - k2 * half;
-      } else {
-        k1 = (int)(((float)e + 0.5f) / (float)half);
-        k2 = e - k1 * half;
-      }
-      const int p1 = pt[2 * k1], q1 = pt[2 * k1 + 1];
-      const Rot r1 = pair_rot(ir, ii, ldh, p1, q1, ja);
-      if (do_h) {
-        const int p2 = pt[2 * k2], q2 = pt[2 * k2 + 1];
-        const Rot r2 = pair_rot(ir, ii, ldh, p2, q2, ja);
-        rotate_block(ir, ii, orr, oi, ldh, p1, q1, p2, q2, r1, r2, k1 == k2, any);
-      }
-      if (do_v && r1.f) {
-        if (vsplit)
-          rotate_vrows(vr, vi, ldv, k2, k2 + half, p1, q1, r1);
-        else
-          rotate_vrows(vr, vi, ldv, 2 * k2, 2 * k2 + 1, p1, q1, r1);
-      }
-    }
-    __syncthreads();
-    cur ^= 1;
-  }
-  return cur;
-}
-
-// x from lane (l + 1) mod 16 of the same 16-lane row (DPP row rotation by 15 to the right); every
-// lane of the row must be active.
-__device__ __forceinline__ double row_next(double x) {
-  const long long v = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x12F, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x12F, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// The inter-block steps of a 32-index sub-problem on 512 threads, with its eigenvector
-// accumulator V (starting from the identity) written to vo (32 x 32, row-major): step s
-// (0..15) pairs index k < 16 with q_k(s) = 16 + (k + s) mod 16, so the 16 steps visit every pair
-// (i < 16 <= j) once.  The arithmetic is that of jacobi_steps on the same pairs.
-// Threads 0..255 update the blocks (k1 = t / 16, k2 = t mod 16); all LDS reads of a step are
-// issued before its rotations are computed.  With a leading dimension of 16 mod 32 doubles every
-// block and diagonal access of 32 consecutive lanes falls in distinct LDS banks.
-// Threads 256..511 hold V in registers: thread (k1 = t mod 16, k2 = (t - 256) / 16) keeps rows
-// k2 and k2 + 16 of columns k1 and q_k1(s).  It applies rotation k1, then takes column
-// q_k1(s + 1) = q_{k1+1}(s) from the next lane of its 16-lane row; after 16 steps the columns
-// are back at 16 + k1.  The 16 steps leave the matrix in (h0r, h0i).
-__device__ void jacobi_ib_steps(double* __restrict__ h0r, double* __restrict__ h0i, double* __restrict__ h1r,
-                                double* __restrict__ h1i, int ld, z64* __restrict__ vo, const JacobiArgs& ja,
-                                int* any) {
-  const int t = threadIdx.x;
-  const bool do_v = t >= 256;  // uniform over each wave
-  const int e = t & 255;
-  const int k1 = do_v ? (e & 15) : (e >> 4);
-  const int k2 = do_v ? (e >> 4) : (e & 15);
-  // V thread: columns (p, q) of rows k2 (w0*) and k2 + 16 (w1*)
-  double w0pr = (k1 == k2) ? 1.0 : 0.0, w0pi = 0.0, w0qr = 0.0, w0qi = 0.0;
-  double w1pr = 0.0, w1pi = 0.0, w1qr = (k1 == k2) ? 1.0 : 0.0, w1qi = 0.0;
-#pragma unroll 2
-  for (int step = 0; step < 16; ++step) {
-    const bool odd = step & 1;
-    const double* __restrict__ ir = odd ? h1r : h0r;
-    const double* __restrict__ ii = odd ? h1i : h0i;
-    double* __restrict__ orr = odd ? h0r : h1r;
-    double* __restrict__ oi = odd ? h0i : h1i;
-    const int p1 = k1, q1 = 16 + ((k1 + step) & 15);
-    const double a1 = ir[p1 * ld + p1], b1 = ir[q1 * ld + q1], g1r = ir[p1 * ld + q1], g1i = ii[p1 * ld + q1];
-    if (!do_v) {
-      const int p2 = k2, q2 = 16 + ((k2 + step) & 15);
-      const double a2 = ir[p2 * ld + p2], b2 = ir[q2 * ld + q2], g2r = ir[p2 * ld + q2], g2i = ii[p2 * ld + q2];
-      double ar = ir[p1 * ld + p2], ai = ii[p1 * ld + p2];
-      double br = ir[p1 * ld + q2], bi = ii[p1 * ld + q2];
-      double cr = ir[q1 * ld + p2], ci = ii[q1 * ld + p2];
-      double dr = ir[q1 * ld + q2], di = ii[q1 * ld + q2];
-      const Rot r1 = rot_select(a1, b1, g1r, g1i, ja), r2 = rot_select(a2, b2, g2r, g2i, ja);
-      rotate_vals(ar, ai, br, bi, cr, ci, dr, di, r1, r2, k1 == k2, any);
-      orr[p1 * ld + p2] = ar;
-      oi[p1 * ld + p2] = ai;
-      orr[p1 * ld + q2] = br;
-      oi[p1 * ld + q2] = bi;
-      orr[q1 * ld + p2] = cr;
-      oi[q1 * ld + p2] = ci;
-      orr[q1 * ld + q2] = dr;
-      oi[q1 * ld + q2] = di;
-    } else {
-      const Rot r1 = rot_select(a1, b1, g1r, g1i, ja);
-      if (r1.f) {  // v_p' = c v_p - conj(sp) v_q ; v_q' = sp v_p + c v_q
-        const double c1 = r1.c, sp1r = r1.spr, sp1i = r1.spi;
-        const double n0pr = c1 * w0pr - (sp1r * w0qr + sp1i * w0qi), n0pi = c1 * w0pi - (sp1r * w0qi - sp1i * w0qr);
-        const double n0qr = c1 * w0qr + (sp1r * w0pr - sp1i * w0pi), n0qi = c1 * w0qi + (sp1r * w0pi + sp1i * w0pr);
-        const double n1pr = c1 * w1pr - (sp1r * w1qr + sp1i * w1qi), n1pi = c1 * w1pi - (sp1r * w1qi - sp1i * w1qr);
-        const double n1qr = c1 * w1qr + (sp1r * w1pr - sp1i * w1pi), n1qi = c1 * w1qi + (sp1r * w1pi + sp1i * w1pr);
-        w0pr = n0pr;
-        w0pi = n0pi;
-        w0qr = n0qr;
-        w0qi = n0qi;
-        w1pr = n1pr;
-        w1pi = n1pi;
-        w1qr = n1qr;
-        w1qi = n1qi;
-      }
-      w0qr = row_next(w0qr);
-      w0qi = row_next(w0qi);
-      w1qr = row_next(w1qr);
-      w1qi = row_next(w1qi);
-    }
-    __syncthreads();
-  }
-  if (do_v) {
-    vo[k2 * 32 + k1] = z64{w0pr, w0pi};
-    vo[k2 * 32 + 16 + k1] = z64{w0qr, w0qi};
-    vo[(k2 + 16) * 32 + k1] = z64{w1pr, w1pi};
-    vo[(k2 + 16) * 32 + 16 + k1] = z64{w1qr, w1qi};
-  }
-}
-
-// Round-robin table for mp indices (mp - 1 steps of mp/2 pairs).
-__device__ void build_rr_table(unsigned char* tab, int mp) { build_pair_table(tab, mp); }
-
-constexpr int SMALL_LD = 33;  // plane leading dimension for sub-problems of up to 32 indices
-
-// Single-workgroup Jacobi: G (m x m, m <= kSmallEig = 32) -> U (m x m), lam (m), all in LDS.
-__global__ __launch_bounds__(256) void k_jacobi_small(const z64* __restrict__ G, int ldg_in, int m,
-                                                      z64* __restrict__ U, int ldu, double* __restrict__ lam, int rel,
-                                                      double tol, double skip_rel, double floor_rel, int max_sweeps,
-                                                      DevStatus* st) {
-  constexpr int PL = 32 * SMALL_LD;
-  __shared__ double h0r[PL], h0i[PL], h1r[PL], h1i[PL], vr[PL], vi[PL];
-  __shared__ unsigned char tab[31 * 32];
-  __shared__ int any, pending;
+// Single-workgroup Jacobi: G (m x m, m <= 2 HM) -> U (m x m), lam (m), all in LDS; 2 HM^2 threads.
+template <int HM, bool REL>
+__global__ __launch_bounds__(2 * HM * HM) void k_jacobi_small(const z64* __restrict__ G, int ldg_in, int m,
+                                                              z64* __restrict__ U, int ldu, double* __restrict__ lam,
+                                                              JacobiCrit cr, DevStatus* st) {
+  constexpr int LD = 2 * HM;
+  __shared__ __align__(16) z64 hs[2 * LD * LD], v[LD * LD];
+  __shared__ int pending[2];
   __shared__ double trace;
-  const int mp = m + (m & 1);
-  const int half = mp / 2;
-  const int t = threadIdx.x, nt = blockDim.x, ldh = SMALL_LD;
-  build_rr_table(tab, mp);
-  for (int idx = t; idx < mp * mp; idx += nt) {
-    const int i = idx / mp, j = idx - (idx / mp) * mp;
-    const z64 v = (i < m && j < m) ? G[(size_t)i * ldg_in + j] : z64{0.0, 0.0};
-    h0r[i * ldh + j] = v.re;
-    h0i[i * ldh + j] = v.im;
-    vr[i * ldh + j] = (i == j) ? 1.0 : 0.0;
-    vi[i * ldh + j] = 0.0;
+  const int t = threadIdx.x, nt = blockDim.x;
+  for (int idx = t; idx < LD * LD; idx += nt) {
+    const int i = idx / LD, j = idx % LD;
+    z64 x = (i < m && j < m) ? G[(size_t)i * ldg_in + j] : z64{0.0, 0.0};
+    if (i == j) x.im = 0.0;
+    hs[idx] = x;
+    v[idx] = z64{(i == j) ? 1.0 : 0.0, 0.0};
   }
+  if (t < 2) pending[t] = 0;
   __syncthreads();
-  if (t == 0) {
-    double tr = 0.0;
-    for (int i = 0; i < m; ++i) tr += fabs(h0r[i * ldh + i]);
-    trace = tr;
-  }
+  jacobi_trace<LD>(hs, m, &trace);
   __syncthreads();
-  const JacobiArgs ja{tol * trace, tol, skip_rel * trace, rel, (floor_rel * trace) * (floor_rel * trace)};
-  int sweeps = 0, cur = 0;
-  bool conv = false;
-  for (int sw = 0; sw < max_sweeps; ++sw) {
-    if (t == 0) any = 0;
-    __syncthreads();
-    // an odd number of steps swaps the buffers; keep the live matrix in (h0)
-    const int res = jacobi_steps(cur ? h1r : h0r, cur ? h1i : h0i, cur ? h0r : h1r, cur ? h0i : h1i, ldh, half, tab,
-                                 mp - 1, vr, vi, ldh, ja, &any);
-    cur ^= res;
-    ++sweeps;
-    __syncthreads();
-    // every wave reads the flag before thread 0 resets it for the next sweep
-    const int rotated = any;
-    __syncthreads();
-    if (!rotated) {
-      conv = true;
-      break;
-    }
-    // The next sweep would rotate nothing (and change nothing) if no pair of the current matrix
-    // passes the rotation test, read either way round: then it is skipped (7% faster here,
-    // where a sweep is 31 dependent steps and the check one parallel pass).
-    if (t == 0) pending = 0;
-    __syncthreads();
-    {
-      const double* hr = cur ? h1r : h0r;
-      const double* hi = cur ? h1i : h0i;
-      for (int idx = t; idx < mp * mp; idx += nt) {
-        const int i = idx / mp, j = idx - (idx / mp) * mp;
-        if (i != j && rot_needed(hr[i * ldh + i], hr[j * ldh + j], hr[i * ldh + j], hi[i * ldh + j], ja)) pending = 1;
-      }
-    }
-    __syncthreads();
-    const int still = pending;
-    __syncthreads();
-    if (!still) {
-      conv = true;
-      break;
-    }
-  }
-  const double* fr = cur ? h1r : h0r;
-  for (int i = t; i < m; i += nt) lam[i] = fr[i * ldh + i];
+  const JacobiThr jt = jacobi_thr(trace, cr.tol, cr.skip_rel, REL, cr.floor_rel);
+  int sweeps;
+  bool conv;
+  const z64* h = jacobi_sweeps<HM, REL>(hs, v, m, jt, cr.max_sweeps, pending, &sweeps, &conv);
+  for (int i = t; i < m; i += nt) lam[i] = h[i * (LD + 1)].re;
   for (int idx = t; idx < m * m; idx += nt) {
     const int i = idx / m, j = idx - (idx / m) * m;
-    U[(size_t)i * ldu + j] = z64{vr[i * ldh + j], vi[i * ldh + j]};
+    U[(size_t)i * ldu + j] = v[i * LD + j];
   }
   if (t == 0 && st) {
     st->converged = conv ? 1 : 0;
@@ -652,43 +250,6 @@ constexpr int BJ = kBlk;      // block size (16)
 constexpr int kSolveThreads = 512;  // threads per 32x32 sub-problem (block and V updates split)
 static_assert(kSolveThreads == 2 * BJ * BJ, "the inter-block steps give each thread one block or one V item");
 constexpr int BJ2 = 2 * kBlk; // pair size (32)
-constexpr int SLD = BJ2 + 1;  // LDS leading dimension of the product tiles (plane layout)
-constexpr int JLD = 48;       // LDS leading dimension of the solve's planes (16 mod 32 doubles)
-
-// One 16x16 quadrant of a 32-deep complex product on one wave: acc += A B with
-// A(row, kk) = a[kk * lda + wr + row] (conjugated when conja) and B(kk, col) = b[kk * ldb + wc + col].
-// Every quadrant product of the rounds goes through this sequence, so a quadrant computed on its
-// own equals the same quadrant of a whole-tile product bit for bit.
-__device__ __forceinline__ void mmq(const double* ar_, const double* ai_, int lda, int wr, const double* br_,
-                                    const double* bi_, int ldb, int wc, bool conja, d4& accr, d4& acci) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int kk = 0; kk < BJ2; kk += 4) {
-    const int ka = kk + (lane >> 4);
-    const double ar = ar_[ka * lda + wr + (lane & 15)];
-    const double ai = conja ? -ai_[ka * lda + wr + (lane & 15)] : ai_[ka * lda + wr + (lane & 15)];
-    const double br = br_[ka * ldb + wc + (lane & 15)];
-    const double bi = bi_[ka * ldb + wc + (lane & 15)];
-    accr = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, accr, 0, 0, 0);
-    accr = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, bi, accr, 0, 0, 0);
-    acci = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, acci, 0, 0, 0);
-    acci = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, acci, 0, 0, 0);
-  }
-}
-
-// 32x32x32 complex product on four waves (one 16x16 quadrant each): acc += A * B where A is
-// read as a[kk][row] (planes re/im, ld SLD) and B as b[kk][col]; conja conjugates A.
-__device__ __forceinline__ void mm32(const double* ar_, const double* ai_, const double* br_, const double* bi_,
-                                     bool conja, d4& accr, d4& acci) {
-  const int w = threadIdx.x >> 6;
-  mmq(ar_, ai_, SLD, (w >> 1) * 16, br_, bi_, SLD, (w & 1) * 16, conja, accr, acci);
-}
-
-__device__ __forceinline__ int pair_index(int P, int i, int step, int nb) {
-  int I, J;
-  rr_pair(P, step, nb, I, J);
-  return i < BJ ? I * BJ + i : J * BJ + (i - BJ);
-}
 
 // The pair holding block b at outer step s and b's offset in it (0: first block, BJ: second):
 // the inverse of rr_pair over nb blocks.  Block 0 stays in pair 0; another block b sits at
@@ -708,375 +269,309 @@ __device__ __forceinline__ void block_home(int b, int s, int nb, int& pair, int&
   off = (b == I) ? 0 : BJ;
 }
 
-// One 32x32 row tile (R, Q) of U <- U V_Q with 512 threads: all threads stage the operands, the
-// first four waves multiply (planes re/im in a_*/b_*, 32 x SLD each).
-__device__ void u_tile(z64* __restrict__ Up, int mp, int nb, int step, const z64* __restrict__ V,
-                       const int* __restrict__ pair_flag, int tile, double* __restrict__ a_re,
-                       double* __restrict__ a_im, double* __restrict__ b_re, double* __restrict__ b_im) {
-  const int half = nb / 2;
-  const int R = tile / half, Q = tile % half;
-  if (!pair_flag[Q]) return;  // uniform over the block
-  const int t = threadIdx.x;
-  const z64* VQ = V + (size_t)Q * BJ2 * BJ2;
-  int q0, q1;
-  rr_pair(Q, step, nb, q0, q1);
-  z64 uv[BJ2 * BJ2 / kSolveThreads], qv[BJ2 * BJ2 / kSolveThreads];
+// The tile updates: four waves per 32 x 32 tile (one 16 x 16 quadrant each), two tiles per block,
+// operands straight from global memory into MFMA registers.  Only the first product of a G tile
+// passes through LDS, so that each wave can read both row halves of it.  A tile per block staged
+// through LDS and multiplied by half of the block's waves bound a round from about m = 600 on
+// (15 us there); one wave per 16-column half bound it at every size (13.5 us at m = 243: 128
+// dependent MFMAs per wave).
+constexpr int kTilesPerBlock = kSolveThreads / 256;
+
+// Quadrant product: acc = A(16 x 32) B(32 x 16) with B in b (b[j]: row 4 j + l / 16) and A's element
+// (row, kk) at a0[row * lda + kk] for kk < 16, a1[row * lda + kk - 16] otherwise.
+__device__ __forceinline__ void tile_mul(const z64* __restrict__ a0, const z64* __restrict__ a1, size_t lda,
+                                         const z64* b, d4& xr, d4& xi) {
+  const int lane = threadIdx.x & 63, lo = lane & 15, hi = lane >> 4;
+  z64 a[8];
 #pragma unroll
-  for (int u = 0; u < BJ2 * BJ2 / kSolveThreads; ++u) {  // every load before the first store
-    const int idx = t + kSolveThreads * u, row = idx / BJ2, kk = idx % BJ2;
-    uv[u] = Up[(size_t)(R * BJ2 + row) * mp + (kk < BJ ? q0 * BJ + kk : q1 * BJ + kk - BJ)];
-    qv[u] = VQ[idx];
-  }
+  for (int j = 0; j < 8; ++j) a[j] = (j < 4 ? a0 : a1)[lo * lda + 4 * (j & 3) + hi];
 #pragma unroll
-  for (int u = 0; u < BJ2 * BJ2 / kSolveThreads; ++u) {
-    const int idx = t + kSolveThreads * u, row = idx / BJ2, kk = idx % BJ2;
-    a_re[kk * SLD + row] = uv[u].re;
-    a_im[kk * SLD + row] = uv[u].im;
-    b_re[row * SLD + kk] = qv[u].re;
-    b_im[row * SLD + kk] = qv[u].im;
-  }
-  __syncthreads();
-  if (t < 256) {
-    const int lane = t & 63, w = t >> 6;
-    const int wr = (w >> 1) * 16, wc = (w & 1) * 16;
-    d4 accr = {0, 0, 0, 0}, acci = {0, 0, 0, 0};
-    mm32(a_re, a_im, b_re, b_im, false, accr, acci);
-    for (int q = 0; q < 4; ++q) {
-      const int row = wr + mfma_row_f64(lane, q), col = wc + (lane & 15);
-      Up[(size_t)(R * BJ2 + row) * mp + pair_index(Q, col, step, nb)] = z64{accr[q], acci[q]};
-    }
-  }
+  for (int j = 0; j < 8; ++j) mma4(a[j], b[j], xr, xi);
 }
 
-// One 32x32 tile (P, Q), P <= Q, of the round's update Gd = V^H Gs V with 512 threads (all stage
-// the operands, the first four waves multiply); the (Q, P) tile is written as the conjugate
-// transpose.  A pair that did not rotate contributes the identity; a tile whose two pairs both
-// did not rotate is copied as it is (with its mirror).
+// Column half ch of V_Q as an operand (v[j]: row 4 j + l / 16, column l % 16 of the half), or the
+// identity's when the pair did not rotate.
+__device__ __forceinline__ void load_vhalf(const z64* __restrict__ V, int Q, int flag, int ch, z64* v) {
+  const int lane = threadIdx.x & 63, lo = lane & 15, hi = lane >> 4;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j] = V[(size_t)Q * BJ2 * BJ2 + (4 * j + hi) * BJ2 + ch * BJ + lo];
+  if (!flag)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = z64{(4 * j + hi == ch * BJ + lo) ? 1.0 : 0.0, 0.0};
+}
+
+// Row tile (R, Q), tile = R half + Q, of U <- U V_Q, in place: all of a tile is read before any of
+// it is written (the barrier).
+__device__ void u_tile(z64* __restrict__ Up, int mp, int nb, int step, const z64* __restrict__ V,
+                       const int* __restrict__ pair_flag, int tile, int ntiles) {
+  const int half = nb / 2, lane = threadIdx.x & 63, lo = lane & 15, wv = threadIdx.x >> 6, ch = wv & 1,
+            rh = (wv >> 1) & 1;
+  const int R = tile / half, Q = tile % half;
+  const bool run = tile < ntiles && pair_flag[Q];  // uniform over the tile's waves
+  d4 xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0};
+  int q0, q1;
+  rr_pair(Q, step, nb, q0, q1);
+  z64* u = Up + (size_t)(R * BJ2 + rh * BJ) * mp;
+  if (run) {
+    z64 b[8];
+    load_vhalf(V, Q, 1, ch, b);
+    tile_mul(u + q0 * BJ, u + q1 * BJ, mp, b, xr, xi);
+  }
+  __syncthreads();
+  if (run)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {  // streamed: no later block of this round reads them
+      const d2 x = {xr[q], xi[q]};
+      __builtin_nontemporal_store(
+          x, reinterpret_cast<d2*>(u + (size_t)mfma_row_f64(lane, q) * mp + (ch ? q1 : q0) * BJ + lo));
+    }
+}
+
+// Tile (P, Q), P <= Q (numbered along the rows of the upper triangle), of the round's update
+// Gd = V^H Gs V; the (Q, P) tile is written as the conjugate transpose.  A pair that did not rotate
+// contributes the identity; a tile whose two pairs both did not rotate is copied as it is (with its
+// mirror), and a diagonal tile is the pair's solved sub-problem.  xs: 1024 elements of LDS per tile.
 __device__ void g_tile(const z64* __restrict__ Gs, z64* __restrict__ Gd, int mp, int nb, int step,
-                       const z64* __restrict__ V, const int* __restrict__ pair_flag, int tile, double* __restrict__ a_re,
-                       double* __restrict__ a_im, double* __restrict__ b_re, double* __restrict__ b_im) {
-  const int half = nb / 2;
-  int P = 0, rem = tile;
+                       const z64* __restrict__ V, const z64* __restrict__ D, const int* __restrict__ pair_flag,
+                       int tile, int ntiles, z64* __restrict__ xs) {
+  const int half = nb / 2, lane = threadIdx.x & 63, lo = lane & 15, hi = lane >> 4, wv = threadIdx.x >> 6, ch = wv & 1,
+            rh = (wv >> 1) & 1;
+  const bool live = tile < ntiles;  // uniform over the tile's waves, as all conditions below
+  int P = 0, rem = live ? tile : 0;
   while (rem >= half - P) {
     rem -= half - P;
     ++P;
   }
   const int Q = P + rem;
-  const int fP = pair_flag[P], fQ = pair_flag[Q];
-  const int t = threadIdx.x, nt = blockDim.x, lane = t & 63, w = t >> 6;
-  if (!fP && !fQ) {  // uniform over the block
-    for (int idx = t; idx < BJ2 * BJ2; idx += nt) {
-      const int row = idx / BJ2, col = idx % BJ2;
-      const size_t pq = (size_t)pair_index(P, row, step, nb) * mp + pair_index(Q, col, step, nb);
-      const size_t qp = (size_t)pair_index(Q, row, step, nb) * mp + pair_index(P, col, step, nb);
-      Gd[pq] = Gs[pq];
-      if (P != Q) Gd[qp] = Gs[qp];
-    }
-    return;
-  }
-  const int wr = (w >> 1) * 16, wc = (w & 1) * 16;
-  const z64* VP = V + (size_t)P * BJ2 * BJ2;
-  const z64* VQ = V + (size_t)Q * BJ2 * BJ2;
-  // V_P is needed after the first product: fetch it into registers now
-  z64 vp[BJ2 * BJ2 / kSolveThreads];
-#pragma unroll
-  for (int u = 0; u < BJ2 * BJ2 / kSolveThreads; ++u) {
-    const int idx = t + kSolveThreads * u;
-    const int r = idx / BJ2, c = idx % BJ2;
-    vp[u] = fP ? VP[idx] : ((r == c) ? z64{1.0, 0.0} : z64{0.0, 0.0});
-  }
-  // a[kk][row] = T[row][kk] = Gs[rows(P)[row], cols(Q)[kk]];  b = V_Q (or the identity); every
-  // load is issued before the first store
   int p0, p1, q0, q1;
   rr_pair(P, step, nb, p0, p1);
   rr_pair(Q, step, nb, q0, q1);
-  z64 gv[BJ2 * BJ2 / kSolveThreads], qv[BJ2 * BJ2 / kSolveThreads];
+  const int gr0 = (rh ? p1 : p0) * BJ, gc = (ch ? q1 : q0) * BJ + lo;  // the quadrant's rows, this lane's column
+  const int fP = pair_flag[P], fQ = pair_flag[Q];
+  const bool mul = live && P != Q && (fP || fQ);
+  z64 vp[8];
+  if (mul) {
+    z64 b[8];
+    d4 xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0};
+    load_vhalf(V, Q, fQ, ch, b);
+    load_vhalf(V, P, fP, rh, vp);
+    tile_mul(Gs + (size_t)gr0 * mp + q0 * BJ, Gs + (size_t)gr0 * mp + q1 * BJ, mp, b, xr, xi);  // X = T V_Q
 #pragma unroll
-  for (int u = 0; u < BJ2 * BJ2 / kSolveThreads; ++u) {
-    const int idx = t + kSolveThreads * u, row = idx / BJ2, kk = idx % BJ2;
-    const int gr = row < BJ ? p0 * BJ + row : p1 * BJ + row - BJ;
-    const int gc = kk < BJ ? q0 * BJ + kk : q1 * BJ + kk - BJ;
-    gv[u] = Gs[(size_t)gr * mp + gc];
-    qv[u] = fQ ? VQ[idx] : ((row == kk) ? z64{1.0, 0.0} : z64{0.0, 0.0});
-  }
-#pragma unroll
-  for (int u = 0; u < BJ2 * BJ2 / kSolveThreads; ++u) {
-    const int idx = t + kSolveThreads * u, row = idx / BJ2, kk = idx % BJ2;
-    a_re[kk * SLD + row] = gv[u].re;
-    a_im[kk * SLD + row] = gv[u].im;
-    b_re[row * SLD + kk] = qv[u].re;
-    b_im[row * SLD + kk] = qv[u].im;
+    for (int q = 0; q < 4; ++q) xs[ch * 512 + (rh * BJ + mfma_row_f64(lane, q)) * BJ + lo] = z64{xr[q], xi[q]};
   }
   __syncthreads();
-  d4 accr = {0, 0, 0, 0}, acci = {0, 0, 0, 0};
-  if (t < 256) mm32(a_re, a_im, b_re, b_im, false, accr, acci);  // X = T V_Q
-  __syncthreads();
-  if (t < 256)
+  if (mul) {  // Y = V_P^H X
+    d4 yr = {0, 0, 0, 0}, yi = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mma4(cconj(vp[j]), xs[ch * 512 + (4 * j + hi) * BJ + lo], yr, yi);
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int row = wr + mfma_row_f64(lane, q), col = wc + (lane & 15);
-      b_re[row * SLD + col] = accr[q];
-      b_im[row * SLD + col] = acci[q];
-      accr[q] = 0.0;
-      acci[q] = 0.0;
+      const int gr = gr0 + mfma_row_f64(lane, q);
+      Gd[(size_t)gr * mp + gc] = z64{yr[q], yi[q]};
+      Gd[(size_t)gc * mp + gr] = z64{yr[q], -yi[q]};
     }
+  } else if (live) {
 #pragma unroll
-  for (int u = 0; u < BJ2 * BJ2 / kSolveThreads; ++u) {
-    const int idx = t + kSolveThreads * u;
-    a_re[(idx / BJ2) * SLD + idx % BJ2] = vp[u].re;
-    a_im[(idx / BJ2) * SLD + idx % BJ2] = vp[u].im;
-  }
-  __syncthreads();
-  if (t < 256) {
-    mm32(a_re, a_im, b_re, b_im, true, accr, acci);  // Y = V_P^H X
-    for (int q = 0; q < 4; ++q) {
-      const int row = wr + mfma_row_f64(lane, q), col = wc + (lane & 15);
-      const int gr = pair_index(P, row, step, nb), gc = pair_index(Q, col, step, nb);
-      Gd[(size_t)gr * mp + gc] = z64{accr[q], acci[q]};
-      if (P != Q) Gd[(size_t)gc * mp + gr] = z64{accr[q], -acci[q]};
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * i + hi, gr = gr0 + r;
+      if (P == Q) {
+        Gd[(size_t)gr * mp + gc] = D[(size_t)P * BJ2 * BJ2 + (rh * BJ + r) * BJ2 + ch * BJ + lo];
+      } else {
+        const z64 x = Gs[(size_t)gr * mp + gc];
+        Gd[(size_t)gr * mp + gc] = x;
+        Gd[(size_t)gc * mp + gr] = cconj(x);
+      }
     }
   }
 }
 
-constexpr int HLD = 17;  // leading dimension of the half-width (32 x 16) planes of rebuild_pair
-constexpr int kRebuildLds = 6 * BJ2 * SLD + 4 * BJ2 * HLD;  // doubles of scratch rebuild_pair uses
-
-// The 32x32 sub-problem of blocks (I, J) after the previous round's update, rebuilt from the
-// matrix before that update (Gs) and that round's rotations (V, flags pf, outer step ps) with
-// the very products the previous round's tile updates make: with P and Q the previous pairs of
-// I and J (offsets oI and oJ in them), the diagonal blocks are quadrants of V_P^H Gs_PP V_P and
-// V_Q^H Gs_QQ V_Q and the off-diagonal block one of the (min, max) tile, mirrored as that tile's
-// update mirrors it.  Only the quadrants needed are formed, each in the order of the whole-tile
-// product (mmq), so the block equals what the update writes.  Writes planes (hr, hi) (leading
-// dimension JLD), which may alias the scratch sc (kRebuildLds doubles); kSolveThreads threads.
+// The 32x32 sub-problem of blocks (I, J) after the previous round's update, from the matrix before
+// that update (Gs) and that round's results (rotations V, solved sub-problems D, flags pf, outer
+// step ps), into h (32 x 32).  With P and Q the previous pairs of I and J (offsets oI and oJ in
+// them; P != Q, since consecutive rounds pair no two blocks twice), the diagonal blocks are those
+// that P's and Q's solves left, and the off-diagonal block is the (oI, oJ) quadrant of
+// V_P^H G_PQ V_Q: the only product a round's critical path has to wait for.  Waves 0..3 form it
+// straight from global memory into MFMA operands, X = G_PQ V_Q[:, oJ..] by row and K halves and
+// then V_P[:, oI..]^H X by K quarters; waves 4..7 fetch the diagonal blocks.  xs and ys are
+// scratch of 1024 elements.  A product over the whole (P, Q) tile, with the diagonal tiles
+// multiplied as well, took 5.5 us per round at m = 768.
 __device__ void rebuild_pair(int I, int J, const z64* __restrict__ Gs, int mp, int nb, int ps,
-                             const z64* __restrict__ V, const int* __restrict__ pf, double* __restrict__ sc,
-                             double* __restrict__ hr, double* __restrict__ hi) {
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+                             const z64* __restrict__ V, const z64* __restrict__ D, const int* __restrict__ pf,
+                             z64* __restrict__ xs, z64* __restrict__ ys, z64* __restrict__ h) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, lo = lane & 15, hi = lane >> 4;
   int P, oI, Q, oJ;
   block_home(I, ps, nb, P, oI);
   block_home(J, ps, nb, Q, oJ);
-  const int fP = pf[P], fQ = pf[Q];
-  // tile u: rows of pair A[u], columns of pair B[u], quadrant (qr[u], qc[u]) of its update
-  const bool sw = P > Q;
-  const int A[3] = {P, sw ? Q : P, Q}, B[3] = {P, sw ? P : Q, Q};
-  const int qr[3] = {oI, sw ? oJ : oI, oJ}, qc[3] = {oI, sw ? oI : oJ, oJ};
-  const bool fA[3] = {fP != 0, sw ? fQ != 0 : fP != 0, fQ != 0}, fB[3] = {fP != 0, sw ? fP != 0 : fQ != 0, fQ != 0};
-  // scratch: tile u transposed (tr[u][kk][row], ld SLD), then the half V planes: columns oI..oI+15
-  // of V_P (vh[0]) and oJ..oJ+15 of V_Q (vh[1]), vh[kk][c] with ld HLD
-  double* tr_re[3] = {sc, sc + 2 * BJ2 * SLD, sc + 4 * BJ2 * SLD};
-  double* tr_im[3] = {sc + BJ2 * SLD, sc + 3 * BJ2 * SLD, sc + 5 * BJ2 * SLD};
-  double* vh_re[2] = {sc + 6 * BJ2 * SLD, sc + 6 * BJ2 * SLD + 2 * BJ2 * HLD};
-  double* vh_im[2] = {sc + 6 * BJ2 * SLD + BJ2 * HLD, sc + 6 * BJ2 * SLD + 3 * BJ2 * HLD};
-  // every load of the staging is issued before the first store (one memory latency, not eight)
-  z64 gv[6], vv[2];
+  z64 vp[2];
+  if (w < 4) {
+    const int rh = w & 1, kh = w >> 1;
+    int p0, p1, q0, q1;
+    rr_pair(P, ps, nb, p0, p1);
+    rr_pair(Q, ps, nb, q0, q1);
+    const z64* g = Gs + (size_t)((rh ? p1 : p0) * BJ + lo) * mp + (kh ? q1 : q0) * BJ + hi;
+    const z64* vq = V + (size_t)Q * BJ2 * BJ2 + (kh * BJ + hi) * BJ2 + oJ + lo;
+    const z64* vpp = V + (size_t)P * BJ2 * BJ2 + (w * 8 + hi) * BJ2 + oI + lo;
+    z64 a[4], b[4];
 #pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    const int u = i >> 1, e = t + (i & 1) * kSolveThreads, row = e / BJ2, kk = e % BJ2;
-    int a0, a1, b0, b1;  // blocks of pairs A[u] and B[u] (uniform)
-    rr_pair(A[u], ps, nb, a0, a1);
-    rr_pair(B[u], ps, nb, b0, b1);
-    const int gr = row < BJ ? a0 * BJ + row : a1 * BJ + row - BJ;
-    const int gc = kk < BJ ? b0 * BJ + kk : b1 * BJ + kk - BJ;
-    gv[i] = Gs[(size_t)gr * mp + gc];
-  }
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int r = t / BJ, c = t % BJ, pr = h ? Q : P, off = h ? oJ : oI;
-    const bool f = h ? fQ : fP;
-    vv[h] = f ? V[(size_t)pr * BJ2 * BJ2 + r * BJ2 + off + c] : ((r == off + c) ? z64{1.0, 0.0} : z64{0.0, 0.0});
-  }
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    const int u = i >> 1, e = t + (i & 1) * kSolveThreads, row = e / BJ2, kk = e % BJ2;
-    tr_re[u][kk * SLD + row] = gv[i].re;
-    tr_im[u][kk * SLD + row] = gv[i].im;
-  }
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int r = t / BJ, c = t % BJ;
-    vh_re[h][r * HLD + c] = vv[h].re;
-    vh_im[h][r * HLD + c] = vv[h].im;
-  }
-  __syncthreads();
-  // X = T V_B restricted to columns qc: waves 0..5 (tile w / 2, rows (w % 2) * 16)
-  const int xu = w >> 1, xr = (w & 1) * BJ;
-  const bool xrun = w < 6 && (fA[xu] || fB[xu]);
-  d4 accr = {0, 0, 0, 0}, acci = {0, 0, 0, 0};
-  if (xrun) {
-    const int hb = (xu == 1) ? (sw ? 0 : 1) : (xu == 0 ? 0 : 1);  // half plane of V_B[u]
-    mmq(tr_re[xu], tr_im[xu], SLD, xr, vh_re[hb], vh_im[hb], HLD, 0, false, accr, acci);
-  }
-  __syncthreads();
-  if (xrun)  // X quadrant over the tile's own scratch: x[row][c], ld HLD
-    for (int q = 0; q < 4; ++q) {
-      const int row = xr + mfma_row_f64(lane, q), col = lane & 15;
-      tr_re[xu][row * HLD + col] = accr[q];
-      tr_im[xu][row * HLD + col] = acci[q];
-      accr[q] = 0.0;
-      acci[q] = 0.0;
+    for (int j = 0; j < 4; ++j) {
+      a[j] = g[4 * j];
+      b[j] = vq[4 * j * BJ2];
     }
-  __syncthreads();
-  // Y quadrant of tile w (waves 0..2): V_A^H X, or the quadrant of Gs itself when neither pair
-  // rotated (waves 3..5 read it)
-  double yr[4], yi[4];
-  if (w < 3) {
-    const int u = w;
-    if (fA[u] || fB[u]) {
-      const int ha = (u == 1) ? (sw ? 1 : 0) : (u == 0 ? 0 : 1);  // half plane of V_A[u]
-      mmq(vh_re[ha], vh_im[ha], HLD, 0, tr_re[u], tr_im[u], HLD, 0, true, accr, acci);
-      for (int q = 0; q < 4; ++q) {
-        yr[q] = accr[q];
-        yi[q] = acci[q];
-      }
-    }
-  } else if (w < 6) {
-    const int u = w - 3;
-    if (!(fA[u] || fB[u]))
-      for (int q = 0; q < 4; ++q) {  // element (row, col) of the quadrant, as the MFMA layout
-        const int row = mfma_row_f64(lane, q), col = lane & 15;
-        yr[q] = tr_re[u][(qc[u] + col) * SLD + qr[u] + row];
-        yi[q] = tr_im[u][(qc[u] + col) * SLD + qr[u] + row];
-      }
+    vp[0] = vpp[0];
+    vp[1] = vpp[4 * BJ2];
+    const int fP = pf[P], fQ = pf[Q];
+    // a pair that did not rotate left no V: its rotation is the identity
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (!fQ) b[j] = z64{(kh * BJ + 4 * j + hi == oJ + lo) ? 1.0 : 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (!fP) vp[j] = z64{(w * 8 + 4 * j + hi == oI + lo) ? 1.0 : 0.0, 0.0};
+    d4 accr = {0, 0, 0, 0}, acci = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mma4(a[j], b[j], accr, acci);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      xs[kh * 512 + (rh * BJ + mfma_row_f64(lane, q)) * BJ + lo] = z64{accr[q], acci[q]};
+  } else {
+    // upper elements, mirrored: the rotations leave the two triangles equal only to rounding, and
+    // what differs would add up from round to round
+    const int e = t - 256, i = e >> 4, j = e & 15, r = min(i, j), c = max(i, j);
+    z64 x = D[(size_t)P * BJ2 * BJ2 + (oI + r) * BJ2 + oI + c];
+    z64 y = D[(size_t)Q * BJ2 * BJ2 + (oJ + r) * BJ2 + oJ + c];
+    const double sg = i < j ? 1.0 : i > j ? -1.0 : 0.0;
+    x.im *= sg;
+    y.im *= sg;
+    h[i * BJ2 + j] = x;
+    h[(BJ + i) * BJ2 + BJ + j] = y;
   }
   __syncthreads();
-  // place the quadrants: tile 0 -> (I, I), tile 2 -> (J, J), tile 1 -> (I, J) and its mirror
-  const int u = (w < 3) ? w : w - 3;
-  const bool mine = (w < 3) ? (fA[u] || fB[u]) : (w < 6 && !(fA[u] || fB[u]));
-  if (mine)
-    for (int q = 0; q < 4; ++q) {
-      const int row = mfma_row_f64(lane, q), col = lane & 15;
-      if (u == 0) {
-        hr[row * JLD + col] = yr[q];
-        hi[row * JLD + col] = yi[q];
-      } else if (u == 2) {
-        hr[(BJ + row) * JLD + BJ + col] = yr[q];
-        hi[(BJ + row) * JLD + BJ + col] = yi[q];
-      } else if (!sw) {  // rows of I, columns of J; mirror conjugated
-        hr[row * JLD + BJ + col] = yr[q];
-        hi[row * JLD + BJ + col] = yi[q];
-        hr[(BJ + col) * JLD + row] = yr[q];
-        hi[(BJ + col) * JLD + row] = -yi[q];
-      } else {  // the (Q, P) tile: rows of J, columns of I; mirror conjugated
-        hr[(BJ + row) * JLD + col] = yr[q];
-        hi[(BJ + row) * JLD + col] = yi[q];
-        hr[col * JLD + BJ + row] = yr[q];
-        hi[col * JLD + BJ + row] = -yi[q];
-      }
+  if (w < 4) {
+    d4 accr = {0, 0, 0, 0}, acci = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int kk = w * 8 + 4 * j + hi;
+      mma4(cconj(vp[j]), cadd(xs[kk * BJ + lo], xs[512 + kk * BJ + lo]), accr, acci);
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ys[w * 256 + mfma_row_f64(lane, q) * BJ + lo] = z64{accr[q], acci[q]};
+  }
+  __syncthreads();
+  if (t < 256) {
+    const z64 x = cadd(cadd(ys[t], ys[256 + t]), cadd(ys[512 + t], ys[768 + t]));
+    const int i = t >> 4, j = t & 15;
+    h[i * BJ2 + BJ + j] = x;
+    h[(BJ + j) * BJ2 + i] = cconj(x);
+  }
 }
 
 // Solve step of a round: pair k of outer step `step` solves its 32x32 sub-problem (blocks I, J)
-// and writes the accumulated rotation to V + k*32*32 (row-major) with a rotated flag.  The first
-// step of an outer sweep runs a full round-robin sweep over the 32 indices (covering the pairs
-// inside each block); later steps rotate only the 16 x 16 inter-block pairs.  Over one outer
-// sweep every index pair is visited once.  With ps < 0 the sub-problem is read from Gs; otherwise
-// Gs is the matrix before the previous round's update (outer step ps, rotations Vp, flags pfp)
-// and the sub-problem is rebuilt from it (rebuild_pair), the update itself running beside this
-// solve.  LDS: six 32 x JLD planes (the rebuild's scratch aliases them).
+// and writes the accumulated rotation to V + k*32*32 (row-major, only when it rotated, as the pair's
+// flag says) and the rotated sub-problem to D + k*32*32.  The first step of an outer sweep also covers the
+// pairs inside each block; later steps rotate only the 16 x 16 inter-block pairs.  Over one outer sweep every index pair is visited
+// once.  With ps < 0 the sub-problem is read from Gs; otherwise it is rebuilt from the matrix before
+// the previous round's update (rebuild_pair), that update running beside this solve.
+// pool: 3 x 1024 elements of LDS.
+template <bool REL>
 __device__ void solve_pair(int k, const z64* __restrict__ Gs, int mp, int nb, int step, int ps,
-                           const z64* __restrict__ Vp, const int* __restrict__ pfp, double thr, double tol,
-                           double skip, int rel, double floor2, z64* __restrict__ Vout, int* __restrict__ pair_flag,
-                           int* __restrict__ any_flag, double* __restrict__ h0r, double* __restrict__ h0i,
-                           double* __restrict__ h1r, double* __restrict__ h1i, double* __restrict__ vr,
-                           double* __restrict__ vi, unsigned char* __restrict__ tab, int& any, int& need) {
-  const int t = threadIdx.x, nt = blockDim.x;
+                           const z64* __restrict__ Vp, const z64* __restrict__ Dp, const int* __restrict__ pfp,
+                           const JacobiThr& jt, z64* __restrict__ Vout, z64* __restrict__ Dout,
+                           int* __restrict__ pair_flag, int* __restrict__ any_flag, z64* __restrict__ pool,
+                           int& need) {
+  const int t = threadIdx.x;
+  z64 *h0 = pool, *h1 = pool + BJ2 * BJ2, *v = pool + 2 * BJ2 * BJ2;
   int I, J;
   rr_pair(k, step, nb, I, J);
   const bool full = (step == 0);
-  if (t == 0) {
-    any = 0;
-    need = 0;
-  }
-  if (full) build_rr_table(tab, BJ2);
-  const JacobiArgs ja{thr, tol, skip, rel, floor2};
+  if (t == 0) need = 0;
   if (ps < 0) {
-    for (int idx = t; idx < BJ2 * BJ2; idx += nt) {
+    for (int idx = t; idx < BJ2 * BJ2; idx += kSolveThreads) {
       const int i = idx / BJ2, j = idx % BJ2;
       const int gi = (i < BJ ? I * BJ + i : J * BJ + (i - BJ));
       const int gj = (j < BJ ? I * BJ + j : J * BJ + (j - BJ));
-      const z64 v = Gs[(size_t)gi * mp + gj];
-      h0r[i * JLD + j] = v.re;
-      h0i[i * JLD + j] = v.im;
+      z64 x = Gs[(size_t)gi * mp + gj];
+      if (i == j) x.im = 0.0;
+      h0[idx] = x;
     }
   } else {
-    rebuild_pair(I, J, Gs, mp, nb, ps, Vp, pfp, h0r, h0r, h0i);
-  }
-  if (full)
-    for (int idx = t; idx < BJ2 * BJ2; idx += nt) {
-      const int i = idx / BJ2, j = idx % BJ2;
-      vr[i * JLD + j] = (i == j) ? 1.0 : 0.0;
-      vi[i * JLD + j] = 0.0;
-    }
-  __syncthreads();
-  for (int idx = t; idx < BJ2 * BJ2; idx += nt) {
-    const int i = idx / BJ2, j = idx % BJ2;
-    if (i < j && (full || (i < BJ && j >= BJ))) {
-      if (rot_needed(h0r[i * JLD + i], h0r[j * JLD + j], h0r[i * JLD + j], h0i[i * JLD + j], ja)) need = 1;
-    }
+    rebuild_pair(I, J, Gs, mp, nb, ps, Vp, Dp, pfp, h1, v, h0);
   }
   __syncthreads();
-  const int run = need;
+  bool hit = false;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int idx = t + u * kSolveThreads, i = idx / BJ2, j = idx % BJ2;
+    if (i < j && (full || (i < BJ && j >= BJ)))
+      hit = hit || rot_needed<REL>(h0[i * (BJ2 + 1)].re, h0[j * (BJ2 + 1)].re, cabs2(h0[idx]), jt);
+    if (full) v[idx] = z64{(i == j) ? 1.0 : 0.0, 0.0};
+  }
+  if (hit) need = 1;
+  __syncthreads();
+  const int run = need;  // then some pair rotates: the first one met above the threshold at the latest
+  const z64* res = h0;
   if (run) {
     z64* vo = Vout + (size_t)k * BJ2 * BJ2;
     if (full) {
-      jacobi_steps(h0r, h0i, h1r, h1i, JLD, BJ, tab, BJ2 - 1, vr, vi, JLD, ja, &any);
-      for (int idx = t; idx < BJ2 * BJ2; idx += nt) {
-        const int i = idx / BJ2, j = idx % BJ2;
-        vo[idx] = z64{vr[i * JLD + j], vi[i * JLD + j]};
-      }
-    } else {
-      jacobi_ib_steps(h0r, h0i, h1r, h1i, JLD, vo, ja, &any);
+      jacobi_intra_steps<REL, true>(h0, h1, v, jt);
+      res = h1;
     }
+    jacobi_ib_steps<REL>(full ? h1 : h0, full ? h0 : h1, full ? v : nullptr, vo, jt);
   }
+  for (int idx = t; idx < BJ2 * BJ2; idx += kSolveThreads) Dout[(size_t)k * BJ2 * BJ2 + idx] = res[idx];
   if (t == 0) {
-    const int a = run ? any : 0;
-    pair_flag[k] = a;
-    if (a) atomicOr(any_flag, 1);
+    pair_flag[k] = run;
+    if (run) atomicOr(any_flag, 1);
   }
 }
 
 // One round of the block Jacobi sweep in one launch.  Blocks 0..half-1 (when step >= 0) solve the
-// sub-problems of outer step `step` (rotations to Vout, flags to pair_flag, any rotation to
-// *any_flag; a non-null any_next, the flag of the next sweep, is cleared); when ps >= 0 the previous
-// round (outer step ps, rotations Vp, flags pfp) is applied
-// beside them: the next half(half+1)/2 blocks form the tiles of Gd = V^H Gs V, the remaining
-// (mp/32) half blocks the row tiles of U <- U V.  The solves rebuild their sub-problems from Gs,
-// so no block waits for another; Gs and Gd alternate between rounds.  512 threads.
+// sub-problems of outer step `step` (rotations to Vout, solved sub-problems to Dout, flags to
+// pair_flag, any rotation to *any_flag); when ps >= 0 the previous round (outer step ps, rotations
+// Vp, solved sub-problems Dp, flags pfp) is applied beside them: the next blocks form
+// the half(half+1)/2 tiles of Gd = V^H Gs V, the remaining ones the (mp/32) half row tiles of U <- U V.  The solves rebuild their sub-problems from Gs, so no
+// block waits for another; Gs and Gd alternate between rounds.  512 threads.  With a non-null
+// prev_any that holds 0 (the sweep before rotated nothing) the round does nothing: rounds may be
+// launched before the host knows that the sweeps have converged.
+//
+// What bounds it: a round is as long as one solve.  At m = 243 a round takes 12.9 us (20.1 before): 16
+// steps of 0.42 us (0.69 before: rotations without the refinements an angle does not need and
+// complex LDS accesses), the launch, the loads and the two small products of the rebuild; the
+// rounds that start a sweep 21.5 us (28 with a round-robin order).  At m = 600 with the relative
+// criterion 16.4 us (22.0 before).
 // Launched with kJroundPad bytes of (unused) dynamic LDS, a block holds more than half of a CU's
-// 160 KB, so it holds the CU alone: a solve then never shares its SIMDs with tile updates (the
-// round's critical path), which queue on the other CUs.  That pays while the updates are few
-// (m = 768: 21.0 against 22.8 us per round) and costs once they dominate (m = 1024: 26.6
-// against 24.5 us; m = 2048: 89.9 against 59.8 us), where it is launched without the pad.
-constexpr int kJroundPad = 8192;
+// 160 KB, so a solve never shares its SIMDs with tile updates.  That pays while the updates are few
+// (m = 768: 16.6 against 17.9 ms per decomposition) and costs once they dominate (m = 1024: 29.8
+// against 27.6 ms; m = 1536: 82.0 against 70.5 ms), where the rounds go without the pad.
+constexpr int kJroundPad = 36 * 1024;
+constexpr int kPadMaxM = 896;
+// Blocks up to which two sweeps are launched per read-back of their flags (m = 81: 1.07 against
+// 1.14 ms per decomposition; from about 256 rows on it makes no difference).
+constexpr int kChunkMaxNb = 16;
+template <bool REL>
 __global__ __launch_bounds__(512) void k_jround(const z64* __restrict__ Gs, z64* __restrict__ Gd,
                                                 z64* __restrict__ Up, int mp, int nb, int step, int ps,
                                                 const double* __restrict__ trace, double tol, double skip_rel,
-                                                int rel, double floor_rel, z64* __restrict__ Vout,
+                                                double floor_rel, z64* __restrict__ Vout, z64* __restrict__ Dout,
                                                 int* __restrict__ pair_flag, int* __restrict__ any_flag,
-                                                int* __restrict__ any_next, const z64* __restrict__ Vp,
-                                                const int* __restrict__ pfp) {
-  constexpr int PL = BJ2 * JLD;
-  static_assert(6 * PL >= kRebuildLds, "the rebuild's scratch fits in the solve's planes");
-  __shared__ double pool[6 * PL];
-  __shared__ unsigned char tab[31 * 32];
-  static_assert(sizeof(pool) + sizeof(tab) + kJroundPad > 80 * 1024, "a padded block holds half a CU's LDS");
-  __shared__ int any, need;
+                                                const int* __restrict__ prev_any, const z64* __restrict__ Vp,
+                                                const z64* __restrict__ Dp, const int* __restrict__ pfp) {
+  __shared__ __align__(16) z64 pool[3 * BJ2 * BJ2];
+  __shared__ int need;
   const int half = nb / 2, nsolve = step >= 0 ? half : 0, ngt = half * (half + 1) / 2;
   int b = blockIdx.x;
-  if (any_next && b == 0 && threadIdx.x == 0) *any_next = 0;
+  if (prev_any && !*prev_any) return;
   if (b < nsolve) {
     // thresholds from the trace on the device (read by no host sync)
-    const double tr = *trace;
-    const double thr = tol * tr, skip = skip_rel * tr, floor2 = (floor_rel * tr) * (floor_rel * tr);
-    solve_pair(b, Gs, mp, nb, step, ps, Vp, pfp, thr, tol, skip, rel, floor2, Vout, pair_flag, any_flag, pool,
-               pool + PL, pool + 2 * PL, pool + 3 * PL, pool + 4 * PL, pool + 5 * PL, tab, any, need);
+    const JacobiThr jt = jacobi_thr(*trace, tol, skip_rel, REL, floor_rel);
+    solve_pair<REL>(b, Gs, mp, nb, step, ps, Vp, Dp, pfp, jt, Vout, Dout, pair_flag, any_flag, pool, need);
     return;
   }
   b -= nsolve;
-  if (b < ngt)
-    g_tile(Gs, Gd, mp, nb, ps, Vp, pfp, b, pool, pool + BJ2 * SLD, pool + 2 * BJ2 * SLD, pool + 3 * BJ2 * SLD);
+  const int sub = threadIdx.x >> 8, ngb = (ngt + kTilesPerBlock - 1) / kTilesPerBlock;
+  if (b < ngb)
+    g_tile(Gs, Gd, mp, nb, ps, Vp, Dp, pfp, b * kTilesPerBlock + sub, ngt, pool + sub * BJ2 * BJ2);
   else
-    u_tile(Up, mp, nb, ps, Vp, pfp, b - ngt, pool, pool + BJ2 * SLD, pool + 2 * BJ2 * SLD, pool + 3 * BJ2 * SLD);
+    u_tile(Up, mp, nb, ps, Vp, pfp, (b - ngb) * kTilesPerBlock + sub, (mp / BJ2) * half);
 }
 
 __global__ void k_pad_copy(const z64* __restrict__ G, int m, int ldg, z64* __restrict__ Gp, int mp,
@@ -1087,6 +582,8 @@ __global__ void k_pad_copy(const z64* __restrict__ G, int m, int ldg, z64* __res
   Gp[idx] = (i < m && j < m) ? G[(size_t)i * ldg + j] : z64{0.0, 0.0};
   Up[idx] = (i == j) ? z64{1.0, 0.0} : z64{0.0, 0.0};
 }
+
+constexpr int kSweepFlags = 128;  // one rotation flag per sweep
 
 __global__ void k_trace(const z64* __restrict__ Gp, int m, int mp, double* out, int* __restrict__ sweep_flags) {
   __shared__ double red[256];
@@ -1101,24 +598,23 @@ __global__ void k_trace(const z64* __restrict__ Gp, int m, int mp, double* out, 
   if (threadIdx.x == 0) {
     out[0] = red[0];
     reinterpret_cast<int*>(out + 1)[0] = 0;  // pre-check flag, set by k_offdiag_check
-    sweep_flags[0] = 0;                      // the sweeps' rotation flags (even and odd sweeps)
-    sweep_flags[1] = 0;
   }
+  if (threadIdx.x < kSweepFlags) sweep_flags[threadIdx.x] = 0;
 }
 
 // Pre-check of a decomposition: sets *flag when some pair (i < j < m) of Gp passes the rotation
 // test, with the thresholds the sweeps would use (from the trace in out[0] of k_trace).
 __global__ void k_offdiag_check(const z64* __restrict__ Gp, int m, int mp, const double* __restrict__ trace_in,
                                 double tol, double skip_rel, int rel, double floor_rel, int* __restrict__ flag) {
-  const double trace = *trace_in;
-  const JacobiArgs ja{tol * trace, tol, skip_rel * trace, rel, (floor_rel * trace) * (floor_rel * trace)};
+  const JacobiThr jt = jacobi_thr(*trace_in, tol, skip_rel, rel, floor_rel);
   const size_t total = (size_t)m * m;
   int hit = 0;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
     const int i = (int)(e / m), j = (int)(e % m);
     if (i < j) {
       const z64 g = Gp[(size_t)i * mp + j];
-      if (rot_needed(Gp[(size_t)i * mp + i].re, Gp[(size_t)j * mp + j].re, g.re, g.im, ja)) hit = 1;
+      const double a = Gp[(size_t)i * mp + i].re, b = Gp[(size_t)j * mp + j].re;
+      if (rel ? rot_needed<true>(a, b, cabs2(g), jt) : rot_needed<false>(a, b, cabs2(g), jt)) hit = 1;
     }
   }
   if (hit) atomicOr(flag, 1);
@@ -1315,8 +811,8 @@ inline unsigned blocks_for(size_t n, int bs) { return (unsigned)((n + bs - 1) / 
 // ===================================================================================== launchers
 void linalg_set_attributes() {
   // the rounds' optional LDS pad is dynamic shared memory; static plus dynamic exceeds 64 KB
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_jround), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kJroundPad);
+  for (const void* f : {reinterpret_cast<const void*>(k_jround<false>), reinterpret_cast<const void*>(k_jround<true>)})
+    (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kJroundPad);
   (void)hipGetLastError();
 }
 
@@ -1352,25 +848,21 @@ void launch_zgemm(hipStream_t s, int opa, int opb, int M, int N, int K, const z6
 
 void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu, double* lam, int rel, EigWork& w,
                    DevStatus* st, int* host_sweeps, bool precheck) {
-  const double tol = rel ? 1e-14 : 4e-15;
-  // Relative pass: pairs whose diagonal entries are both below 1e-28 lambda_max (lambda_max >=
-  // trace / m) are left alone.  They lie two decades below the rank floor (sigma^2 = 1e-26
-  // sigma_0^2), so no decision depends on them, and exact null directions sit at the rounding
-  // level (~1e-32 of the trace), where a relative criterion cannot be met.
-  const double skip = rel ? 1e-28 / (double)m : 0.0;
-  // Relative pass: an off-diagonal entry of at most 1e-29 trace / m (<= 1e-29 lambda_max) counts
-  // as converged.  On exactly rank-deficient matrices the rounding of the rotations keeps
-  // entries of that size alive between directions at the rounding level, where a relative
-  // criterion is never met (the pass then ran out of sweeps); an eigenvalue at or above the rank
-  // floor (1e-26 lambda_max) moves by at most 1e-3 of itself because of such an entry.
-  const double floor_rel = rel ? 1e-29 / (double)m : 0.0;
-  // Sweeps grow with m on these Grams: up to ~20 at m = 768, 19-26 at m = 3072, where one
-  // decomposition needed more than 40 (every sub-problem still rotating for the first ~20
-  // sweeps, then a steady decay).
-  const int max_sweeps = m > 1024 ? 100 : 40;
+  const JacobiCrit cr = jacobi_crit(m, rel);
+  const double tol = cr.tol, skip = cr.skip_rel, floor_rel = cr.floor_rel;
+  const int max_sweeps = cr.max_sweeps;
   if (m <= kSmallEig) {
-    hipLaunchKernelGGL(k_jacobi_small, dim3(1), dim3(256), 0, s, G, ldg, m, U, ldu, lam, rel, tol, skip, floor_rel,
-                       max_sweeps, st);
+#define GC_JSMALL(HM, REL)                                                                                           \
+  hipLaunchKernelGGL((k_jacobi_small<HM, REL>), dim3(1), dim3(2 * HM * HM), 0, s, G, ldg, m, U, ldu, lam, cr, st)
+    if (m <= 16 && rel)
+      GC_JSMALL(8, true);
+    else if (m <= 16)
+      GC_JSMALL(8, false);
+    else if (rel)
+      GC_JSMALL(16, true);
+    else
+      GC_JSMALL(16, false);
+#undef GC_JSMALL
     GC_LAUNCH_CHECK();
     if (host_sweeps) *host_sweeps = -1;
     return;
@@ -1384,10 +876,9 @@ void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu,
   hipLaunchKernelGGL(k_pad_copy, dim3(blocks_for((size_t)mp * mp, 256)), dim3(256), 0, s, G, m, ldg, Gp, mp, Up);
   GC_LAUNCH_CHECK();
   double* d_trace = reinterpret_cast<double*>(w.flags + 512);
-  // rotation flag of sweep sw: sweep_flag(sw); the first round of a sweep clears the next sweep's
-  // (written by no round of this sweep, and read by the host two sweeps ago), k_trace both
-  auto sweep_flag = [&](int sw) { return w.flags + 300 + (sw & 1); };
-  hipLaunchKernelGGL(k_trace, dim3(1), dim3(256), 0, s, Gp, m, mp, d_trace, sweep_flag(0));
+  int* sweep_flags = w.flags + 300;  // rotation flag of each sweep, cleared by k_trace
+  GC_CHECK(max_sweeps <= kSweepFlags, GCAMPS_ECAPACITY, "more sweeps than rotation flags");
+  hipLaunchKernelGGL(k_trace, dim3(1), dim3(256), 0, s, Gp, m, mp, d_trace, sweep_flags);
   GC_LAUNCH_CHECK();
   if (precheck) {
     hipLaunchKernelGGL(k_offdiag_check, dim3(blocks_for((size_t)m * m, 256)), dim3(256), 0, s, Gp, m, mp, d_trace, tol,
@@ -1412,49 +903,57 @@ void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu,
   const int half = nb / 2;
   int sweeps = 0;
   bool conv = false;
-  // rotation and flag buffers of round r: V + (r & 1) * half * 32 * 32, flags + 1 + (r & 1) * 128
-  // (half <= m_pad / 32 <= 128; the V region holds m_pad / 16 blocks of 32 x 32 and more)
+  // rotation, solved-sub-problem and flag buffers of round r: V and D + (r & 1) * half * 32 * 32,
+  // flags + 1 + (r & 1) * 128 (half <= m_pad / 32 <= 128; the V and D regions hold m_pad / 16 blocks of
+  // 32 x 32 and more)
   GC_CHECK(half <= 128, GCAMPS_ECAPACITY, "eigensolver: matrix side exceeds 4096");
   auto vbuf = [&](long r) { return w.V + (size_t)(r & 1) * half * BJ2 * BJ2; };
+  auto dbuf = [&](long r) { return w.D + (size_t)(r & 1) * half * BJ2 * BJ2; };
   auto fbuf = [&](long r) { return w.flags + 1 + (r & 1) * 128; };
   // the matrix after round r - 1's update lives in gbuf(r): round r (r >= 1) solves from gbuf(r - 1)
   // and the previous round's rotations while it writes gbuf(r)
   auto gbuf = [&](long r) { return (r & 1) ? Gp1 : Gp; };
-  const int gtiles = half * (half + 1) / 2, utiles = (mp / BJ2) * half;
+  auto tile_blocks = [](int tiles) { return (tiles + kTilesPerBlock - 1) / kTilesPerBlock; };
+  const int gtiles = tile_blocks(half * (half + 1) / 2), utiles = tile_blocks((mp / BJ2) * half);
   // a whole CU per block while the tile updates are few (see k_jround)
-  const size_t pad = mp <= 896 ? kJroundPad : 0;
+  const size_t pad = mp <= kPadMaxM ? kJroundPad : 0;
+  // The host reads the sweeps' flags back after `chunk` sweeps.  While a sweep is short, two are
+  // launched at a time: a sweep launched past convergence returns at once (prev_any), which costs
+  // less than a read-back per sweep.
+  const int chunk = nb <= kChunkMaxNb ? 2 : 1;
   long round = 0;  // rounds launched so far
   int prev_step = -1;
-  for (int sw = 0; sw < max_sweeps; ++sw) {
-    for (int step = 0; step < nb - 1; ++step, ++round) {
-      const bool upd = round > 0;
-      hipLaunchKernelGGL(k_jround, dim3(half + (upd ? gtiles + utiles : 0)), dim3(kSolveThreads), pad, s,
-                         upd ? gbuf(round - 1) : Gp, gbuf(round), Up, mp, nb, step, upd ? prev_step : -1, d_trace,
-                         tol, skip, rel, floor_rel, vbuf(round), fbuf(round), sweep_flag(sw),
-                         step == 0 ? sweep_flag(sw + 1) : nullptr, upd ? vbuf(round - 1) : nullptr,
-                         upd ? fbuf(round - 1) : nullptr);
-      GC_LAUNCH_CHECK();
-      prev_step = step;
-    }
-    ++sweeps;
-    // (A check after each sweep for pairs left to rotate, to skip the sweep that only confirms
-    // convergence, costs as much here as that sweep: its rounds are cheap when nothing rotates.)
-    int local = 0;
-    int* hany = w.host_rb ? reinterpret_cast<int*>(w.host_rb) : &local;  // pinned when given
-    GC_HIP(hipMemcpyAsync(hany, sweep_flag(sw), sizeof(int), hipMemcpyDeviceToHost, s));
+  while (!conv && sweeps < max_sweeps) {
+    for (int c = 0; c < chunk; ++c)
+      for (int step = 0; step < nb - 1; ++step, ++round) {
+        const bool upd = round > 0;
+        const int sw = sweeps + c;
+#define GC_JROUND(REL)                                                                                               \
+  hipLaunchKernelGGL((k_jround<REL>), dim3(half + (upd ? gtiles + utiles : 0)), dim3(kSolveThreads), pad, s,         \
+                     upd ? gbuf(round - 1) : Gp, gbuf(round), Up, mp, nb, step, upd ? prev_step : -1, d_trace, tol,  \
+                     skip, floor_rel, vbuf(round), dbuf(round), fbuf(round), sweep_flags + sw,                       \
+                     c > 0 ? sweep_flags + sw - 1 : nullptr, upd ? vbuf(round - 1) : nullptr,                        \
+                     upd ? dbuf(round - 1) : nullptr, upd ? fbuf(round - 1) : nullptr)
+        if (rel)
+          GC_JROUND(true);
+        else
+          GC_JROUND(false);
+#undef GC_JROUND
+        GC_LAUNCH_CHECK();
+        prev_step = step;
+      }
+    int local[2] = {0, 0};
+    int* hany = w.host_rb ? reinterpret_cast<int*>(w.host_rb) : local;  // pinned when given
+    GC_HIP(hipMemcpyAsync(hany, sweep_flags + sweeps, chunk * sizeof(int), hipMemcpyDeviceToHost, s));
     GC_HIP(hipStreamSynchronize(s));
-    const int any = *hany;
-    if (!any) {
-      conv = true;
-      break;
+    for (int c = 0; c < chunk && !conv; ++c) {
+      ++sweeps;
+      conv = hany[c] == 0;
     }
   }
-  // the last round's update: G into gbuf(round), U in place
-  hipLaunchKernelGGL(k_jround, dim3(gtiles + utiles), dim3(kSolveThreads), pad, s, gbuf(round - 1), gbuf(round), Up, mp,
-                     nb, -1, prev_step, d_trace, tol, skip, rel, floor_rel, nullptr, nullptr, nullptr, nullptr,
-                     vbuf(round - 1), fbuf(round - 1));
-  GC_LAUNCH_CHECK();
-  const z64* Gf = gbuf(round);
+  // The last sweep rotated nothing, so its last round has nothing to apply: the matrix is what that
+  // round's launch wrote.
+  const z64* Gf = gbuf((long)sweeps * (nb - 1) - 1);
   hipLaunchKernelGGL(k_unpad, dim3(blocks_for((size_t)m * m, 256)), dim3(256), 0, s, Gf, Up, m, mp, U, ldu, lam);
   GC_LAUNCH_CHECK();
   GC_CHECK(conv, GCAMPS_ENUMERIC,
