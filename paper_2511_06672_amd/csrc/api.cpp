@@ -279,6 +279,10 @@ int32_t gcamps_init(const gcamps_config* cfg, void* dev_workspace, size_t bytes,
     c->pinned_bytes = std::max<size_t>(1 << 20, (size_t)n * 2401 * 4 + 4096);
     GC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->pinned), c->pinned_bytes, hipHostMallocDefault));
     GC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->rb), kRbBytes, hipHostMallocDefault));
+    GC_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&c->rb_dev), c->rb, 0));
+    int clock_khz = 0;
+    GC_HIP(hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev));
+    c->tick_ms = 1.0 / std::max(1, clock_khz);
     c->eig.host_rb = reinterpret_cast<double*>(c->rb + kRbEig);
     GC_HIP(hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming));
     GC_HIP(hipEventCreate(&c->ev0));

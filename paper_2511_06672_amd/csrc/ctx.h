@@ -123,6 +123,8 @@ struct gcamps_ctx {
   // pinned staging
   char* pinned = nullptr;
   char* rb = nullptr;  // pinned read-back block (status, Cholesky state, eigensolver flags)
+  char* rb_dev = nullptr;  // the same block as the device addresses it
+  double tick_ms = 0.0;    // one tick of the device's wall clock in ms
   size_t pinned_bytes = 0;
   hipEvent_t stage_ev = nullptr;
   bool stage_pending = false;
@@ -208,6 +210,7 @@ struct gcamps_ctx {
     const int m = wide ? p : q, kW = wide ? q : p;
     GC_CHECK((size_t)m <= lay.mcap && (size_t)m * kW <= lay.slot_elems, GCAMPS_ECAPACITY,
              "factorisation exceeds workspace capacity");
+    if (m <= kSmallEig && kW <= kSplitSmallMaxK) return split_small(M, p, q, mode, left_ortho, Lout, Rout);
     const z64 one = {1.0, 0.0};
     GC_HIP(hipEventRecord(evf0, stream));
     auto gram = [&]() {
@@ -272,14 +275,8 @@ struct gcamps_ctx {
         std::swap(B, B2);
       }
     }
-    // recorded decision: kept rank in the low bits, bit 30 = the accurate second pass ran
-    int force_k = 0, force_pass2 = -1;
-    if (rank_frz) {
-      GC_CHECK(rank_pos < rank_frz->size(), GCAMPS_EINVAL, "frozen replay ran past the recorded ranks");
-      const int32_t v = (*rank_frz)[rank_pos++];
-      force_k = v & kRankMask;
-      force_pass2 = (v >> kPass2Bit) & 1;
-    }
+    int force_k, force_pass2;
+    forced_decision(force_k, force_pass2);
     launch_rownorm2(stream, B, nb, kW, kW, sig2);
     launch_trunc(stream, sig2, nb, cfg.cutoff, cfg.chi_max, mode, force_k, perm, sig, st, tail);
     GC_HIP(hipEventRecord(evf1, stream));
@@ -307,37 +304,79 @@ struct gcamps_ctx {
     {  // both events have completed: read_status synchronised the stream after evf1
       float fms = 0.0f;
       GC_HIP(hipEventElapsedTime(&fms, evf0, evf1));
-      const double pl = std::max(p, q), ql = std::min(p, q);
-      kstats[0] += 1;
-      kstats[1] += 4.0 * (6.0 * pl * ql * ql + 20.0 * ql * ql * ql);
-      kstats[2] += fms;
+      count_fact(p, q, fms);
       if (trace_fact)  // GCAMPS_TRACE_FACT: one line per factorisation on stderr
         std::fprintf(stderr, "gcamps-fact m=%d k=%d mode=%d reduce=%d basis=%d kept=%d pass2=%d ms=%.3f sweeps=%d/%d/%d\n",
                      m, kW, mode, reduced ? 1 : 0, nb, h.kept, pass2 ? 1 : 0, fms, sw_h, sw_main, sw_p2);
     }
-    if (rank_rec) rank_rec->push_back(h.kept | (pass2 ? (1 << kPass2Bit) : 0));
-    if (tape) {
-      FactRec& f = last_fact;
-      f.m = m;
-      f.kW = kW;
-      f.k = h.kept;
-      f.p = p;
-      f.q = q;
-      f.wide = wide ? 1 : 0;
-      f.left = left_ortho;
-      f.renorm = mode == 0 ? 1 : 0;
-      f.U = arena->take<z64>((size_t)m * m);
-      f.B = arena->take<z64>((size_t)m * kW);
-      f.sig = arena->take<double>(m);
-      f.perm = arena->take<int>(m);
-      launch_copy(stream, f.U, U, (size_t)m * m);
-      launch_copy(stream, f.B, B, (size_t)m * kW);
-      GC_HIP(hipMemcpyAsync(f.sig, sig, m * sizeof(double), hipMemcpyDeviceToDevice, stream));
-      GC_HIP(hipMemcpyAsync(f.perm, perm, m * sizeof(int), hipMemcpyDeviceToDevice, stream));
-    }
+    record_fact(h, pass2, mode, left_ortho, p, q);
     launch_emit(stream, wide ? 1 : 0, left_ortho, mode == 0 ? 1 : 0, p, q, h.kept, U, ldu, B, kW, perm, sig, Lout,
                 Rout);
     last_basis = nb;
+    return h;
+  }
+
+  // Recorded decision of the next factorisation in a frozen replay: kept rank in the low bits, bit 30 =
+  // the accurate second pass ran.  force_k = 0 and force_pass2 = -1 outside replays.
+  void forced_decision(int& force_k, int& force_pass2) {
+    force_k = 0;
+    force_pass2 = -1;
+    if (!rank_frz) return;
+    GC_CHECK(rank_pos < rank_frz->size(), GCAMPS_EINVAL, "frozen replay ran past the recorded ranks");
+    const int32_t v = (*rank_frz)[rank_pos++];
+    force_k = v & kRankMask;
+    force_pass2 = (v >> kPass2Bit) & 1;
+  }
+  void count_fact(int p, int q, double ms) {
+    const double pl = std::max(p, q), ql = std::min(p, q);
+    kstats[0] += 1;
+    kstats[1] += 4.0 * (6.0 * pl * ql * ql + 20.0 * ql * ql * ql);
+    kstats[2] += ms;
+  }
+  // The decision into the rank log and the factorisation's basis (U, B, sig, perm) onto the tape.
+  void record_fact(const DevStatus& h, bool pass2, int mode, int left_ortho, int p, int q) {
+    if (rank_rec) rank_rec->push_back(h.kept | (pass2 ? (1 << kPass2Bit) : 0));
+    if (!tape) return;
+    const int m = std::min(p, q), kW = std::max(p, q);
+    FactRec& f = last_fact;
+    f.m = m;
+    f.kW = kW;
+    f.k = h.kept;
+    f.p = p;
+    f.q = q;
+    f.wide = p <= q ? 1 : 0;
+    f.left = left_ortho;
+    f.renorm = mode == 0 ? 1 : 0;
+    f.U = arena->take<z64>((size_t)m * m);
+    f.B = arena->take<z64>((size_t)m * kW);
+    f.sig = arena->take<double>(m);
+    f.perm = arena->take<int>(m);
+    launch_copy(stream, f.U, U, (size_t)m * m);
+    launch_copy(stream, f.B, B, (size_t)m * kW);
+    GC_HIP(hipMemcpyAsync(f.sig, sig, m * sizeof(double), hipMemcpyDeviceToDevice, stream));
+    GC_HIP(hipMemcpyAsync(f.perm, perm, m * sizeof(int), hipMemcpyDeviceToDevice, stream));
+  }
+  // factorize() of a matrix whose smaller side fits one workgroup: one launch, which also leaves
+  // the status in the pinned read-back block.
+  DevStatus split_small(const z64* M, int p, int q, int mode, int left_ortho, z64* Lout, z64* Rout) {
+    const int m = std::min(p, q), kW = std::max(p, q);
+    int force_k, force_pass2;
+    forced_decision(force_k, force_pass2);
+    SplitArgs a{M, p, q, left_ortho, mode == 0 ? 1 : 0, force_pass2, {cfg.cutoff, cfg.chi_max, mode, force_k},
+                U, B, Lout, Rout, sig, perm, st, reinterpret_cast<DevStatus*>(rb_dev + kRbStatus)};
+    launch_split_small(stream, a);
+    GC_HIP(hipStreamSynchronize(stream));
+    DevStatus h;
+    std::memcpy(&h, rb + kRbStatus, sizeof(DevStatus));
+    GC_CHECK(h.converged, GCAMPS_ENUMERIC, "eigensolver did not converge");
+    GC_CHECK(std::isfinite(h.eps) && h.kept >= 1, GCAMPS_ENUMERIC, "factorisation produced non-finite values");
+    stats[5] += 8.0 * (double)m * m * kW * 2.0 * (h.pass2 ? 2 : 1);
+    count_fact(p, q, h.ticks * tick_ms);
+    if (trace_fact)
+      std::fprintf(stderr, "gcamps-fact m=%d k=%d mode=%d reduce=0 basis=%d kept=%d pass2=%d ms=%.3f sweeps=0/%d/0\n", m, kW,
+                   mode, m, h.kept, h.pass2, h.ticks * tick_ms, h.sweeps);
+    record_fact(h, h.pass2 != 0, mode, left_ortho, p, q);
+    last_basis = m;
     return h;
   }
 

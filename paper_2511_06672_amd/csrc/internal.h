@@ -90,6 +90,7 @@ constexpr int kMaxN = 128;
 constexpr double kNearTieLowp = 1e-4;  // smallest re-score window with FP32 / split-BF16 scoring
 constexpr size_t kDenseMax = size_t(1) << 16;  // largest d^n of the dense (validation) state
 constexpr int kSmallEig = 32;   // largest m handled by the single-workgroup eigensolver
+constexpr int kSplitSmallMaxK = 512;  // largest larger side of a one-launch split (kernels_split.hip)
 // Truncating splits with kReduceMinM < m <= kReduceMaxM take the pivoted-Cholesky path: below,
 // its fixed costs (panel launches, two more eigensolves) outweigh what it saves (measured on the
 // headline workload: m = 81 0.95 against 0.62 ms, m = 243 3.1 against 2.1 ms); above, it is
@@ -108,13 +109,13 @@ struct DevStatus {
   int32_t converged;   // eigensolver convergence flag (1 = ok)
   int32_t need_pass2;  // factorisation needs the accurate second pass
   int32_t sweeps;      // eigensolver sweeps used
-  int32_t pad;
+  int32_t pass2;       // small split: the second pass ran
   double eps;          // discarded relative weight
   double smin_lp;      // minimum low-precision score
   double s2min;        // minimum FP64 score
   double norm2;        // |Theta|^2 of the scored tensor
   double lam_max;      // largest Gram eigenvalue
-  double pad2;
+  int64_t ticks;       // small split: wall-clock ticks from the Gram to the truncation rule
 };
 
 // Weyl string result of the commutation step (device layout).

@@ -77,6 +77,25 @@ void launch_trunc(hipStream_t s, const double* sig2, int m, double cutoff, int c
 void launch_emit(hipStream_t s, int wide, int left_ortho, int renorm, int p, int q, int kept,
                  const z64* U, int ldu, const z64* B, int ldb, const int* perm, const double* sig,
                  z64* L, z64* R);
+// The whole split of a matrix M (p x q, smaller side m <= kSmallEig) in one launch: M -> L (p x kept),
+// R (kept x q) as launch_emit writes them, by the rule of launch_trunc, with the relative-accuracy second
+// pass where a kept value calls for it (force_pass2: -1, or the recorded decision).  U (m x m), B (m x the
+// larger side), sig and perm are left as the general factorisation leaves them; *st and *host_st
+// (pinned host memory as the device addresses it) get the decision, with the selection's fields of *st kept.
+struct SplitRule {
+  double cutoff;
+  int chi_max, mode, force_k;
+};
+struct SplitArgs {
+  const z64* M;
+  int p, q, left, renorm, force_pass2;
+  SplitRule rule;
+  z64 *U, *B, *L, *R;
+  double* sig;
+  int* perm;
+  DevStatus *st, *host_st;
+};
+void launch_split_small(hipStream_t s, const SplitArgs& a);
 void launch_copy(hipStream_t s, z64* dst, const z64* src, size_t count);
 void launch_fill_identity(hipStream_t s, z64* U, int m, int ld);
 
