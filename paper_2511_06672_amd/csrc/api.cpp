@@ -163,6 +163,7 @@ Layout make_layout(const gcamps_config& c) {
   if (L.dense_dim > kDenseMax) L.dense_dim = 0;
   L.off_dense = take(L.dense_dim * (4 * sizeof(z64) + 2 * sizeof(int) + (size_t)c.n));
   L.off_pcst = take(sizeof(PcState));
+  L.off_chol = take(sizeof(CholState));
   L.total = o;
   return L;
 }
@@ -276,6 +277,7 @@ int32_t gcamps_init(const gcamps_config* cfg, void* dev_workspace, size_t bytes,
     c->dluts = reinterpret_cast<uint32_t*>(w + lay.off_luts);
     c->dsites = reinterpret_cast<int*>(w + lay.off_sites);
     c->pcst = reinterpret_cast<PcState*>(w + lay.off_pcst);
+    c->chst = reinterpret_cast<CholState*>(w + lay.off_chol);
     c->pinned_bytes = std::max<size_t>(1 << 20, (size_t)n * 2401 * 4 + 4096);
     GC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->pinned), c->pinned_bytes, hipHostMallocDefault));
     GC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->rb), kRbBytes, hipHostMallocDefault));

@@ -23,7 +23,7 @@ struct Layout {
   size_t off_slots, off_theta, off_G, off_U, off_Z, off_Utmp, off_B, off_B2, off_sig2, off_sig, off_lam,
       off_perm, off_eigG, off_eigV, off_eigD, off_flags, off_s2, off_s2w, off_wlist, off_partial, off_nbuf, nbuf_bytes, off_q64, off_q32,
       off_rtab, off_qinv, off_tab, off_target, off_weyl, off_err, off_status, off_luts, off_sites, off_dense,
-      dense_dim, off_pcst, total;
+      dense_dim, off_pcst, off_chol, total;
 };
 
 Layout make_layout(const gcamps_config& c);
@@ -100,6 +100,7 @@ struct gcamps_ctx {
   DevWeyl* weyl = nullptr;
   DevStatus* st = nullptr;
   PcState* pcst = nullptr;  // rank-reduction state (device)
+  CholState* chst = nullptr;  // pivots of an exact move (device)
   void* scratch_dev = nullptr;  // device address of the library's static scratch on this ctx's GPU
   z64 *theta = nullptr, *G = nullptr, *U = nullptr, *Z = nullptr, *Utmp = nullptr, *B = nullptr, *B2 = nullptr;
   double *sig2 = nullptr, *sig = nullptr, *lam = nullptr, *s2 = nullptr, *s2w = nullptr, *partial = nullptr;
@@ -184,7 +185,8 @@ struct gcamps_ctx {
     GC_HIP(hipEventRecord(stage_ev, stream));
     stage_pending = true;
   }
-  static_assert(sizeof(DevStatus) <= kRbPcState && kRbPcState + sizeof(PcState) <= kRbEig &&
+  static_assert(sizeof(DevStatus) <= kRbPcState && kRbPcState + sizeof(PcState) <= kRbChol &&
+                    kRbChol + sizeof(CholState) <= kRbEig &&
                     kRbWeyl + sizeof(DevWeyl) <= kRbWeylErr && kRbWeylErr + sizeof(int) <= kRbBytes,
                 "read-back block layout");
   void read_status(DevStatus& h) {  // through pinned memory: no staging copy
@@ -211,6 +213,8 @@ struct gcamps_ctx {
     GC_CHECK((size_t)m <= lay.mcap && (size_t)m * kW <= lay.slot_elems, GCAMPS_ECAPACITY,
              "factorisation exceeds workspace capacity");
     if (m <= kSmallEig && kW <= kSplitSmallMaxK) return split_small(M, p, q, mode, left_ortho, Lout, Rout);
+    DevStatus mv{};
+    if (mode == 1 && !tape && !rank_rec && !rank_frz && move_full_rank(M, p, q, left_ortho, Lout, Rout, mv)) return mv;
     const z64 one = {1.0, 0.0};
     GC_HIP(hipEventRecord(evf0, stream));
     auto gram = [&]() {
@@ -314,6 +318,73 @@ struct gcamps_ctx {
                 Rout);
     last_basis = nb;
     return h;
+  }
+
+  // factorize() in mode 1 of a matrix of full rank: true when the pivots of the Gram's Cholesky
+  // factorisation show full rank (see kernels_chol.hip).  A pivot of kMovePivot times the largest diagonal
+  // entry leaves X K^-H orthonormal to about m 2^-53 / kMovePivot, and two Newton-Schulz steps take a gap
+  // of kMoveGap below rounding.  Gradient recordings and replays keep the eigenbasis their reverse sweep
+  // needs.
+  bool move_full_rank(const z64* M, int p, int q, int left_ortho, z64* Lout, z64* Rout, DevStatus& h) {
+    constexpr double kMovePivot = 1e-9, kMoveGap = 1e-5;
+    const bool wide = p <= q;
+    const int m = wide ? p : q, P = wide ? q : p;
+    const bool trivial = wide == (left_ortho != 0);  // the orthonormal factor is the square one
+    const z64 one = {1.0, 0.0};
+    z64* A = reinterpret_cast<z64*>(ws + lay.off_B);  // B and B2 are adjacent: room for m + P rows
+    if ((size_t)(m + P) * m > 2 * lay.slot_elems) return false;
+    GC_HIP(hipEventRecord(evf0, stream));
+    if (wide)
+      launch_zgemm(stream, 0, 1, m, m, q, M, q, M, q, A, m, one, 0, 1);
+    else
+      launch_zgemm(stream, 1, 0, m, m, p, M, q, M, q, A, m, one, 0, 1);
+    z64* X = A + (size_t)m * m;
+    if (!trivial) {
+      if (wide)
+        launch_conj_transpose(stream, M, p, q, X);
+      else
+        launch_copy(stream, X, M, (size_t)P * m);
+    }
+    launch_cholesky(stream, A, m, trivial ? m : m + P, chst);
+    if (trivial) {
+      launch_fill_identity(stream, left_ortho ? Lout : Rout, m, m);
+      launch_copy(stream, left_ortho ? Rout : Lout, M, (size_t)p * q);
+    } else {
+      z64* Xn = left_ortho ? Lout : Rout;  // P x m
+      for (int it = 0; it < 2; ++it) {     // Newton-Schulz: X <- X (3 I - X^H X) / 2
+        launch_zgemm(stream, 1, 0, m, m, P, X, m, X, m, G, m, one, 0, 1);
+        if (it == 0) launch_identity_gap(stream, G, m, chst);
+        launch_scaled_copy(stream, Xn, X, (size_t)P * m, 1.5);
+        launch_zgemm(stream, 0, 0, P, m, m, X, m, G, m, Xn, m, z64{-0.5, 0.0}, 1, 0);
+        std::swap(X, Xn);
+      }
+      if (left_ortho) {
+        launch_copy(stream, Lout, X, (size_t)P * m);
+        launch_zgemm(stream, 1, 0, m, q, p, X, m, M, q, Rout, q, one, 0, 0);
+      } else {
+        launch_zgemm(stream, 0, 0, p, m, q, M, q, X, m, Lout, m, one, 0, 0);
+        launch_conj_transpose(stream, X, P, m, Rout);
+      }
+    }
+    GC_HIP(hipEventRecord(evf1, stream));
+    GC_HIP(hipMemcpyAsync(rb + kRbChol, chst, sizeof(CholState), hipMemcpyDeviceToHost, stream));
+    GC_HIP(hipStreamSynchronize(stream));
+    CholState cs;
+    std::memcpy(&cs, rb + kRbChol, sizeof(CholState));
+    if (!(cs.dmax > 0.0 && cs.dmin >= kMovePivot * cs.dmax && cs.emax <= kMoveGap)) return false;
+    h = DevStatus{};
+    h.kept = m;
+    h.converged = 1;
+    h.lam_max = cs.dmax;
+    stats[5] += 8.0 * (double)m * m * P * 2.0;
+    float fms = 0.0f;
+    GC_HIP(hipEventElapsedTime(&fms, evf0, evf1));
+    count_fact(p, q, fms);
+    if (trace_fact)
+      std::fprintf(stderr, "gcamps-fact m=%d k=%d mode=1 reduce=0 basis=%d kept=%d pass2=0 ms=%.3f sweeps=0/0/0\n", m, P, m,
+                   m, fms);
+    last_basis = m;
+    return true;
   }
 
   // Recorded decision of the next factorisation in a frozen replay: kept rank in the low bits, bit 30 =

@@ -58,9 +58,9 @@ inline JacobiCrit jacobi_crit(int m, int rel) {
   return JacobiCrit{rel ? 1e-14 : 2e-15, rel ? 1e-28 / (double)m : 0.0, rel ? 1e-29 / (double)m : 0.0,
                     m > 1024 ? 100 : 40};
 }
-// Offsets in a context's pinned read-back block: device status, Cholesky state, eigensolver
-// slots, conjugated Weyl string and its error flag.
-constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbEig = 512, kRbWeyl = 1024, kRbWeylErr = 2560, kRbBytes = 4096;
+// Offsets in a context's pinned read-back block: device status, pivoted and plain Cholesky
+// states, eigensolver slots, conjugated Weyl string and its error flag.
+constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbChol = 384, kRbEig = 512, kRbWeyl = 1024, kRbWeylErr = 2560, kRbBytes = 4096;
 // precheck: test every pair against the rotation criterion first and return U = I, lam =
 // diag(G) without a sweep when none qualifies (for matrices expected to be diagonal already,
 // e.g. a Rayleigh-Ritz step; the result equals what one sweep that rotates nothing leaves).
@@ -116,6 +116,23 @@ void launch_normalize_cols(hipStream_t s, z64* X, int m, int r, int ldx);
 // X (m x r, ld r) replaced by its polar factor by `iters` Newton-Schulz steps (X nearly
 // orthonormal); Xn (m x r) and S (r x r) are scratch.
 void orthonormalize_cols(hipStream_t s, z64* X, z64* Xn, z64* S, int m, int r, int iters);
+
+// dst = f * src.
+void launch_scaled_copy(hipStream_t s, z64* dst, const z64* src, size_t count, double f);
+
+// ------------------------------------------------------------------ exact moves (kernels_chol.hip)
+// Pivots of a Cholesky factorisation (largest diagonal entry of the matrix, smallest pivot) and the
+// largest entry of |S - I| seen by launch_identity_gap.
+struct CholState {
+  double dmax, dmin, emax;
+};
+// Cholesky elimination of A's first m columns: rows 0..m hold the Hermitian G = K K^H (ld m; destroyed), rows
+// m..rows a matrix X that ends as X K^-H.  st receives the pivots; a pivot that is not positive
+// leaves dmin = 0 and finite garbage.
+void launch_cholesky(hipStream_t s, z64* A, int m, int rows, CholState* st);
+void launch_identity_gap(hipStream_t s, const z64* S, int m, CholState* st);
+// dst (q x p) = src^H (src p x q).
+void launch_conj_transpose(hipStream_t s, const z64* src, int p, int q, z64* dst);
 
 // ------------------------------------------------------------------ MPS kernels (kernels_mps.hip)
 struct MpoCoeff {

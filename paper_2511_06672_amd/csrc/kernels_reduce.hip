@@ -280,14 +280,18 @@ void launch_normalize_cols(hipStream_t s, z64* X, int m, int r, int ldx) {
   GC_LAUNCH_CHECK();
 }
 
+void launch_scaled_copy(hipStream_t s, z64* dst, const z64* src, size_t count, double f) {
+  hipLaunchKernelGGL(k_scaled_copy, dim3(blocks_of(count, 256)), dim3(256), 0, s, dst, src, count, f);
+  GC_LAUNCH_CHECK();
+}
+
 void orthonormalize_cols(hipStream_t s, z64* X, z64* Xn, z64* S, int m, int r, int iters) {
   // Newton-Schulz steps toward the polar factor: X <- X (3 I - X^H X) / 2, X and Xn alternating
   // (ld r); the result ends in X.
   for (int it = 0; it < iters; ++it) {
     launch_zgemm(s, 1, 0, r, r, m, X, r, X, r, S, r, z64{1.0, 0.0}, 0, 1);
     const size_t cnt = (size_t)m * r;
-    hipLaunchKernelGGL(k_scaled_copy, dim3(blocks_of(cnt, 256)), dim3(256), 0, s, Xn, X, cnt, 1.5);
-    GC_LAUNCH_CHECK();
+    launch_scaled_copy(s, Xn, X, cnt, 1.5);
     launch_zgemm(s, 0, 0, m, r, r, X, r, S, r, Xn, r, z64{-0.5, 0.0}, 1, 0);
     std::swap(X, Xn);
   }
