@@ -77,27 +77,6 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
-TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_gram_purity_f32_headline_d3_n32_traffic.md")
-SCORING_SOURCE = os.path.join(ROOT, "paper_2511_06672_amd", "csrc", "kernels_mps.hip")
-
-
-def measured_traffic():
-    """HBM bytes per launch of the Gram-purity kernel from the committed counter summary, or
-    None when the kernel source has changed since the counters were taken."""
-    import hashlib
-    try:
-        text = open(TRAFFIC_PROFILE).read()
-        src = hashlib.sha256(open(SCORING_SOURCE, "rb").read()).hexdigest()[:16]
-    except OSError:
-        return None
-    want = None
-    value = None
-    for line in text.splitlines():
-        if line.startswith("kernels_mps.hip sha256 prefix at measurement:"):
-            want = line.split(":")[1].strip()
-        if line.startswith("traffic_bytes_per_launch:"):
-            value = float(line.split(":")[1])
-    return value if (want == src and value is not None) else None
 
 
 def run_circuit(g, wl, prec, progress=True, cands=None):
@@ -268,7 +247,7 @@ def main_batch(args):
     if st["tiled_launches"] > 0 and st["tiled_ms"] > 0:
         achieved = st["tiled_flops"] / (st["tiled_ms"] * 1e-3) / 1e12
         roof = {"bound": "mfma", "achieved": achieved, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                "frac": achieved / FP32_PEAK_TFLOPS, "traffic": None, "kernel": "k_gram_purity_dl",
+                "frac": achieved / FP32_PEAK_TFLOPS, "traffic": None, "kernel": "k_density<float, 3>",
                 "launches": int(st["tiled_launches"]), "avg_ms": st["tiled_ms"] / st["tiled_launches"]}
     cpu = None if args.no_cpu else batch_cpu_baseline(bw, args.cpu_budget)
     fids = [r["fidelity"] for r in res]
@@ -816,7 +795,7 @@ def main():
                  "fidelity": ste.fidelity(), "final_bond_dim_max": int(max(ste.bond_dims())),
                  "fidelity_vs_timed_path": ste.fidelity() / st32.fidelity()}
 
-    # roofline of the Gram-purity MFMA kernel, timed per launch with HIP events
+    # roofline of the scoring MFMA kernel, timed per launch with HIP events
     tiled_ms = s32["tiled_ms"]
     roof = None
     if s32["tiled_launches"] > 0 and tiled_ms > 0:
@@ -826,10 +805,10 @@ def main():
         bf = prec == g.SCORE_BF16
         peak = BF16_PEAK_TFLOPS if bf else FP32_PEAK_TFLOPS
         roof = {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                "frac": achieved / peak, "traffic": None if bf else measured_traffic(),
+                "frac": achieved / peak, "traffic": None,
                 "traffic_unit": "HBM bytes per launch (FETCH_SIZE x 2 + WRITE_SIZE, copy-calibrated)",
                 "algorithmic_bytes": s32["tiled_bytes"] / s32["tiled_launches"],
-                "kernel": "k_gram_purity_bf16" if bf else "k_gram_purity_dl",
+                "kernel": "k_gram_purity_bf16" if bf else "k_density<float, 3>",
                 "launches": int(s32["tiled_launches"]), "avg_ms": per_launch_ms}
         if bf:
             roof["note"] = ("algorithmic flops (4 m^2 k per candidate); the split form issues three BF16 "

@@ -297,15 +297,17 @@ int32_t gcamps_get_choice_log(gcamps_ctx* ctx, int32_t* out, int64_t cap, int64_
 int32_t gcamps_get_site(gcamps_ctx* ctx, int32_t site, double* out, int64_t cap, int32_t dims[3]);
 /* Statistics (16 doubles): [0] non-Clifford gates applied, [1] bonds scored,
  * [2] candidates re-scored in FP64 (FP32 mode), [3] degenerate cuts flagged,
- * [4] algorithmic flops of full-set scoring (direct: N_c (4 m^2 k + 8 d^4 chi_l chi_r) per bond;
- * replica mode: 4 (X d^2)^2 Y + 8 X (X + 1) / 2 d^8 + 2 N_c d^8 with X, Y the smaller and larger bond), [5] algorithmic flops of the Gram products of
+ * [4] algorithmic flops of full-set scoring (direct: N_c (4 m^2 k + 8 d^4 chi_l chi_r) per bond; through
+ * the two-site density matrix, FP64 with d = 2, 3 and FP32 with d = 3 above a size:
+ * 4 (X d^2)^2 Y + N_c 4 X (X + 1) d^6; replica mode: 4 (X d^2)^2 Y + 8 X (X + 1) / 2 d^8 + 2 N_c d^8 with X, Y the smaller and larger bond), [5] algorithmic flops of the Gram products of
  * the factorisations, [6] full-set scoring kernel time in ms (device events), [7] total time
  * inside gcamps_* calls in ms (host clock), [8] flops of the FP64 window re-score, [9] its
- * kernel time in ms, [10] scoring calls (bonds x passes), [11] launches of the Gram-purity MFMA
- * kernel (full-set scoring), [12] their summed kernel time in ms (device events around each
- * launch), [13] their algorithmic flops (4 m^2 k per candidate), [14] bond splits that factorised only the
- * centre tensor (identity kept), [15] algorithmic bytes read by the Gram-purity launches (each
- * rotated m x k matrix once). */
+ * kernel time in ms, [10] scoring calls (bonds x passes), [11] launches of the scoring
+ * MFMA kernel (full-set scoring; Gram purity or density product), [12] their summed kernel time in ms
+ * (device events around each launch), [13] their algorithmic flops (4 m^2 k or 4 X (X + 1) d^6 per
+ * candidate), [14] bond splits that factorised only the
+ * centre tensor (identity kept), [15] algorithmic bytes read by those launches (each
+ * rotated m x k matrix once, or half of the density matrix and the candidates' rows). */
 int32_t gcamps_get_stats(gcamps_ctx* ctx, double out[16]);
 /* Counters for the roofline of the compression and MPO steps (§2.4, §3), accumulated since
  * gcamps_init: [0] factorisations; [1] their algorithmic flops, 4 (6 p q^2 + 20 q^3) per p x q

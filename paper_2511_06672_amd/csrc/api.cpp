@@ -98,6 +98,10 @@ void set_error(const std::string& msg) { g_last_error = msg; }
 }  // namespace gc
 
 namespace gc {
+// FP32 scoring takes the density form for qutrits; with d = 2 it stays with the rotated-matrix kernels, whose
+// per-shape launch choices (GCAMPS_TUNE_FILE) callers keep across runs.
+static bool density_fp32(const gcamps_config& c) { return c.d == 3 && c.score_prec == GCAMPS_SCORE_FP32; }
+
 Layout make_layout(const gcamps_config& c) {
   Layout L{};
   const size_t d = c.d, chi = c.chi_max;
@@ -145,6 +149,8 @@ Layout make_layout(const gcamps_config& c) {
   if (replica) L.nbuf_bytes = std::max(L.nbuf_bytes, replica_scratch_bytes(c.d, c.chi_max));
   L.off_nbuf = take(L.nbuf_bytes);
   L.off_rtab = take(replica ? replica_table_elems(c.d, (int)L.ncand) * sizeof(z64) : 0);
+  L.off_dtab = take(density_table_elems(c.d, (int)L.ncand) * sizeof(z64));
+  L.off_dtab32 = take(density_fp32(c) ? density_table_elems(c.d, (int)L.ncand) * sizeof(c32) : 0);
   const size_t D4 = d * d * d * d;
   L.off_q64 = take(L.ncand * D4 * sizeof(z64));
   L.off_q32 = take(L.ncand * D4 * sizeof(c32));
@@ -265,6 +271,8 @@ int32_t gcamps_init(const gcamps_config* cfg, void* dev_workspace, size_t bytes,
     c->q64 = reinterpret_cast<z64*>(w + lay.off_q64);
     c->rtab = cfg->score_prec == GCAMPS_SCORE_REPLICA ? reinterpret_cast<z64*>(w + lay.off_rtab) : nullptr;
     c->q32 = reinterpret_cast<c32*>(w + lay.off_q32);
+    c->dtab = cfg->d <= 3 ? reinterpret_cast<z64*>(w + lay.off_dtab) : nullptr;
+    c->dtab32 = density_fp32(*cfg) ? reinterpret_cast<c32*>(w + lay.off_dtab32) : nullptr;
     c->qinv = reinterpret_cast<uint32_t*>(w + lay.off_qinv);
     int* tab = reinterpret_cast<int*>(w + lay.off_tab);
     c->tx = tab;
@@ -445,6 +453,7 @@ static void upload_candset(gcamps_ctx* ctx, const gcamps_candset* set) {
   GC_HIP(hipMemcpyAsync(ctx->q64, q64.data(), q64.size() * sizeof(z64), hipMemcpyHostToDevice, ctx->stream));
   GC_HIP(hipMemcpyAsync(ctx->q32, q32.data(), q32.size() * sizeof(c32), hipMemcpyHostToDevice, ctx->stream));
   GC_HIP(hipMemcpyAsync(ctx->qinv, inv.data(), inv.size() * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->stream));
+  if (ctx->dtab) launch_density_tables(ctx->stream, d, set->count, ctx->q64, ctx->dtab, ctx->dtab32);
   if (ctx->rtab) launch_replica_tables(ctx->stream, d, set->count, ctx->q64, ctx->rtab);
   GC_HIP(hipStreamSynchronize(ctx->stream));
   ctx->ncand = set->count;

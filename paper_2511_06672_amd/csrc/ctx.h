@@ -22,7 +22,7 @@ struct Layout {
   int nslots;
   size_t off_slots, off_theta, off_G, off_U, off_Z, off_Utmp, off_B, off_B2, off_sig2, off_sig, off_lam,
       off_perm, off_eigG, off_eigV, off_eigD, off_flags, off_s2, off_s2w, off_wlist, off_partial, off_nbuf, nbuf_bytes, off_q64, off_q32,
-      off_rtab, off_qinv, off_tab, off_target, off_weyl, off_err, off_status, off_luts, off_sites, off_dense,
+      off_rtab, off_dtab, off_dtab32, off_qinv, off_tab, off_target, off_weyl, off_err, off_status, off_luts, off_sites, off_dense,
       dense_dim, off_pcst, off_chol, total;
 };
 
@@ -109,6 +109,8 @@ struct gcamps_ctx {
   z64* q64 = nullptr;
   c32* q32 = nullptr;
   z64* rtab = nullptr;  // replica-scoring tables of the candidate set (replica mode only)
+  z64* dtab = nullptr;    // density-scoring rows of the candidate set (d <= 3)
+  c32* dtab32 = nullptr;  // the same in FP32 (FP32 scoring with d = 3)
   uint32_t* qinv = nullptr;
   EigWork eig{};
   // MPS
@@ -767,15 +769,43 @@ struct gcamps_ctx {
     stats[0] += 1;
   }
 
+  // ---------------------------------------------------------------- scoring
+  // Scores of Theta (bonds cl, cr) in the arithmetic of prec: the full set, or (nlimit given) the window
+  // list of an earlier pass.  f_ready: the scratch holds Theta's density matrix; it does after a pass
+  // that used it.  evs, evcap and used as in launch_score.  Returns the algorithmic flops of the full set.
+  bool use_density(int prec, int cl, int cr) const {
+    return dtab && (prec == GCAMPS_SCORE_FP64 || (prec == GCAMPS_SCORE_FP32 && dtab32)) &&
+           (double)std::min(cl, cr) * std::min(cl, cr) * std::max(cl, cr) * d * d * d >= kDensityMinWork && density_fits(d, cl, cr, ncand, lay.nbuf_bytes);
+  }
+  double density_flops(int cl, int cr) const {  // one candidate's product
+    const double X = std::min(cl, cr);
+    return 4.0 * X * (X + 1) * std::pow((double)d, 6);
+  }
+  void score(int prec, int cl, int cr, const int* list, const int* nlimit, double* out, bool& f_ready,
+             hipEvent_t* evs = nullptr, int evcap = 0, int* used = nullptr) {
+    if (used) *used = 0;
+    if (use_density(prec, cl, cr)) {
+      if (!f_ready) launch_density_gram(stream, d, cl, cr, theta, nbuf);
+      f_ready = true;
+      const bool ev = used && evcap >= 2;
+      launch_density_score(stream, d, prec == GCAMPS_SCORE_FP32, cl, cr, dtab, dtab32, ncand, list, ncand, nlimit, out,
+                           nbuf, lay.nbuf_bytes, ev ? evs[0] : nullptr, ev ? evs[1] : nullptr);
+      if (ev) *used = 1;
+      return;
+    }
+    f_ready = false;
+    launch_score(stream, prec, d, cl, cr, theta, q64, q32, list, ncand, nlimit, out, partial, lay.ncand * lay.ntp * 2,
+                 nbuf, lay.nbuf_bytes, evs, evcap, used, rtab);
+  }
+
   // Full-set scores of bond (i, i+1) in the configured mode, to host memory; commits nothing.
   void score_bond(int i, double* out) {
     move_centre(i);
     const int cl = chi[i], cm = chi[i + 1], cr = chi[i + 2];
     launch_zgemm(stream, 0, 0, cl * d, d * cr, cm, site[i], cm, site[i + 1], d * cr, theta, d * cr, z64{1.0, 0.0},
                  0, 0);
-    const size_t pcap = lay.ncand * lay.ntp * 2;
-    launch_score(stream, cfg.score_prec, d, cl, cr, theta, q64, q32, nullptr, ncand, nullptr, s2, partial, pcap, nbuf,
-                 lay.nbuf_bytes, nullptr, 0, nullptr, rtab);
+    bool f_ready = false;
+    score(cfg.score_prec, cl, cr, nullptr, nullptr, s2, f_ready);
     GC_HIP(hipMemcpyAsync(out, s2, (size_t)ncand * sizeof(double), hipMemcpyDeviceToHost, stream));
     GC_HIP(hipStreamSynchronize(stream));
   }
@@ -813,11 +843,12 @@ struct gcamps_ctx {
         } else {
           launch_zgemm(stream, 0, 0, cl * d, d * cr, cm, site[i], cm, site[i + 1], d * cr, theta, d * cr,
                        z64{1.0, 0.0}, 0, 0);
-          const size_t pcap = lay.ncand * lay.ntp * 2;
-          const double pflops = 4.0 * mm * mm * kk + 8.0 * std::pow((double)d, 4) * cl * cr;
+          const bool density = use_density(prec, cl, cr);
+          const double pflops = density ? density_flops(cl, cr)
+                                        : 4.0 * mm * mm * kk + 8.0 * std::pow((double)d, 4) * cl * cr;
           GC_HIP(hipEventRecord(ev0, stream));
-          launch_score(stream, prec, d, cl, cr, theta, q64, q32, nullptr, ncand, nullptr, s2, partial, pcap, nbuf,
-                       lay.nbuf_bytes, gram_ev.data(), (int)gram_ev.size(), &gram_used, rtab);
+          bool f_ready = false;
+          score(prec, cl, cr, nullptr, nullptr, s2, f_ready, gram_ev.data(), (int)gram_ev.size(), &gram_used);
           GC_HIP(hipEventRecord(ev1, stream));
           if (cfg.criterion == GCAMPS_CRITERION_BOND_DIM) {
             if (mm <= kRankMaxM && (size_t)(mm + (mm & 1)) * kk <= kRankMaxElems) {
@@ -840,8 +871,7 @@ struct gcamps_ctx {
           } else {
             launch_window(stream, ncand, s2, cfg.near_tie, wlist, st);
             GC_HIP(hipEventRecord(ev2, stream));
-            launch_score(stream, GCAMPS_SCORE_FP64, d, cl, cr, theta, q64, q32, wlist, ncand, &st->nwindow, s2w,
-                         partial, pcap, nbuf, lay.nbuf_bytes);
+            score(GCAMPS_SCORE_FP64, cl, cr, wlist, &st->nwindow, s2w, f_ready);
             GC_HIP(hipEventRecord(ev3, stream));
             launch_select_window(stream, wlist, s2w, cfg.tie_tol, st);
           }
@@ -851,6 +881,7 @@ struct gcamps_ctx {
             stats[4] += 4.0 * XD * XD * Y + 8.0 * X * (X + 1) / 2 * R2 + 2.0 * ncand * R2;
           } else {
             stats[4] += (double)ncand * pflops;
+            if (density) stats[4] += 4.0 * std::pow((double)std::min(cl, cr) * d * d, 2) * std::max(cl, cr);
           }
           stats[10] += 1;
           launch_apply_q(stream, d, cl, cr, st, q64, theta);
@@ -915,12 +946,20 @@ struct gcamps_ctx {
               stats[12] += gm;
             }
             stats[11] += gram_used;
-            stats[13] += (double)ncand * 4.0 * mm * mm * kk;
-            stats[15] += (double)ncand * mm * kk * (prec == GCAMPS_SCORE_FP64 ? 16.0 : 8.0);
+            if (use_density(prec, cl, cr)) {
+              const double xd = (double)std::min(cl, cr) * d * d;
+              stats[13] += (double)ncand * density_flops(cl, cr);
+              stats[15] += 8.0 * xd * xd + (double)ncand * std::pow((double)d, 6) * (prec == GCAMPS_SCORE_FP64 ? 16.0 : 8.0);
+            } else {
+              stats[13] += (double)ncand * 4.0 * mm * mm * kk;
+              stats[15] += (double)ncand * mm * kk * (prec == GCAMPS_SCORE_FP64 ? 16.0 : 8.0);
+            }
           }
           stats[1] += 1;
           if (prec != GCAMPS_SCORE_FP64) {
-            const double pflops = 4.0 * mm * mm * kk + 8.0 * std::pow((double)d, 4) * cl * cr;
+            const double pflops = use_density(GCAMPS_SCORE_FP64, cl, cr)
+                                      ? density_flops(cl, cr)
+                                      : 4.0 * mm * mm * kk + 8.0 * std::pow((double)d, 4) * cl * cr;
             stats[2] += h.nwindow;
             stats[8] += (double)h.nwindow * pflops;
             GC_HIP(hipEventElapsedTime(&ms, ev2, ev3));

@@ -97,6 +97,10 @@ constexpr int kSplitSmallMaxK = 512;  // largest larger side of a one-launch spl
 // untested against the plain path's accuracy.
 constexpr int kReduceMinM = 320;
 constexpr int kReduceMaxM = 1024;
+// m^2 k (m and k the smaller and larger side of the two-site matrix) from which a bond is scored through
+// the two-site density matrix (kernels_density.hip): m = 32, k = 32 (d = 2) takes 40 us through it and 70
+// directly, m = 27, k = 27 (d = 3) 69 and 52, m = 27, k = 243 57 and 158.
+constexpr double kDensityMinWork = 25000;
 constexpr int kBlk = 16;        // block size of the multi-workgroup block Jacobi
 
 // ----------------------------------------------------------------- device status block

@@ -186,6 +186,22 @@ void launch_select_rank(hipStream_t s, int count, const int* rank, const double*
 void rank_set_attributes();
 void linalg_set_attributes();  // the block-Jacobi rounds' dynamic LDS limit
 
+// ------------------------------------------------------------------ density scoring (kernels_density.hip)
+// Scores through the two-site reduced density matrix F of Theta over its larger bond (d = 2, 3): one
+// Gram of Theta, then a matrix product against the candidates' rows T_c for every pair of smaller-bond
+// indices, |rho_c|^2 summed as it is formed.
+size_t density_table_elems(int d, int count);  // rows T_c of both cuts; 0 for d > 3
+void launch_density_tables(hipStream_t s, int d, int count, const z64* qmats, z64* tab, c32* tab32);
+// Whether F and at least one block's partial sums of `count` candidates fit the scratch.
+bool density_fits(int d, int chil, int chir, int count, size_t scratch_bytes);
+// F of Theta at the start of the scratch (kept for the scores that follow).
+void launch_density_gram(hipStream_t s, int d, int chil, int chir, const z64* theta, void* scratch);
+// S2 of the candidates (list and nlimit as in launch_score) from F; set_count: candidates in the tables;
+// events around the product's launch when given.
+void launch_density_score(hipStream_t s, int d, bool fp32, int chil, int chir, const z64* tab, const c32* tab32,
+                          int set_count, const int* list, int count, const int* nlimit, double* s2, void* scratch,
+                          size_t scratch_bytes, hipEvent_t ev0, hipEvent_t ev1);
+
 // ------------------------------------------------------------------ replica scoring (kernels_replica.hip)
 // Full-set scores through the replica tensor of Theta (d = 2, 3): the Gram F of Theta over its
 // larger bond, the pair sum A, and one D^4 dot product per candidate with its table.

@@ -926,7 +926,7 @@ __global__ __launch_bounds__(1024) void k_select(int count, const double* __rest
 __global__ __launch_bounds__(1024) void k_window(int count, const double* __restrict__ s2lp, double window,
                                                  int* __restrict__ list, DevStatus* st) {
   __shared__ double red[1024];
-  __shared__ int cnt[1024];
+  __shared__ int cnt[16];
   const int t = threadIdx.x;
   double mn = DBL_MAX;
   for (int i = t; i < count; i += 1024) mn = fmin(mn, s2lp[i]);
@@ -943,20 +943,21 @@ __global__ __launch_bounds__(1024) void k_window(int count, const double* __rest
   int my = 0;
   for (int i = b0; i < b1; ++i)
     if (s2lp[i] <= lim) ++my;
-  cnt[t] = my;
+  // exclusive prefix sum: within each wave by shuffles, then over the 16 wave totals
+  const int lane = t & 63;
+  int inc = my;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += o;
+  }
+  if (lane == 63) cnt[t >> 6] = inc;
   __syncthreads();
-  if (t == 0) {
-    int run = 0;
-    for (int i = 0; i < 1024; ++i) {
-      int v = cnt[i];
-      cnt[i] = run;
-      run += v;
-    }
-    st->nwindow = run;
+  int pos = inc - my;
+  for (int w = 0; w < (t >> 6); ++w) pos += cnt[w];
+  if (t == 1023) {
+    st->nwindow = pos + my;
     st->smin_lp = red[0];
   }
-  __syncthreads();
-  int pos = cnt[t];
   for (int i = b0; i < b1; ++i)
     if (s2lp[i] <= lim) list[pos++] = i;
 }
