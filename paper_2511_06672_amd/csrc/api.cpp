@@ -150,7 +150,7 @@ Layout make_layout(const gcamps_config& c) {
   L.off_nbuf = take(L.nbuf_bytes);
   L.off_rtab = take(replica ? replica_table_elems(c.d, (int)L.ncand) * sizeof(z64) : 0);
   L.off_dtab = take(density_table_elems(c.d, (int)L.ncand) * sizeof(z64));
-  L.off_dtab32 = take(density_fp32(c) ? density_table_elems(c.d, (int)L.ncand) * sizeof(c32) : 0);
+  L.off_dtab32 = take(c.d == 3 ? density_table_elems(c.d, (int)L.ncand) * sizeof(c32) : 0);  // in every mode
   const size_t D4 = d * d * d * d;
   L.off_q64 = take(L.ncand * D4 * sizeof(z64));
   L.off_q32 = take(L.ncand * D4 * sizeof(c32));
