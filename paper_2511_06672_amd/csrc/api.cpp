@@ -163,11 +163,11 @@ Layout make_layout(const gcamps_config& c) {
   L.off_luts = take((size_t)c.n * D4 * sizeof(uint32_t));
   L.off_sites = take((size_t)c.n * sizeof(int));
   // dense state (validation; d^n <= kDenseMax): amplitude output and scratch (4 d^n complex128)
-  // plus the per-index Clifford table (two int32 and n int8 per index)
+  // plus the per-index Clifford table (two packed digit strings per index)
   L.dense_dim = 1;
   for (int i = 0; i < c.n && L.dense_dim <= kDenseMax; ++i) L.dense_dim *= d;
   if (L.dense_dim > kDenseMax) L.dense_dim = 0;
-  L.off_dense = take(L.dense_dim * (4 * sizeof(z64) + 2 * sizeof(int) + (size_t)c.n));
+  L.off_dense = take(L.dense_dim * (4 * sizeof(z64) + std::max<size_t>(16, 8 + c.n)));
   L.off_pcst = take(sizeof(PcState));
   L.off_chol = take(sizeof(CholState));
   L.total = o;
@@ -585,93 +585,14 @@ static void statevector_impl(gcamps_ctx* ctx, z64* out, z64* scratch) {
     R *= d;
     if (i != n - 1) std::swap(va, vb);
   }
-  // tableau rows to host
-  std::vector<int> hx(2 * n * n), hz(2 * n * n), hp(2 * n);
-  GC_HIP(hipMemcpyAsync(hx.data(), ctx->tx, hx.size() * sizeof(int), hipMemcpyDeviceToHost, s));
-  GC_HIP(hipMemcpyAsync(hz.data(), ctx->tz, hz.size() * sizeof(int), hipMemcpyDeviceToHost, s));
-  GC_HIP(hipMemcpyAsync(hp.data(), ctx->tp, hp.size() * sizeof(int), hipMemcpyDeviceToHost, s));
-  GC_HIP(hipStreamSynchronize(s));
-  // |s0> = C|0>: projector prod_k (1/d) sum_j S_k^j applied to a fixed generic vector
-  std::vector<z64> start(D);
-  for (long long y = 0; y < D; ++y) start[y] = z64{std::cos(0.731 * y + 0.2), std::sin(1.37 * y + 0.5) + 0.3};
-  GC_HIP(hipMemcpy(va, start.data(), D * sizeof(z64), hipMemcpyHostToDevice));
-  // all exponent rows of S_k^j (k < n, j < d) uploaded once: [k][j][x | z]
-  std::vector<int> pows((size_t)n * d * 2 * n);
-  std::vector<int> pph((size_t)n * d);
-  for (int k = 0; k < n; ++k) {
-    int xzsum = 0;
-    for (int i = 0; i < n; ++i) xzsum += hx[k * n + i] * hz[k * n + i];
-    for (int j = 0; j < d; ++j) {
-      int* row = &pows[((size_t)k * d + j) * 2 * n];
-      for (int i = 0; i < n; ++i) {
-        row[i] = (j * hx[k * n + i]) % d;
-        row[n + i] = (j * hz[k * n + i]) % d;
-      }
-      pph[(size_t)k * d + j] = (j * hp[k] + 2 * (xzsum % d) * (j * (j - 1) / 2)) % (2 * d);
-    }
-  }
-  int* dxz = reinterpret_cast<int*>(ctx->B2);
-  GC_HIP(hipMemcpy(dxz, pows.data(), pows.size() * sizeof(int), hipMemcpyHostToDevice));
-  for (int k = 0; k < n; ++k) {
-    for (int j = 0; j < d; ++j) {
-      const int* row = dxz + ((size_t)k * d + j) * 2 * n;
-      launch_apply_weyl_dense(s, n, d, D, row, row + n, pph[(size_t)k * d + j], va, vb, j > 0 ? 1 : 0,
-                              z64{1.0 / d, 0.0});
-    }
-    std::swap(va, vb);
-  }
+  double* norm2 = reinterpret_cast<double*>(ctx->B2);
+  launch_stab_state(s, n, d, (int)D, ctx->tx, ctx->tz, ctx->tp, va, vb, norm2);
+  void* ab = ctx->ws + ctx->lay.off_dense + (size_t)4 * D * sizeof(z64);
+  launch_clifford_dense(s, n, d, (int)D, ctx->tx, ctx->tz, ctx->tp, ab, mv, va, norm2, out);
   double nrm = 0.0;
-  double* dn = reinterpret_cast<double*>(dxz + pows.size() + 64);
-  launch_norm2(s, va, D, dn);
-  GC_HIP(hipMemcpyAsync(&nrm, dn, sizeof(double), hipMemcpyDeviceToHost, s));
+  GC_HIP(hipMemcpyAsync(&nrm, norm2, sizeof(double), hipMemcpyDeviceToHost, s));
   GC_HIP(hipStreamSynchronize(s));
   GC_CHECK(nrm > 1e-20, GCAMPS_ENUMERIC, "stabilizer projection vanished");
-  launch_scale(s, va, D, z64{1.0 / std::sqrt(nrm), 0.0});
-  // per-x table of C X^x C^dagger = prod_k D_k^{x_k} = tau^{p_x} X^{a_x} Z^{b_x}
-  std::vector<int> aidx(D), px(D);
-  std::vector<int8_t> bd((size_t)D * n);
-  std::vector<int> ax(n), bz(n);
-  for (long long x = 0; x < D; ++x) {
-    std::fill(ax.begin(), ax.end(), 0);
-    std::fill(bz.begin(), bz.end(), 0);
-    int p = 0;
-    long long rem = x;
-    std::vector<int> dig(n);
-    for (int i = n - 1; i >= 0; --i) {
-      dig[i] = (int)(rem % d);
-      rem /= d;
-    }
-    for (int k = 0; k < n; ++k) {
-      int e = dig[k];
-      if (!e) continue;
-      const int* rx = &hx[(n + k) * n];
-      const int* rz = &hz[(n + k) * n];
-      int xz = 0;
-      for (int i = 0; i < n; ++i) xz += rx[i] * rz[i];
-      int pw = (e * hp[n + k] + 2 * (xz % d) * (e * (e - 1) / 2)) % (2 * d);
-      int cross = 0;
-      for (int i = 0; i < n; ++i) cross += bz[i] * ((e * rx[i]) % d);
-      p = (p + pw + 2 * (cross % d)) % (2 * d);
-      for (int i = 0; i < n; ++i) {
-        ax[i] = (ax[i] + e * rx[i]) % d;
-        bz[i] = (bz[i] + e * rz[i]) % d;
-      }
-    }
-    long long packed = 0;
-    for (int i = 0; i < n; ++i) packed = packed * d + ax[i];
-    aidx[x] = (int)packed;
-    px[x] = p;
-    for (int i = 0; i < n; ++i) bd[(size_t)x * n + i] = (int8_t)bz[i];
-  }
-  char* tbl = ctx->ws + ctx->lay.off_dense + (size_t)4 * D * sizeof(z64);
-  int* d_aidx = reinterpret_cast<int*>(tbl);
-  int* d_px = d_aidx + D;
-  int8_t* d_bd = reinterpret_cast<int8_t*>(d_px + D);
-  GC_HIP(hipMemcpy(d_aidx, aidx.data(), D * sizeof(int), hipMemcpyHostToDevice));
-  GC_HIP(hipMemcpy(d_px, px.data(), D * sizeof(int), hipMemcpyHostToDevice));
-  GC_HIP(hipMemcpy(d_bd, bd.data(), (size_t)D * n, hipMemcpyHostToDevice));
-  launch_clifford_dense(s, n, d, D, d_aidx, d_bd, d_px, mv, va, out);
-  GC_HIP(hipStreamSynchronize(s));
 }
 
 int32_t gcamps_statevector(gcamps_ctx* ctx, void* dev_out, void* dev_scratch, size_t scratch_bytes) {

@@ -222,17 +222,15 @@ void launch_window(hipStream_t s, int count, const double* s2lp, double window, 
 // FP64 rule over the window: c* = lowest listed index with s2 <= min + tie_tol.
 void launch_select_window(hipStream_t s, const int* list, const double* s2win, double tie_tol,
                           DevStatus* st);
-// Weyl string applied to a dense vector of D = d^n amplitudes:
-//   out(y) (+)= coeff * tau^p omega^{<z, y - x>} in(y - x)
-void launch_apply_weyl_dense(hipStream_t s, int n, int d, long long D, const int* x, const int* z,
-                             int p, const z64* in, z64* out, int accumulate, z64 coeff);
-// psi(y) = sum_x m(x) tau^{p_x} omega^{<b_x, y - a_x>} s0(y - a_x) with per-x table
-// (a_x packed as base-d index, b_x as n digits, p_x).
-void launch_clifford_dense(hipStream_t s, int n, int d, long long D, const int* a_idx,
-                           const int8_t* b_dig, const int* p_x, const z64* mvec, const z64* s0,
-                           z64* out);
-void launch_scale(hipStream_t s, z64* v, size_t count, z64 f);
-void launch_norm2(hipStream_t s, const z64* v, size_t count, double* out);
+// ------------------------------------------------------------------ dense state (kernels_dense.hip)
+// v <- C|0> for the tableau's Clifford C, not normalised (norm2 = its squared norm): the stabilizer
+// projectors applied to a fixed generic vector.  w is scratch; v and w trade places.
+void launch_stab_state(hipStream_t s, int n, int d, int D, const int* tx, const int* tz, const int* tp, z64*& v,
+                       z64*& w, double* norm2);
+// out(y) = sum_x m(x) (C X^x C^dagger s0)(y) / sqrt(*norm2), D = d^n <= 2^16.  ab: 16 D bytes of scratch;
+// m is overwritten.
+void launch_clifford_dense(hipStream_t s, int n, int d, int D, const int* tx, const int* tz, const int* tp, void* ab,
+                           z64* m, const z64* s0, const double* norm2, z64* out);
 
 // ------------------------------------------------------------------ reverse sweep (kernels_adjoint.hip)
 // out[0] = 1/sqrt(sum_{j<k} sig_j^2) when renorm, else 1.

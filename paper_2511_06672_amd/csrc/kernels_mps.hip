@@ -992,79 +992,6 @@ __global__ __launch_bounds__(1024) void k_select_window(const int* __restrict__ 
   }
 }
 
-// ===================================================================================== dense helpers
-__device__ __forceinline__ z64 tau_pow(int p, int d) {
-  double ang = M_PI * (double)p / (double)d;
-  return z64{cos(ang), sin(ang)};
-}
-
-__global__ void k_apply_weyl_dense(int n, int d, long long D, const int* __restrict__ x, const int* __restrict__ z,
-                                   int p, const z64* __restrict__ in, z64* __restrict__ out, int accumulate,
-                                   z64 coeff) {
-  long long y = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (y >= D) return;
-  // digits of y, site 0 most significant
-  long long rem = y, src = 0, mul = 1;
-  int ph = 0;
-  for (int i = n - 1; i >= 0; --i) {
-    int yi = (int)(rem % d);
-    rem /= d;
-    int si = (yi - x[i] + d) % d;
-    ph += z[i] * si;
-    src += si * mul;
-    mul *= d;
-  }
-  z64 f = tau_pow((p + 2 * (ph % d)) % (2 * d), d);
-  z64 v = cmul(cmul(coeff, f), in[src]);
-  out[y] = accumulate ? cadd(out[y], v) : v;
-}
-
-__global__ void k_clifford_dense(int n, int d, long long D, const int* __restrict__ a_idx,
-                                 const int8_t* __restrict__ b_dig, const int* __restrict__ p_x,
-                                 const z64* __restrict__ mvec, const z64* __restrict__ s0, z64* __restrict__ out) {
-  long long y = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (y >= D) return;
-  int yd[32];
-  long long rem = y;
-  for (int i = n - 1; i >= 0; --i) {
-    yd[i] = (int)(rem % d);
-    rem /= d;
-  }
-  z64 acc = {0.0, 0.0};
-  for (long long xi = 0; xi < D; ++xi) {
-    z64 mv = mvec[xi];
-    if (mv.re == 0.0 && mv.im == 0.0) continue;
-    long long a = a_idx[xi];
-    const int8_t* bd = b_dig + xi * n;
-    long long src = 0, mul = 1;
-    int ph = 0;
-    for (int i = n - 1; i >= 0; --i) {
-      int ai = (int)(a % d);
-      a /= d;
-      int si = (yd[i] - ai + d) % d;
-      ph += bd[i] * si;
-      src += si * mul;
-      mul *= d;
-    }
-    z64 f = tau_pow((p_x[xi] + 2 * (ph % d)) % (2 * d), d);
-    acc = cadd(acc, cmul(mv, cmul(f, s0[src])));
-  }
-  out[y] = acc;
-}
-
-__global__ void k_scale(z64* v, size_t count, z64 f) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) v[i] = cmul(v[i], f);
-}
-
-__global__ void k_norm2(const z64* __restrict__ v, size_t count, double* out) {
-  __shared__ double red[1024];
-  double s = 0.0;
-  for (size_t i = threadIdx.x; i < count; i += 1024) s += cabs2(v[i]);
-  double r = block_sum(s, red);
-  if (threadIdx.x == 0) *out = r;
-}
-
 }  // namespace
 
 // ===================================================================================== launchers
@@ -1252,30 +1179,6 @@ void launch_window(hipStream_t s, int count, const double* s2lp, double window, 
 
 void launch_select_window(hipStream_t s, const int* list, const double* s2win, double tie_tol, DevStatus* st) {
   hipLaunchKernelGGL(k_select_window, dim3(1), dim3(1024), 0, s, list, s2win, tie_tol, st);
-  GC_LAUNCH_CHECK();
-}
-
-void launch_apply_weyl_dense(hipStream_t s, int n, int d, long long D, const int* x, const int* z, int p,
-                             const z64* in, z64* out, int accumulate, z64 coeff) {
-  hipLaunchKernelGGL(k_apply_weyl_dense, dim3(blocks_for((size_t)D, 256)), dim3(256), 0, s, n, d, D, x, z, p, in,
-                     out, accumulate, coeff);
-  GC_LAUNCH_CHECK();
-}
-
-void launch_clifford_dense(hipStream_t s, int n, int d, long long D, const int* a_idx, const int8_t* b_dig,
-                           const int* p_x, const z64* mvec, const z64* s0, z64* out) {
-  hipLaunchKernelGGL(k_clifford_dense, dim3(blocks_for((size_t)D, 128)), dim3(128), 0, s, n, d, D, a_idx, b_dig, p_x,
-                     mvec, s0, out);
-  GC_LAUNCH_CHECK();
-}
-
-void launch_scale(hipStream_t s, z64* v, size_t count, z64 f) {
-  hipLaunchKernelGGL(k_scale, dim3(blocks_for(count, 256)), dim3(256), 0, s, v, count, f);
-  GC_LAUNCH_CHECK();
-}
-
-void launch_norm2(hipStream_t s, const z64* v, size_t count, double* out) {
-  hipLaunchKernelGGL(k_norm2, dim3(1), dim3(1024), 0, s, v, count, out);
   GC_LAUNCH_CHECK();
 }
 
