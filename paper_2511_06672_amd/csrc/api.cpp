@@ -156,9 +156,7 @@ Layout make_layout(const gcamps_config& c) {
   L.off_q32 = take(L.ncand * D4 * sizeof(c32));
   L.off_qinv = take(L.ncand * D4 * sizeof(uint32_t));
   L.off_tab = take((2 * (size_t)c.n * c.n * 2 + 2 * c.n) * sizeof(int));
-  L.off_target = take((2 * (size_t)c.n + 1) * sizeof(int));
   L.off_weyl = take(sizeof(DevWeyl));
-  L.off_err = take(sizeof(int) * 4);
   L.off_status = take(sizeof(DevStatus));
   L.off_luts = take((size_t)c.n * D4 * sizeof(uint32_t));
   L.off_sites = take((size_t)c.n * sizeof(int));
@@ -222,6 +220,7 @@ int32_t gcamps_init(const gcamps_config* cfg, void* dev_workspace, size_t bytes,
     std::call_once(attrs_once, [] {
       rank_set_attributes();
       linalg_set_attributes();
+      expect_set_attributes();
     });
     int dev = 0;
     GC_HIP(hipGetDevice(&dev));
@@ -278,9 +277,7 @@ int32_t gcamps_init(const gcamps_config* cfg, void* dev_workspace, size_t bytes,
     c->tx = tab;
     c->tz = tab + 2 * (size_t)n * n;
     c->tp = tab + 4 * (size_t)n * n;
-    c->target = reinterpret_cast<int*>(w + lay.off_target);
     c->weyl = reinterpret_cast<DevWeyl*>(w + lay.off_weyl);
-    c->derr = reinterpret_cast<int*>(w + lay.off_err);
     c->st = reinterpret_cast<DevStatus*>(w + lay.off_status);
     c->dluts = reinterpret_cast<uint32_t*>(w + lay.off_luts);
     c->dsites = reinterpret_cast<int*>(w + lay.off_sites);
@@ -520,40 +517,53 @@ int32_t gcamps_expectation(gcamps_ctx* ctx, const int8_t* x, const int8_t* z, in
   return guarded(ctx, [&] {
     GC_CHECK(ctx && x && z && out, GCAMPS_EINVAL, "null argument");
     const int n = ctx->n, d = ctx->d;
-    int* tg = reinterpret_cast<int*>(ctx->stage_begin());
+    ExpectArgs a{};
     for (int i = 0; i < n; ++i) {
       GC_CHECK(x[i] >= 0 && x[i] < d && z[i] >= 0 && z[i] < d, GCAMPS_EINVAL, "exponent out of range");
-      tg[i] = x[i];
-      tg[n + i] = z[i];
+      a.target.x[i] = (uint8_t)x[i];
+      a.target.z[i] = (uint8_t)z[i];
+      a.site[i] = ctx->site[i];
     }
-    tg[2 * n] = ((p % (2 * d)) + 2 * d) % (2 * d);
-    ctx->stage_upload(ctx->target, (2 * n + 1) * sizeof(int));
-    launch_weyl_extract(ctx->stream, n, d, ctx->tx, ctx->tz, ctx->tp, ctx->target, ctx->weyl, ctx->derr);
-    DevWeyl P;
-    GC_HIP(hipMemcpyAsync(&P, ctx->weyl, sizeof(DevWeyl), hipMemcpyDeviceToHost, ctx->stream));
-    GC_HIP(hipStreamSynchronize(ctx->stream));
-    // transfer matrices, E_0 = [[1]]; buffers: Utmp (E), Z (E'), G (tmp)
+    a.target.p = ((p % (2 * d)) + 2 * d) % (2 * d);
+    a.n = n;
+    a.d = d;
+    a.tx = ctx->tx;
+    a.tz = ctx->tz;
+    a.tp = ctx->tp;
+    a.weyl = ctx->weyl;
+    std::copy(ctx->chi.begin(), ctx->chi.begin() + n + 1, a.chi);
+    // runs of small sites in one launch each, the sites between them by products on the whole chip;
+    // buffers: Utmp (E), Z (E'), B2 (E A), B (the bra's tensor)
+    auto small = [&](int i) {
+      return a.chi[i] * d * a.chi[i + 1] <= kExpectMaxSite && a.chi[i] * a.chi[i] <= kExpectMaxBond2 &&
+             a.chi[i + 1] * a.chi[i + 1] <= kExpectMaxBond2;
+    };
     z64* E = ctx->Utmp;
     z64* En = ctx->Z;
-    z64* tmp = ctx->B2;
-    z64 one = {1.0, 0.0};
-    GC_HIP(hipMemcpyAsync(E, &one, sizeof(z64), hipMemcpyHostToDevice, ctx->stream));
-    for (int i = 0; i < n; ++i) {
-      const int cl = ctx->chi[i], cr = ctx->chi[i + 1];
-      const z64* A = ctx->site[i];
-      for (int t = 0; t < d; ++t) {
-        launch_zgemm(ctx->stream, 0, 0, cl, cr, cl, E, cl, A + (size_t)t * cr, d * cr, tmp, cr, one, 0, 0);
-        const int s = (t + P.x[i]) % d;
-        const double ang = 2.0 * M_PI * ((P.z[i] * t) % d) / d;
-        z64 w = {std::cos(ang), std::sin(ang)};
-        launch_zgemm(ctx->stream, 1, 0, cr, cr, cl, A + (size_t)s * cr, d * cr, tmp, cr, En, cr, w, t > 0 ? 1 : 0, 0);
+    const z64 one = {1.0, 0.0};
+    int i = 0;
+    for (;;) {
+      a.first = i;
+      while (i < n && small(i)) ++i;
+      a.last = i;
+      a.extract = a.first == 0;
+      a.e_in = a.first == 0 ? nullptr : E;
+      a.e_out = i < n ? E : nullptr;
+      a.result = i < n ? nullptr : reinterpret_cast<ExpectResult*>(ctx->rb_dev + kRbExpect);
+      launch_expect_chain(ctx->stream, a);
+      if (i == n) break;
+      for (; i < n && !small(i); ++i) {
+        const int cl = a.chi[i], cr = a.chi[i + 1];
+        launch_zgemm(ctx->stream, 0, 0, cl, d * cr, cl, E, cl, a.site[i], d * cr, ctx->B2, d * cr, one, 0, 0);
+        launch_weyl_site(ctx->stream, d, cl, cr, i, ctx->weyl, a.site[i], ctx->B);
+        launch_zgemm(ctx->stream, 1, 0, cr, cr, cl * d, ctx->B, cr, ctx->B2, cr, En, cr, one, 0, 0);
+        std::swap(E, En);
       }
-      std::swap(E, En);
     }
-    z64 e;
-    GC_HIP(hipMemcpyAsync(&e, E, sizeof(z64), hipMemcpyDeviceToHost, ctx->stream));
     GC_HIP(hipStreamSynchronize(ctx->stream));
-    std::complex<double> val = std::complex<double>(e.re, e.im) * std::polar(1.0, M_PI * P.p / d);
+    ExpectResult r;
+    std::memcpy(&r, ctx->rb + kRbExpect, sizeof(r));
+    const std::complex<double> val = std::complex<double>(r.value.re, r.value.im) * std::polar(1.0, M_PI * r.p / d);
     out[0] = val.real();
     out[1] = val.imag();
   });

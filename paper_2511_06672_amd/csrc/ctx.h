@@ -22,7 +22,7 @@ struct Layout {
   int nslots;
   size_t off_slots, off_theta, off_G, off_U, off_Z, off_Utmp, off_B, off_B2, off_sig2, off_sig, off_lam,
       off_perm, off_eigG, off_eigV, off_eigD, off_flags, off_s2, off_s2w, off_wlist, off_partial, off_nbuf, nbuf_bytes, off_q64, off_q32,
-      off_rtab, off_dtab, off_dtab32, off_qinv, off_tab, off_target, off_weyl, off_err, off_status, off_luts, off_sites, off_dense,
+      off_rtab, off_dtab, off_dtab32, off_qinv, off_tab, off_weyl, off_status, off_luts, off_sites, off_dense,
       dense_dim, off_pcst, off_chol, total;
 };
 
@@ -95,7 +95,7 @@ struct gcamps_ctx {
   int d = 0, n = 0;
   bool poisoned = false;
   // device regions
-  int *tx = nullptr, *tz = nullptr, *tp = nullptr, *target = nullptr, *derr = nullptr, *dsites = nullptr;
+  int *tx = nullptr, *tz = nullptr, *tp = nullptr, *dsites = nullptr;
   uint32_t* dluts = nullptr;
   DevWeyl* weyl = nullptr;
   DevStatus* st = nullptr;
@@ -189,7 +189,7 @@ struct gcamps_ctx {
   }
   static_assert(sizeof(DevStatus) <= kRbPcState && kRbPcState + sizeof(PcState) <= kRbChol &&
                     kRbChol + sizeof(CholState) <= kRbEig &&
-                    kRbWeyl + sizeof(DevWeyl) <= kRbWeylErr && kRbWeylErr + sizeof(int) <= kRbBytes,
+                    kRbWeyl + sizeof(DevWeyl) <= kRbExpect && kRbExpect + sizeof(ExpectResult) <= kRbBytes,
                 "read-back block layout");
   void read_status(DevStatus& h) {  // through pinned memory: no staging copy
     GC_HIP(hipMemcpyAsync(rb + kRbStatus, st, sizeof(DevStatus), hipMemcpyDeviceToHost, stream));
@@ -540,18 +540,17 @@ struct gcamps_ctx {
   // ---------------------------------------------------------------- bottom loop
   // P = C^dagger W C for a Weyl target W = tau^p X^x Z^z (x, z, p given as 2n+1 ints).
   GateRec extract_string(const int* xzp) {
-    int* tg = reinterpret_cast<int*>(stage_begin());
-    for (int i = 0; i < 2 * n + 1; ++i) tg[i] = xzp[i];
-    stage_upload(target, (2 * n + 1) * sizeof(int));
-    launch_weyl_extract(stream, n, d, tx, tz, tp, target, weyl, derr);
-    GC_HIP(hipMemcpyAsync(rb + kRbWeyl, weyl, sizeof(DevWeyl), hipMemcpyDeviceToHost, stream));
-    GC_HIP(hipMemcpyAsync(rb + kRbWeylErr, derr, sizeof(int), hipMemcpyDeviceToHost, stream));
+    WeylTarget W;
+    for (int i = 0; i < n; ++i) {
+      W.x[i] = (uint8_t)(((xzp[i] % d) + d) % d);
+      W.z[i] = (uint8_t)(((xzp[n + i] % d) + d) % d);
+    }
+    W.p = xzp[2 * n];
+    launch_weyl_extract(stream, n, d, tx, tz, tp, W, reinterpret_cast<DevWeyl*>(rb_dev + kRbWeyl));
     GC_HIP(hipStreamSynchronize(stream));
     DevWeyl P;
-    int err = 0;
     std::memcpy(&P, rb + kRbWeyl, sizeof(DevWeyl));
-    std::memcpy(&err, rb + kRbWeylErr, sizeof(int));
-    GC_CHECK(err == 0, GCAMPS_ENUMERIC, "tableau decomposition failed");
+    GC_CHECK(P.bad == 0, GCAMPS_ENUMERIC, "tableau decomposition failed");
     GateRec g;
     g.l = P.l;
     g.r = P.r;

@@ -122,13 +122,20 @@ struct DevStatus {
   int64_t ticks;       // small split: wall-clock ticks from the Gram to the truncation rule
 };
 
+// Weyl string to be commuted through the tableau (exponents in [0, d)), passed to kernels by value.
+struct WeylTarget {
+  uint8_t x[kMaxN];
+  uint8_t z[kMaxN];
+  int32_t p;
+};
+
 // Weyl string result of the commutation step (device layout).
 struct DevWeyl {
   int32_t x[kMaxN];
   int32_t z[kMaxN];
   int32_t p;
   int32_t l, r;
-  int32_t pad;
+  int32_t bad;  // nonzero: the rows did not multiply out to the target
 };
 
 // ----------------------------------------------------------------- compiled words

@@ -14,9 +14,38 @@ void launch_tableau_layer(hipStream_t s, int n, int d, int count, const int* sit
 // C <- C Q^dagger for the candidate selected in st->cstar (no-op when 0).
 void launch_tableau_right_mult(hipStream_t s, int n, int d, int site, const DevStatus* st,
                                const uint32_t* inv_luts, int* tx, int* tz, int* tp);
-// P = C^dagger W C for the target W (x, z, p) held in `target`; result in out.
+// P = C^dagger W C for the target W; out may be host memory that the device addresses.
 void launch_weyl_extract(hipStream_t s, int n, int d, const int* tx, const int* tz, const int* tp,
-                         const int* target, DevWeyl* out, int* err);
+                         const WeylTarget& target, DevWeyl* out);
+
+// ------------------------------------------------------------------ expectation (kernels_expect.hip)
+// A run of sites whose tensors have at most kExpectMaxSite entries and whose bonds at most kExpectMaxBond2
+// entries squared is contracted by one workgroup with E, A and E A in LDS (152 of 160 KB).  The line is what
+// fits: at bond 32, d = 3 a site costs it 11 us of matrix instructions at the single CU's rate, against three
+// launches of 6 us each for the form on the whole chip.
+constexpr int kExpectMaxSite = 4096;
+constexpr int kExpectMaxBond2 = 1600;
+struct ExpectResult {
+  z64 value;  // without the phase of P
+  int32_t p;  // tau exponent of P's phase
+};
+struct ExpectArgs {
+  int n, d, first, last;
+  int extract;            // commute target through the tableau (else P is *weyl)
+  const int *tx, *tz, *tp;
+  DevWeyl* weyl;          // P, written when extract and not null
+  const z64* e_in;        // left environment (chi x chi, row-major) at `first`; null: 1
+  z64* e_out;             // environment at `last`, when not null
+  ExpectResult* result;   // at the end of the chain, when not null (host memory that the device addresses)
+  WeylTarget target;
+  int chi[kMaxN + 1];
+  const z64* site[kMaxN];
+};
+void launch_expect_chain(hipStream_t s, const ExpectArgs& a);
+// out = the site tensor with the conjugate of P's factor at `site` applied from the bra's side:
+// out[(al, t), b] = conj(omega^{z t}) in[(al, t + x), b].
+void launch_weyl_site(hipStream_t s, int d, int chil, int chir, int site, const DevWeyl* P, const z64* in, z64* out);
+void expect_set_attributes();
 
 // ------------------------------------------------------------------ dense linear algebra
 // C = alpha * op(A) op(B) (+ C if accumulate); row-major, complex128; op 0 = N, 1 = conj-transpose.
@@ -60,7 +89,7 @@ inline JacobiCrit jacobi_crit(int m, int rel) {
 }
 // Offsets in a context's pinned read-back block: device status, pivoted and plain Cholesky
 // states, eigensolver slots, conjugated Weyl string and its error flag.
-constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbChol = 384, kRbEig = 512, kRbWeyl = 1024, kRbWeylErr = 2560, kRbBytes = 4096;
+constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbChol = 384, kRbEig = 512, kRbWeyl = 1024, kRbExpect = 2560, kRbBytes = 4096;
 // precheck: test every pair against the rotation criterion first and return U = I, lam =
 // diag(G) without a sweep when none qualifies (for matrices expected to be diagonal already,
 // e.g. a Rayleigh-Ritz step; the result equals what one sweep that rotates nothing leaves).

@@ -5,15 +5,11 @@
 // i and phase tp[r] (power of tau, mod 2d).  Rows 0..n-1 are S_k = C Z_k C^dagger, rows
 // n..2n-1 are D_k = C X_k C^dagger.  All arithmetic is exact integer arithmetic.
 #include "kernels.h"
+#include "weyl.h"
 
 namespace gc {
 
 namespace {
-
-__device__ __forceinline__ int imod(int v, int m) {
-  v %= m;
-  return v < 0 ? v + m : v;
-}
 
 // Sum over the 64 lanes of a wavefront (every lane receives the total).
 __device__ __forceinline__ int wave_sum(int v) {
@@ -139,75 +135,22 @@ __global__ void k_tableau_right_mult(int n, int d, int site, const DevStatus* st
   }
 }
 
-// P = C^dagger W C for the target W = tau^{p_t} X^{x_t} Z^{z_t} (target layout: x[n], z[n], p).
-// Exponents from the symplectic relations: delta_j = -lam(W, S_j), s_j = lam(W, D_j) with
-// lam(u, v) = <z_u, x_v> - <x_u, z_v>.  The phase follows from multiplying the rows out:
-// prod_j S_j^{s_j} D_j^{delta_j} = tau^q W(t), and P = W(delta, s, p_t - q + 2 <s, delta>).
-__global__ void k_weyl_extract(int n, int d, const int* __restrict__ tx, const int* __restrict__ tz,
-                               const int* __restrict__ tp, const int* __restrict__ target, DevWeyl* out,
-                               int* err) {
-  __shared__ int s_exp[kMaxN], d_exp[kMaxN];
+__global__ __launch_bounds__(kMaxN) void k_weyl_extract(int n, int d, const int* __restrict__ tx,
+                                                        const int* __restrict__ tz, const int* __restrict__ tp,
+                                                        WeylTarget target, DevWeyl* out) {
+  __shared__ DevWeyl P;
+  __shared__ WeylScratch ws;
+  weyl_commute(n, d, tx, tz, tp, target, P, ws);
   const int t = threadIdx.x;
-  const int* tgx = target;
-  const int* tgz = target + n;
-  const int pt = target[2 * n];
-  for (int j = t; j < n; j += blockDim.x) {
-    int ls = 0, ld = 0;
-    for (int i = 0; i < n; ++i) {
-      ls += tgz[i] * tx[j * n + i] - tgx[i] * tz[j * n + i];
-      ld += tgz[i] * tx[(n + j) * n + i] - tgx[i] * tz[(n + j) * n + i];
-    }
-    d_exp[j] = imod(-ls, d);
-    s_exp[j] = imod(ld, d);
+  if (t < n) {
+    out->x[t] = P.x[t];
+    out->z[t] = P.z[t];
   }
-  __syncthreads();
-  if (t >= 64) return;
-  const int lane = t;
-  WaveWeyl acc;
-  acc.x[0] = acc.x[1] = acc.z[0] = acc.z[1] = 0;
-  acc.p = 0;
-  for (int j = 0; j < n; ++j) {
-    if (s_exp[j]) {
-      WaveWeyl r;
-      ww_load(r, tx, tz, tp, j, n, lane);
-      ww_mul(acc, ww_pow(r, s_exp[j], d), d);
-    }
-    if (d_exp[j]) {
-      WaveWeyl r;
-      ww_load(r, tx, tz, tp, n + j, n, lane);
-      ww_mul(acc, ww_pow(r, d_exp[j], d), d);
-    }
-  }
-  int bad = 0;
-  for (int h = 0; h < 2; ++h) {
-    int i = lane + 64 * h;
-    if (i < n && (acc.x[h] != imod(tgx[i], d) || acc.z[h] != imod(tgz[i], d))) bad = 1;
-  }
-  bad = wave_sum(bad);
-  int sd = 0;
-  for (int h = 0; h < 2; ++h) {
-    int i = lane + 64 * h;
-    if (i < n) sd += s_exp[i] * d_exp[i];
-  }
-  sd = wave_sum(sd);
-  for (int h = 0; h < 2; ++h) {
-    int i = lane + 64 * h;
-    if (i < n) {
-      out->x[i] = d_exp[i];
-      out->z[i] = s_exp[i];
-    }
-  }
-  if (lane == 0) {
-    out->p = imod(pt - acc.p + 2 * imod(sd, d), 2 * d);
-    int l = -1, r = -1;
-    for (int i = 0; i < n; ++i)
-      if (d_exp[i] || s_exp[i]) {
-        if (l < 0) l = i;
-        r = i;
-      }
-    out->l = l;
-    out->r = r;
-    *err = bad ? 1 : 0;
+  if (t == 0) {
+    out->p = P.p;
+    out->l = P.l;
+    out->r = P.r;
+    out->bad = P.bad;
   }
 }
 
@@ -233,8 +176,8 @@ void launch_tableau_right_mult(hipStream_t s, int n, int d, int site, const DevS
 }
 
 void launch_weyl_extract(hipStream_t s, int n, int d, const int* tx, const int* tz, const int* tp,
-                         const int* target, DevWeyl* out, int* err) {
-  hipLaunchKernelGGL(k_weyl_extract, dim3(1), dim3(128), 0, s, n, d, tx, tz, tp, target, out, err);
+                         const WeylTarget& target, DevWeyl* out) {
+  hipLaunchKernelGGL(k_weyl_extract, dim3(1), dim3(kMaxN), 0, s, n, d, tx, tz, tp, target, out);
   GC_LAUNCH_CHECK();
 }
 
