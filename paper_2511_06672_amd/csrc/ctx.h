@@ -825,19 +825,18 @@ struct gcamps_ctx {
         const int mm = std::min(cl * d, d * cr), kk = std::max(cl * d, d * cr);
         int gram_used = 0;
         bool shortcut = false;
+        CommitRule rule{-1, ncand, s2, nullptr, nullptr, cfg.tie_tol, st, reinterpret_cast<DevStatus*>(rb_dev + kRbStatus)};
         if (frozen) {
           // replay: the recorded choice replaces scoring and selection
           GC_CHECK(choice_pos < choice_frz->size(), GCAMPS_EINVAL, "frozen replay ran past the recorded choices");
           const int c = (*choice_frz)[choice_pos++];
           GC_CHECK(c >= 0 && c < ncand, GCAMPS_EINVAL, "recorded choice outside the candidate set");
-          int* ci = reinterpret_cast<int*>(stage_begin());
-          *ci = c;
-          stage_upload(&st->cstar, sizeof(int));
+          rule.fixed = c;
           shortcut = (c == 0 && mm > kSmallEig);
           if (!shortcut) {
             launch_zgemm(stream, 0, 0, cl * d, d * cr, cm, site[i], cm, site[i + 1], d * cr, theta, d * cr,
                          z64{1.0, 0.0}, 0, 0);
-            launch_apply_q(stream, d, cl, cr, st, q64, theta);
+            if (c != 0) launch_commit(stream, d, rule, cl, cr, q64, theta, CommitTableau{});
           }
         } else {
           launch_zgemm(stream, 0, 0, cl * d, d * cr, cm, site[i], cm, site[i + 1], d * cr, theta, d * cr,
@@ -864,15 +863,14 @@ struct gcamps_ctx {
               std::memcpy(hr, ranks.data(), (size_t)ncand * sizeof(int32_t));
               stage_upload(wlist, (size_t)ncand * sizeof(int32_t));
             }
-            launch_select_rank(stream, ncand, wlist, s2, cfg.tie_tol, st);
-          } else if (prec == GCAMPS_SCORE_FP64) {
-            launch_select(stream, ncand, s2, cfg.tie_tol, st);
-          } else {
+            rule.rank = wlist;
+          } else if (prec != GCAMPS_SCORE_FP64) {
             launch_window(stream, ncand, s2, cfg.near_tie, wlist, st);
             GC_HIP(hipEventRecord(ev2, stream));
             score(GCAMPS_SCORE_FP64, cl, cr, wlist, &st->nwindow, s2w, f_ready);
             GC_HIP(hipEventRecord(ev3, stream));
-            launch_select_window(stream, wlist, s2w, cfg.tie_tol, st);
+            rule.list = wlist;
+            rule.s2 = s2w;
           }
           if (prec == GCAMPS_SCORE_REPLICA && mm > kScoreSmallM) {
             // Gram of Theta over the larger bond (Hermitian half), pair sum, one d^8 dot per candidate
@@ -883,16 +881,14 @@ struct gcamps_ctx {
             if (density) stats[4] += 4.0 * std::pow((double)std::min(cl, cr) * d * d, 2) * std::max(cl, cr);
           }
           stats[10] += 1;
-          launch_apply_q(stream, d, cl, cr, st, q64, theta);
-          launch_tableau_right_mult(stream, n, d, i, st, qinv, tx, tz, tp);
+          launch_commit(stream, d, rule, cl, cr, q64, theta, CommitTableau{n, i, qinv, tx, tz, tp});
           // When the identity is kept, Theta = A_i A_{i+1} with the neighbour of the centre
           // orthonormal (right-orthonormal A_{i+1} when sweeping left to right, left-orthonormal
           // A_i otherwise), so Theta's Schmidt values are those of the centre tensor alone and the
           // split only needs the factorisation of that (smaller) tensor.
           if (mm > kSmallEig) {
-            DevStatus pre;
-            read_status(pre);
-            shortcut = (pre.cstar == 0);
+            GC_HIP(hipStreamSynchronize(stream));
+            shortcut = reinterpret_cast<const DevStatus*>(rb + kRbStatus)->cstar == 0;
           }
         }
         DevStatus h;
@@ -927,12 +923,13 @@ struct gcamps_ctx {
           h = factorize(theta, cl * d, d * cr, 0, ltr ? 1 : 0, Lbuf, Rbuf, true);
           if (tape) {
             op.f = last_fact;
-            op.cstar = h.cstar;
+            op.cstar = frozen ? rule.fixed : h.cstar;
             tape->push_back(op);
           }
           std::swap(site[i], Lbuf);
           std::swap(site[i + 1], Rbuf);
         }
+        if (frozen) h.cstar = rule.fixed;
         stats[14] += shortcut ? 1 : 0;
         if (!frozen) {
           float ms = 0.f;

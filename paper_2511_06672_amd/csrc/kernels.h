@@ -11,9 +11,6 @@ namespace gc {
 void launch_tableau_init(hipStream_t s, int n, int* tx, int* tz, int* tp);
 void launch_tableau_layer(hipStream_t s, int n, int d, int count, const int* sites,
                           const uint32_t* luts, int* tx, int* tz, int* tp);
-// C <- C Q^dagger for the candidate selected in st->cstar (no-op when 0).
-void launch_tableau_right_mult(hipStream_t s, int n, int d, int site, const DevStatus* st,
-                               const uint32_t* inv_luts, int* tx, int* tz, int* tp);
 // P = C^dagger W C for the target W; out may be host memory that the device addresses.
 void launch_weyl_extract(hipStream_t s, int n, int d, const int* tx, const int* tz, const int* tp,
                          const WeylTarget& target, DevWeyl* out);
@@ -184,9 +181,6 @@ void launch_mpo_sum_site(hipStream_t s, int kind, int d, int J, int chil, int ch
 // out = Q_c Theta for the candidate c given by the host (a copy for c == 0).
 void launch_rotate_copy(hipStream_t s, int d, int chil, int chir, int c, const z64* qmats, const z64* theta,
                         z64* out);
-// Theta <- Q_{cstar} Theta in place (no-op when cstar == 0).  Theta (chil, d, d, chir).
-void launch_apply_q(hipStream_t s, int d, int chil, int chir, const DevStatus* st, const z64* qmats,
-                    z64* theta);
 // Candidate scores S2_c for the candidates cand_list[0..count) (or 0..count when cand_list is
 // null), in the arithmetic of `prec` (GCAMPS_SCORE_*; REPLICA takes the full set only and
 // needs replica_tables).  nlimit (nullable): device count that
@@ -199,7 +193,29 @@ void launch_score(hipStream_t s, int prec, int d, int chil, int chir, const z64*
                   const int* nlimit, double* s2, double* partial, size_t partial_cap, void* nbuf,
                   size_t nbuf_bytes, hipEvent_t* evs = nullptr, int evcap = 0, int* evused = nullptr,
                   const z64* replica_tables = nullptr);
-void launch_select(hipStream_t s, int count, const double* s2, double tie_tol, DevStatus* st);
+
+// ------------------------------------------------------------------ commit of a bond (kernels_commit.hip)
+// The choice: the lowest index with s2 <= min s2 + tol over the candidates 0..count, or over the
+// st->nwindow entries of list (s2 per entry); with ranks, over the candidates of the smallest rank and only
+// if that is below the identity's (else 0).  c* goes to st->cstar and host->cstar, the minimum to st->s2min.
+struct CommitRule {
+  int fixed;          // >= 0: this candidate, nothing is chosen and neither tableau nor status is written
+  int count;
+  const double* s2;
+  const int* list;    // window, or null
+  const int* rank;    // bond dimension per candidate, or null
+  double tol;
+  DevStatus* st;
+  DevStatus* host;    // host memory that the device addresses
+};
+struct CommitTableau {
+  int n, site;
+  const uint32_t* inv_luts;
+  int *tx, *tz, *tp;
+};
+// Theta <- Q_{c*} Theta in place, Theta (chil, d, d, chir), and the tableau C <- C Q_{c*}^dagger.
+void launch_commit(hipStream_t s, int d, const CommitRule& r, int chil, int chir, const z64* qmats, z64* theta,
+                   const CommitTableau& tb);
 
 // ------------------------------------------------------------------ bond-dimension criterion (kernels_rank.hip)
 constexpr int kRankMaxM = 32;        // smaller side of the two-site matrix
@@ -208,10 +224,6 @@ constexpr int kRankMaxElems = 8192;  // entries of the two-site matrix (LDS of o
 // singular values of reshape(Q_c Theta), one-sided Jacobi SVD per candidate).
 void launch_cand_rank(hipStream_t s, int d, int chil, int chir, const z64* theta, const z64* qmats, int count,
                       double cutoff, int chi_max, int* rank_out);
-// c* = 0 unless some candidate's rank is below the identity's; then the lowest index of the
-// smallest rank with s2 <= min s2 (over that rank) + tie_tol.
-void launch_select_rank(hipStream_t s, int count, const int* rank, const double* s2, double tie_tol,
-                        DevStatus* st);
 void rank_set_attributes();
 void linalg_set_attributes();  // the block-Jacobi rounds' dynamic LDS limit
 
@@ -248,9 +260,7 @@ void launch_score_replica(hipStream_t s, int d, int chil, int chir, const z64* t
 // list length goes to st->nwindow.
 void launch_window(hipStream_t s, int count, const double* s2lp, double window, int* list,
                    DevStatus* st);
-// FP64 rule over the window: c* = lowest listed index with s2 <= min + tie_tol.
-void launch_select_window(hipStream_t s, const int* list, const double* s2win, double tie_tol,
-                          DevStatus* st);
+
 // ------------------------------------------------------------------ dense state (kernels_dense.hip)
 // v <- C|0> for the tableau's Clifford C, not normalised (norm2 = its squared norm): the stabilizer
 // projectors applied to a fixed generic vector.  w is scratch; v and w trade places.

@@ -96,25 +96,7 @@ __global__ void k_mpo_sum_site(int kind, int d, int J, int chil, int chir, MpoTe
   out[idx] = v;
 }
 
-// ===================================================================================== apply Q
-__global__ void k_apply_q(int d, int chil, int chir, const DevStatus* __restrict__ st, const z64* __restrict__ qm,
-                          z64* __restrict__ theta) {
-  const int c = st->cstar;
-  if (c == 0) return;
-  size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)chil * chir) return;
-  const int a = (int)(idx / chir), b = (int)(idx % chir);
-  const int D2 = d * d;
-  const z64* q = qm + (size_t)c * D2 * D2;
-  z64 v[kMaxD * kMaxD];
-  for (int x = 0; x < D2; ++x) v[x] = theta[((size_t)a * D2 + x) * chir + b];
-  for (int y = 0; y < D2; ++y) {
-    z64 acc = {0.0, 0.0};
-    for (int x = 0; x < D2; ++x) acc = cadd(acc, cmul(q[y * D2 + x], v[x]));
-    theta[((size_t)a * D2 + y) * chir + b] = acc;
-  }
-}
-
+// ===================================================================================== rotation
 // out = Q_c Theta for an explicit candidate c (a copy when c == 0); Theta (chil, d, d, chir).
 __global__ void k_rotate_copy(int d, int chil, int chir, int c, const z64* __restrict__ qm,
                               const z64* __restrict__ theta, z64* __restrict__ out) {
@@ -893,36 +875,7 @@ __global__ void k_score_reduce(int ntp, const int* __restrict__ nlimit, int coun
   s2[slot] = -log(pur / (tr * tr));
 }
 
-// ===================================================================================== selection
-__global__ __launch_bounds__(1024) void k_select(int count, const double* __restrict__ s2, double tol,
-                                                 DevStatus* st) {
-  __shared__ double red[1024];
-  __shared__ int redi[1024];
-  const int t = threadIdx.x;
-  double mn = DBL_MAX;
-  for (int i = t; i < count; i += 1024) mn = fmin(mn, s2[i]);
-  red[t] = mn;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (t < off) red[t] = fmin(red[t], red[t + off]);
-    __syncthreads();
-  }
-  const double smin = red[0];
-  int best = 0x7fffffff;
-  for (int i = t; i < count; i += 1024)
-    if (s2[i] <= smin + tol && i < best) best = i;
-  redi[t] = best;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (t < off) redi[t] = min(redi[t], redi[t + off]);
-    __syncthreads();
-  }
-  if (t == 0) {
-    st->cstar = redi[0];
-    st->s2min = smin;
-  }
-}
-
+// ===================================================================================== window
 __global__ __launch_bounds__(1024) void k_window(int count, const double* __restrict__ s2lp, double window,
                                                  int* __restrict__ list, DevStatus* st) {
   __shared__ double red[1024];
@@ -962,36 +915,6 @@ __global__ __launch_bounds__(1024) void k_window(int count, const double* __rest
     if (s2lp[i] <= lim) list[pos++] = i;
 }
 
-__global__ __launch_bounds__(1024) void k_select_window(const int* __restrict__ list, const double* __restrict__ s2w,
-                                                        double tol, DevStatus* st) {
-  __shared__ double red[1024];
-  __shared__ int redi[1024];
-  const int t = threadIdx.x;
-  const int nw = st->nwindow;
-  double mn = DBL_MAX;
-  for (int i = t; i < nw; i += 1024) mn = fmin(mn, s2w[i]);
-  red[t] = mn;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (t < off) red[t] = fmin(red[t], red[t + off]);
-    __syncthreads();
-  }
-  const double smin = red[0];
-  int best = 0x7fffffff;
-  for (int i = t; i < nw; i += 1024)
-    if (s2w[i] <= smin + tol && list[i] < best) best = list[i];
-  redi[t] = best;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (t < off) redi[t] = min(redi[t], redi[t + off]);
-    __syncthreads();
-  }
-  if (t == 0) {
-    st->cstar = redi[0];
-    st->s2min = smin;
-  }
-}
-
 }  // namespace
 
 // ===================================================================================== launchers
@@ -1013,12 +936,6 @@ void launch_mpo_sum_site(hipStream_t s, int kind, int d, int J, int chil, int ch
   const size_t total = (size_t)ol * d * orr;
   hipLaunchKernelGGL(k_mpo_sum_site, dim3(blocks_for(total, 256)), dim3(256), 0, s, kind, d, J, chil, chir, terms, in,
                      out);
-  GC_LAUNCH_CHECK();
-}
-
-void launch_apply_q(hipStream_t s, int d, int chil, int chir, const DevStatus* st, const z64* qmats, z64* theta) {
-  size_t total = (size_t)chil * chir;
-  hipLaunchKernelGGL(k_apply_q, dim3(blocks_for(total, 128)), dim3(128), 0, s, d, chil, chir, st, qmats, theta);
   GC_LAUNCH_CHECK();
 }
 
@@ -1167,18 +1084,8 @@ void launch_score(hipStream_t s, int prec, int d, int chil, int chir, const z64*
   GC_LAUNCH_CHECK();
 }
 
-void launch_select(hipStream_t s, int count, const double* s2, double tie_tol, DevStatus* st) {
-  hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, s, count, s2, tie_tol, st);
-  GC_LAUNCH_CHECK();
-}
-
 void launch_window(hipStream_t s, int count, const double* s2lp, double window, int* list, DevStatus* st) {
   hipLaunchKernelGGL(k_window, dim3(1), dim3(1024), 0, s, count, s2lp, window, list, st);
-  GC_LAUNCH_CHECK();
-}
-
-void launch_select_window(hipStream_t s, const int* list, const double* s2win, double tie_tol, DevStatus* st) {
-  hipLaunchKernelGGL(k_select_window, dim3(1), dim3(1024), 0, s, list, s2win, tie_tol, st);
   GC_LAUNCH_CHECK();
 }
 

@@ -174,48 +174,6 @@ __global__ __launch_bounds__(kRankThreads) void k_cand_rank(int d, int chil, int
   }
 }
 
-// c* = 0 unless some candidate leaves a smaller rank than the identity; then, among the
-// candidates of the smallest rank, the lowest index with s2 <= min s2 + tol.
-__global__ __launch_bounds__(1024) void k_select_rank(int count, const int* __restrict__ rank,
-                                                      const double* __restrict__ s2, double tol, DevStatus* st) {
-  __shared__ double red[1024];
-  __shared__ int redi[1024];
-  const int t = threadIdx.x;
-  int rmin = INT_MAX;
-  for (int i = t; i < count; i += 1024) rmin = min(rmin, rank[i]);
-  redi[t] = rmin;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (t < off) redi[t] = min(redi[t], redi[t + off]);
-    __syncthreads();
-  }
-  const int rbest = redi[0];
-  __syncthreads();
-  double mn = DBL_MAX;
-  for (int i = t; i < count; i += 1024)
-    if (rank[i] == rbest) mn = fmin(mn, s2[i]);
-  red[t] = mn;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (t < off) red[t] = fmin(red[t], red[t + off]);
-    __syncthreads();
-  }
-  const double smin = red[0];
-  int best = INT_MAX;
-  for (int i = t; i < count; i += 1024)
-    if (rank[i] == rbest && s2[i] <= smin + tol && i < best) best = i;
-  redi[t] = best;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (t < off) redi[t] = min(redi[t], redi[t + off]);
-    __syncthreads();
-  }
-  if (t == 0) {
-    st->cstar = (rbest < rank[0]) ? redi[0] : 0;
-    st->s2min = smin;
-  }
-}
-
 }  // namespace
 
 void launch_cand_rank(hipStream_t s, int d, int chil, int chir, const z64* theta, const z64* qmats, int count,
@@ -228,11 +186,6 @@ void launch_cand_rank(hipStream_t s, int d, int chil, int chir, const z64* theta
   const size_t lds = 2 * (size_t)mp * k * sizeof(double);
   hipLaunchKernelGGL(k_cand_rank, dim3(count), dim3(kRankThreads), lds, s, d, chil, chir, theta, qmats, count, cutoff,
                      chi_max, rank_out);
-  GC_LAUNCH_CHECK();
-}
-
-void launch_select_rank(hipStream_t s, int count, const int* rank, const double* s2, double tie_tol, DevStatus* st) {
-  hipLaunchKernelGGL(k_select_rank, dim3(1), dim3(1024), 0, s, count, rank, s2, tie_tol, st);
   GC_LAUNCH_CHECK();
 }
 

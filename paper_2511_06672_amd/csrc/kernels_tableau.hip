@@ -11,13 +11,6 @@ namespace gc {
 
 namespace {
 
-// Sum over the 64 lanes of a wavefront (every lane receives the total).
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 __global__ void k_tableau_init(int n, int* tx, int* tz, int* tp) {
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
   int total = 2 * n * n;
@@ -52,89 +45,6 @@ __global__ void k_tableau_layer(int n, int d, int count, const int* __restrict__
   tp[r] = p;
 }
 
-// Weyl string held by one wavefront: lane owns sites lane and lane + 64.
-struct WaveWeyl {
-  int x[2], z[2];
-  int p;
-};
-
-__device__ __forceinline__ void ww_load(WaveWeyl& w, const int* tx, const int* tz, const int* tp, int row,
-                                        int n, int lane) {
-  for (int h = 0; h < 2; ++h) {
-    int i = lane + 64 * h;
-    w.x[h] = (i < n) ? tx[row * n + i] : 0;
-    w.z[h] = (i < n) ? tz[row * n + i] : 0;
-  }
-  w.p = tp[row];
-}
-
-// w^e: exponents times e, phase e*p + 2 <x,z> e(e-1)/2
-__device__ __forceinline__ WaveWeyl ww_pow(const WaveWeyl& w, int e, int d) {
-  int xz = wave_sum(w.x[0] * w.z[0] + w.x[1] * w.z[1]);
-  WaveWeyl o;
-  for (int h = 0; h < 2; ++h) {
-    o.x[h] = imod(e * w.x[h], d);
-    o.z[h] = imod(e * w.z[h], d);
-  }
-  o.p = imod(e * w.p + 2 * imod(xz, d) * (e * (e - 1) / 2), 2 * d);
-  return o;
-}
-
-// a * b: exponents add, phase p_a + p_b + 2 <z_a, x_b>
-__device__ __forceinline__ void ww_mul(WaveWeyl& a, const WaveWeyl& b, int d) {
-  int cross = wave_sum(a.z[0] * b.x[0] + a.z[1] * b.x[1]);
-  for (int h = 0; h < 2; ++h) {
-    a.x[h] = imod(a.x[h] + b.x[h], d);
-    a.z[h] = imod(a.z[h] + b.z[h], d);
-  }
-  a.p = imod(a.p + b.p + 2 * imod(cross, d), 2 * d);
-}
-
-// C <- C Q^dagger at pair (site, site+1).  For each Pauli P of the pair the new row is
-// C (Q^dagger P Q) C^dagger, i.e. the old rows multiplied out with the exponents of
-// Q^dagger P Q = tau^q X_a^xa Z_a^za X_b^xb Z_b^zb in the order D_a, S_a, D_b, S_b.
-__global__ void k_tableau_right_mult(int n, int d, int site, const DevStatus* st,
-                                     const uint32_t* __restrict__ inv_luts, int* tx, int* tz, int* tp) {
-  const int c = st->cstar;
-  if (c == 0) return;
-  const int lane = threadIdx.x;
-  const int D4 = d * d * d * d;
-  const uint32_t* lut = inv_luts + (size_t)c * D4;
-  const int a = site, b = site + 1;
-  WaveWeyl Sa, Sb, Da, Db;
-  ww_load(Sa, tx, tz, tp, a, n, lane);
-  ww_load(Sb, tx, tz, tp, b, n, lane);
-  ww_load(Da, tx, tz, tp, n + a, n, lane);
-  ww_load(Db, tx, tz, tp, n + b, n, lane);
-  // targets: Z_a, Z_b, X_a, X_b  (index v = ((xa*d + za)*d + xb)*d + zb)
-  const int tgt[4] = {d * d, 1, d * d * d, d};
-  const int rows[4] = {a, b, n + a, n + b};
-  WaveWeyl out[4];
-  for (int t = 0; t < 4; ++t) {
-    uint32_t e = lut[tgt[t]];
-    int img = (int)(e & 0xffffu);
-    int ezb = img % d, exb = (img / d) % d, eza = (img / (d * d)) % d, exa = img / (d * d * d);
-    WaveWeyl acc;
-    acc.x[0] = acc.x[1] = acc.z[0] = acc.z[1] = 0;
-    acc.p = (int)(e >> 16);
-    ww_mul(acc, ww_pow(Da, exa, d), d);
-    ww_mul(acc, ww_pow(Sa, eza, d), d);
-    ww_mul(acc, ww_pow(Db, exb, d), d);
-    ww_mul(acc, ww_pow(Sb, ezb, d), d);
-    out[t] = acc;
-  }
-  for (int t = 0; t < 4; ++t) {
-    for (int h = 0; h < 2; ++h) {
-      int i = lane + 64 * h;
-      if (i < n) {
-        tx[rows[t] * n + i] = out[t].x[h];
-        tz[rows[t] * n + i] = out[t].z[h];
-      }
-    }
-    if (lane == 0) tp[rows[t]] = out[t].p;
-  }
-}
-
 __global__ __launch_bounds__(kMaxN) void k_weyl_extract(int n, int d, const int* __restrict__ tx,
                                                         const int* __restrict__ tz, const int* __restrict__ tp,
                                                         WeylTarget target, DevWeyl* out) {
@@ -166,12 +76,6 @@ void launch_tableau_layer(hipStream_t s, int n, int d, int count, const int* sit
                           int* tx, int* tz, int* tp) {
   hipLaunchKernelGGL(k_tableau_layer, dim3((2 * n + 127) / 128), dim3(128), 0, s, n, d, count, sites, luts,
                      tx, tz, tp);
-  GC_LAUNCH_CHECK();
-}
-
-void launch_tableau_right_mult(hipStream_t s, int n, int d, int site, const DevStatus* st,
-                               const uint32_t* inv_luts, int* tx, int* tz, int* tp) {
-  hipLaunchKernelGGL(k_tableau_right_mult, dim3(1), dim3(64), 0, s, n, d, site, st, inv_luts, tx, tz, tp);
   GC_LAUNCH_CHECK();
 }
 
