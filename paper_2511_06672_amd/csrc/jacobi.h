@@ -106,103 +106,141 @@ __device__ __forceinline__ double row_next(double x) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// Both step loops below hold the Hermitian H as complex elements in two LDS buffers (one read, one
-// written by a step; one barrier per step).  Element (i, j) sits at i * LD + j with LD = 32
-// (16 for at most 16 indices): a row of 16 consecutive elements and the 16 diagonal or
-// pair-diagonal elements of a step fall in distinct banks.  A step's blocks and its share of the
-// eigenvector update go to different waves: H item (k1, k2) is the 2x2 block of pairs k1 and k2
-// and needs both rotations, V item (k1, k2) applies rotation k1 to two rows of the accumulator.
-// Each thread computes the rotations it needs itself: a step is bound by its FP64 issue slots
-// (two waves per SIMD) and by one dependent chain LDS read, rotation, update, LDS write, barrier.
+// x of the first lane of the same 16-lane row (DPP row broadcast).
+__device__ __forceinline__ double row_first(double x) {
+  const long long v = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_mov_dpp((int)v, 0x150, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), 0x150, 0xF, 0xF, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// The step loops below work on 512 threads: of the first 256, H item (k1, k2) is the 2x2 block of pairs
+// k1 and k2 and needs both rotations; of the others, V item (k1, k2) applies rotation k1 to two rows of the
+// eigenvector accumulator.  A step is bound by its FP64 issue slots (two waves per SIMD), its LDS
+// accesses and one dependent chain LDS read, rotation, update, LDS write, barrier.
+// The items of a 16-lane row share k1 and start at k2 = k1: every lane computes rotation k2 and takes
+// rotation k1 from the first lane.  The V items follow one step behind with the rotations that the first
+// row leaves in LDS, off the H items' chain.  With both rotations computed by every H thread, rotation
+// k1 by every V thread and all four elements through LDS, a 27 x 81 split took 206 us against 156 us and an
+// inter-block round at m = 243 13.3 us against 12.0 us.
+struct RotSlot {
+  z64 s;
+  double c, pad;
+};
 
 // The inter-block steps of a 32-index sub-problem on 512 threads: step s (0..15) pairs index
 // k < 16 with q_k(s) = 16 + (k + s) mod 16, so the 16 steps visit every pair (i < 16 <= j) once and
-// leave the matrix in h0.  The eigenvector accumulator starts from vi (32 x 32, row-major; null: the
-// identity) and ends in vo.
-// Threads 256..511 hold V in registers: thread (k1 = t mod 16, k2 = (t - 256) / 16) keeps rows
-// k2 and k2 + 16 of columns k1 and q_k1(s).  It applies rotation k1, then takes column
-// q_k1(s + 1) = q_{k1+1}(s) from the next lane of its 16-lane row; after 16 steps the columns
-// are back at 16 + k1.
+// leave the matrix in h0 (32 x 32, row-major; h1 is scratch).  The eigenvector accumulator starts from vi (32 x 32,
+// row-major; null: the identity) and ends in vo.
+// H and V live in registers.  After a step pair k takes over index q_{k+1}: an element (p1, q2) comes
+// from the next lane of its row, (q1, p2) and (q1, q2) from the next row through LDS, and the next step's
+// diagonal and pair elements go to LDS beside them.  After 16 steps the indices are back.
 template <bool REL>
 __device__ __forceinline__ void jacobi_ib_steps(z64* __restrict__ h0, z64* __restrict__ h1, const z64* vi, z64* vo,
                                                 const JacobiThr& jt) {
-  const int t = threadIdx.x, e = t & 255;
-  const bool do_v = t >= 256;  // uniform over each wave
-  const int k1 = do_v ? (e & 15) : (e >> 4), k2 = do_v ? (e >> 4) : (e & 15);
-  // V thread: columns (p, q) of rows k2 (x*) and k2 + 16 (y*)
-  z64 xp = {(k1 == k2) ? 1.0 : 0.0, 0.0}, xq = {0.0, 0.0}, yp = {0.0, 0.0}, yq = xp;
-  if (do_v && vi) {
-    xp = vi[k2 * 32 + k1];
-    xq = vi[k2 * 32 + 16 + k1];
-    yp = vi[(k2 + 16) * 32 + k1];
-    yq = vi[(k2 + 16) * 32 + 16 + k1];
-  }
+  const int t = threadIdx.x, e = t & 255, l = e & 15;
+  if (__builtin_amdgcn_readfirstlane(t >> 8) == 0) {  // uniform over each wave
+    const int k1 = e >> 4, k2 = (l + k1) & 15, down = ((k1 + 1) & 15) * 16;
+    z64 a = h0[k1 * 32 + k2], b = h0[k1 * 32 + 16 + k2];
+    z64 c = h0[(16 + k1) * 32 + k2], d = h0[(16 + k1) * 32 + 16 + k2];
+    d2 ab = {h0[k2 * 33].re, h0[(16 + k2) * 33].re};
+    z64 g = h0[k2 * 32 + 16 + k2];
+    RotSlot* rot = reinterpret_cast<RotSlot*>(h1 + 544);
+    // exchange buffers of even and odd steps: h0 is free once every thread has read its elements
 #pragma unroll 2
-  for (int step = 0; step < 16; ++step) {
-    const z64* __restrict__ in = (step & 1) ? h1 : h0;
-    z64* __restrict__ out = (step & 1) ? h0 : h1;
-    const int q1 = 16 + ((k1 + step) & 15);
-    const double a1 = in[k1 * 33].re, b1 = in[q1 * 33].re;
-    const z64 g1 = in[k1 * 32 + q1];
-    if (!do_v) {
-      const int q2 = 16 + ((k2 + step) & 15);
-      const double a2 = in[k2 * 33].re, b2 = in[q2 * 33].re;
-      const z64 g2 = in[k2 * 32 + q2];
-      z64 a = in[k1 * 32 + k2], b = in[k1 * 32 + q2], c = in[q1 * 32 + k2], d = in[q1 * 32 + q2];
-      const Rot r1 = make_rot<REL>(a1, b1, g1.re, g1.im, jt), r2 = make_rot<REL>(a2, b2, g2.re, g2.im, jt);
+    for (int step = 0; step < 16; ++step) {
+      z64* x = (step & 1) ? h0 : h1;
+      const Rot r2 = make_rot<REL>(ab.x, ab.y, g.re, g.im, jt);
+      const Rot r1 = {row_first(r2.c), row_first(r2.sr), row_first(r2.si)};
+      if (e < 16) rot[(step & 1) * 16 + l] = RotSlot{{r2.sr, r2.si}, r2.c, 0.0};
       rot_rows(a, c, r1);
       rot_rows(b, d, r1);
       rot_cols(a, b, r2);
       rot_cols(c, d, r2);
-      out[k1 * 32 + k2] = a;
-      out[k1 * 32 + q2] = b;
-      out[q1 * 32 + k2] = c;
-      out[q1 * 32 + q2] = d;
-    } else {
-      const Rot r1 = make_rot<REL>(a1, b1, g1.re, g1.im, jt);
-      rot_cols(xp, xq, r1);
-      rot_cols(yp, yq, r1);
+      if (step == 15) break;
+      x[e] = c;
+      x[256 + e] = d;
+      double* px = reinterpret_cast<double*>(x + 512);
+      if (l == 0) {
+        px[2 * k1] = a.re;
+        px[2 * ((k1 + 15) & 15) + 1] = d.re;
+      } else if (l == 1) {
+        x[528 + k1] = b;
+      }
+      b = z64{row_next(b.re), row_next(b.im)};
+      __syncthreads();
+      c = x[down + ((l + 15) & 15)];
+      d = x[256 + down + l];
+      ab = reinterpret_cast<const d2*>(x + 512)[k2];
+      g = x[528 + k2];
+    }
+    const int q1 = 16 + ((k1 + 15) & 15), q2 = 16 + ((k2 + 15) & 15);
+    h0[k1 * 32 + k2] = a;
+    h0[k1 * 32 + q2] = b;
+    h0[q1 * 32 + k2] = c;
+    h0[q1 * 32 + q2] = d;
+    __syncthreads();
+  } else {
+    // columns (p, q) = (l, q_l) of rows k2 (x*) and k2 + 16 (y*)
+    const int k2 = e >> 4;
+    z64 xp = {(l == k2) ? 1.0 : 0.0, 0.0}, xq = {0.0, 0.0}, yp = {0.0, 0.0}, yq = xp;
+    if (vi) {
+      xp = vi[k2 * 32 + l];
+      xq = vi[k2 * 32 + 16 + l];
+      yp = vi[(k2 + 16) * 32 + l];
+      yq = vi[(k2 + 16) * 32 + 16 + l];
+    }
+    const RotSlot* rot = reinterpret_cast<const RotSlot*>(h1 + 544);
+#pragma unroll 2
+    for (int step = 0; step < 16; ++step) {
+      __syncthreads();
+      const RotSlot s = rot[(step & 1) * 16 + l];
+      const Rot r = {s.c, s.s.re, s.s.im};
+      rot_cols(xp, xq, r);
+      rot_cols(yp, yq, r);
       xq = z64{row_next(xq.re), row_next(xq.im)};
       yq = z64{row_next(yq.re), row_next(yq.im)};
     }
-    __syncthreads();
-  }
-  if (do_v) {
-    vo[k2 * 32 + k1] = xp;
-    vo[k2 * 32 + 16 + k1] = xq;
-    vo[(k2 + 16) * 32 + k1] = yp;
-    vo[(k2 + 16) * 32 + 16 + k1] = yq;
+    vo[k2 * 32 + l] = xp;
+    vo[k2 * 32 + 16 + l] = xq;
+    vo[(k2 + 16) * 32 + l] = yp;
+    vo[(k2 + 16) * 32 + 16 + l] = yq;
   }
 }
 
 // The steps inside the two 16-blocks of a 32-index sub-problem on 512 threads: step s (1..15) pairs
 // i with i xor s in each block, eight pairs per block, so the 15 steps visit every pair of a block
-// once and leave the matrix in h1.  Pair k < 8 of the first block starts at the element whose
+// once and leave the matrix in h1.  H is held in the two LDS buffers (one read, one written by a step):
+// element (i, j) at i * 32 + j, so that a row of 16 consecutive elements and the 16 diagonal or pair elements of
+// a step fall in distinct banks.  Pair k < 8 of the first block starts at the element whose
 // lowest set bit of s is clear, pair k >= 8 of the second at one where it is set: the 16 first (and
-// the 16 second) elements of a step then differ modulo 16 and fall in distinct banks.  v (32 x 32,
+// the 16 second) elements of a step then differ modulo 16.  v (32 x 32,
 // LDS) is updated in place; FIRST: v is the identity before, so only its diagonal blocks change
-// (one row per V thread, otherwise two).  A round-robin order over the 32 indices, whose accesses
-// conflict and whose V traffic doubles, took 0.69 us per step.
+// (one row per V thread, otherwise two).  Ends with a barrier.
+__device__ __forceinline__ void intra_pair(int k, int s, int& p, int& q) {
+  const int bit = s & -s, low = bit - 1, c = k & 7;
+  p = (((c & ~low) << 1) | (c & low)) + (k >= 8 ? 16 + bit : 0);
+  q = p ^ s;
+}
 template <bool REL, bool FIRST>
 __device__ __forceinline__ void jacobi_intra_steps(z64* __restrict__ h0, z64* __restrict__ h1, z64* __restrict__ v,
                                                    const JacobiThr& jt) {
-  const int t = threadIdx.x, e = t & 255;
-  const bool do_v = t >= 256;  // uniform over each wave
-  const int k1 = do_v ? (e & 15) : (e >> 4), k2 = do_v ? (e >> 4) : (e & 15);
-  z64* x = v + (k2 + (FIRST && k1 >= 8 ? 16 : 0)) * 32;
-  for (int s = 1; s < 16; ++s) {
-    const z64* __restrict__ in = (s & 1) ? h0 : h1;
-    z64* __restrict__ out = (s & 1) ? h1 : h0;
-    const int bit = s & -s, low = bit - 1;
-    const int c1 = k1 & 7, p1 = (((c1 & ~low) << 1) | (c1 & low)) + (k1 >= 8 ? 16 + bit : 0), q1 = p1 ^ s;
-    const double a1 = in[p1 * 33].re, b1 = in[q1 * 33].re;
-    const z64 g1 = in[p1 * 32 + q1];
-    if (!do_v) {
-      const int c2 = k2 & 7, p2 = (((c2 & ~low) << 1) | (c2 & low)) + (k2 >= 8 ? 16 + bit : 0), q2 = p2 ^ s;
+  __shared__ RotSlot rot[32];
+  const int t = threadIdx.x, e = t & 255, l = e & 15;
+  if (__builtin_amdgcn_readfirstlane(t >> 8) == 0) {  // uniform over each wave
+    const int k1 = e >> 4, k2 = (l + k1) & 15;
+    for (int s = 1; s < 16; ++s) {
+      const z64* __restrict__ in = (s & 1) ? h0 : h1;
+      z64* __restrict__ out = (s & 1) ? h1 : h0;
+      int p1, q1, p2, q2;
+      intra_pair(k1, s, p1, q1);
+      intra_pair(k2, s, p2, q2);
       const double a2 = in[p2 * 33].re, b2 = in[q2 * 33].re;
       const z64 g2 = in[p2 * 32 + q2];
       z64 a = in[p1 * 32 + p2], b = in[p1 * 32 + q2], c = in[q1 * 32 + p2], d = in[q1 * 32 + q2];
-      const Rot r1 = make_rot<REL>(a1, b1, g1.re, g1.im, jt), r2 = make_rot<REL>(a2, b2, g2.re, g2.im, jt);
+      const Rot r2 = make_rot<REL>(a2, b2, g2.re, g2.im, jt);
+      const Rot r1 = {row_first(r2.c), row_first(r2.sr), row_first(r2.si)};
+      if (e < 16) rot[(s & 1) * 16 + l] = RotSlot{{r2.sr, r2.si}, r2.c, 0.0};
       rot_rows(a, c, r1);
       rot_rows(b, d, r1);
       rot_cols(a, b, r2);
@@ -211,21 +249,32 @@ __device__ __forceinline__ void jacobi_intra_steps(z64* __restrict__ h0, z64* __
       out[p1 * 32 + q2] = b;
       out[q1 * 32 + p2] = c;
       out[q1 * 32 + q2] = d;
-    } else {
-      const Rot r1 = make_rot<REL>(a1, b1, g1.re, g1.im, jt);
-      z64 xp = x[p1], xq = x[q1];
-      rot_cols(xp, xq, r1);
-      x[p1] = xp;
-      x[q1] = xq;
+      __syncthreads();
+    }
+  } else {
+    z64* x = v + ((e >> 4) + (FIRST && l >= 8 ? 16 : 0)) * 32;
+    for (int s = 1; s < 16; ++s) {
+      int p, q;
+      intra_pair(l, s, p, q);
+      z64 xp = x[p], xq = x[q], yp = {0.0, 0.0}, yq = yp;
       if (!FIRST) {
-        z64 yp = x[16 * 32 + p1], yq = x[16 * 32 + q1];
-        rot_cols(yp, yq, r1);
-        x[16 * 32 + p1] = yp;
-        x[16 * 32 + q1] = yq;
+        yp = x[16 * 32 + p];
+        yq = x[16 * 32 + q];
+      }
+      __syncthreads();
+      const RotSlot o = rot[(s & 1) * 16 + l];
+      const Rot r = {o.c, o.s.re, o.s.im};
+      rot_cols(xp, xq, r);
+      x[p] = xp;
+      x[q] = xq;
+      if (!FIRST) {
+        rot_cols(yp, yq, r);
+        x[16 * 32 + p] = yp;
+        x[16 * 32 + q] = yq;
       }
     }
-    __syncthreads();
   }
+  __syncthreads();
 }
 
 // A full round-robin sweep (mp - 1 steps of mp / 2 pairs, mp <= 2 HM even) over H and the

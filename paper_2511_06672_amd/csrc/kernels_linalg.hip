@@ -476,9 +476,10 @@ template <bool REL>
 __device__ void solve_pair(int k, const z64* __restrict__ Gs, int mp, int nb, int step, int ps,
                            const z64* __restrict__ Vp, const z64* __restrict__ Dp, const int* __restrict__ pfp,
                            const JacobiThr& jt, z64* __restrict__ Vout, z64* __restrict__ Dout,
-                           int* __restrict__ pair_flag, int* __restrict__ any_flag, z64* __restrict__ pool,
-                           int& need) {
+                           int* __restrict__ pair_flag, int* __restrict__ any_flag, const int* __restrict__ prev_any,
+                           z64* __restrict__ pool, int& need) {
   const int t = threadIdx.x;
+  const int live = prev_any ? *prev_any : 1;  // tested after the loads below are on their way
   z64 *h0 = pool, *h1 = pool + BJ2 * BJ2, *v = pool + 2 * BJ2 * BJ2;
   int I, J;
   rr_pair(k, step, nb, I, J);
@@ -496,6 +497,7 @@ __device__ void solve_pair(int k, const z64* __restrict__ Gs, int mp, int nb, in
   } else {
     rebuild_pair(I, J, Gs, mp, nb, ps, Vp, Dp, pfp, h1, v, h0);
   }
+  if (!live) return;
   __syncthreads();
   bool hit = false;
 #pragma unroll
@@ -533,11 +535,10 @@ __device__ void solve_pair(int k, const z64* __restrict__ Gs, int mp, int nb, in
 // prev_any that holds 0 (the sweep before rotated nothing) the round does nothing: rounds may be
 // launched before the host knows that the sweeps have converged.
 //
-// What bounds it: a round is as long as one solve.  At m = 243 a round takes 12.9 us (20.1 before): 16
-// steps of 0.42 us (0.69 before: rotations without the refinements an angle does not need and
-// complex LDS accesses), the launch, the loads and the two small products of the rebuild; the
-// rounds that start a sweep 21.5 us (28 with a round-robin order).  At m = 600 with the relative
-// criterion 16.4 us (22.0 before).
+// What bounds it: a round is as long as one solve.  At m = 243 a round takes 12.0 us (20.1 with one
+// refined rotation per thread and scalar LDS accesses): the launch and the loads 4 to 5 us (what a round
+// without rotations takes), the two small products of the rebuild and 16 steps of 0.3 to 0.4 us; the
+// rounds that start a sweep 20 us.  At m = 384 with the relative criterion 13.4 us.
 // Launched with kJroundPad bytes of (unused) dynamic LDS, a block holds more than half of a CU's
 // 160 KB, so a solve never shares its SIMDs with tile updates.  That pays while the updates are few
 // (m = 768: 16.6 against 17.9 ms per decomposition) and costs once they dominate (m = 1024: 29.8
@@ -559,13 +560,13 @@ __global__ __launch_bounds__(512) void k_jround(const z64* __restrict__ Gs, z64*
   __shared__ int need;
   const int half = nb / 2, nsolve = step >= 0 ? half : 0, ngt = half * (half + 1) / 2;
   int b = blockIdx.x;
-  if (prev_any && !*prev_any) return;
   if (b < nsolve) {
     // thresholds from the trace on the device (read by no host sync)
     const JacobiThr jt = jacobi_thr(*trace, tol, skip_rel, REL, floor_rel);
-    solve_pair<REL>(b, Gs, mp, nb, step, ps, Vp, Dp, pfp, jt, Vout, Dout, pair_flag, any_flag, pool, need);
+    solve_pair<REL>(b, Gs, mp, nb, step, ps, Vp, Dp, pfp, jt, Vout, Dout, pair_flag, any_flag, prev_any, pool, need);
     return;
   }
+  if (prev_any && !*prev_any) return;
   b -= nsolve;
   const int sub = threadIdx.x >> 8, ngb = (ngt + kTilesPerBlock - 1) / kTilesPerBlock;
   if (b < ngb)
