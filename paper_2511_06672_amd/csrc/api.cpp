@@ -285,7 +285,8 @@ int32_t gcamps_init(const gcamps_config* cfg, void* dev_workspace, size_t bytes,
     c->chst = reinterpret_cast<CholState*>(w + lay.off_chol);
     c->pinned_bytes = std::max<size_t>(1 << 20, (size_t)n * 2401 * 4 + 4096);
     GC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->pinned), c->pinned_bytes, hipHostMallocDefault));
-    GC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->rb), kRbBytes, hipHostMallocDefault));
+    GC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->rb), kRbBytes, hipHostMallocMapped | hipHostMallocCoherent));
+    std::memset(c->rb, 0, kRbBytes);
     GC_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&c->rb_dev), c->rb, 0));
     int clock_khz = 0;
     GC_HIP(hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev));
@@ -531,6 +532,7 @@ int32_t gcamps_expectation(gcamps_ctx* ctx, const int8_t* x, const int8_t* z, in
     a.tz = ctx->tz;
     a.tp = ctx->tp;
     a.weyl = ctx->weyl;
+    a.ticket = ++ctx->ticket;
     std::copy(ctx->chi.begin(), ctx->chi.begin() + n + 1, a.chi);
     // runs of small sites in one launch each, the sites between them by products on the whole chip;
     // buffers: Utmp (E), Z (E'), B2 (E A), B (the bra's tensor)
@@ -560,7 +562,7 @@ int32_t gcamps_expectation(gcamps_ctx* ctx, const int8_t* x, const int8_t* z, in
         std::swap(E, En);
       }
     }
-    GC_HIP(hipStreamSynchronize(ctx->stream));
+    ctx->await(reinterpret_cast<ExpectResult*>(ctx->rb + kRbExpect)->ticket, a.ticket);
     ExpectResult r;
     std::memcpy(&r, ctx->rb + kRbExpect, sizeof(r));
     const std::complex<double> val = std::complex<double>(r.value.re, r.value.im) * std::polar(1.0, M_PI * r.p / d);

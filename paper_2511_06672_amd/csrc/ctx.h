@@ -126,6 +126,8 @@ struct gcamps_ctx {
   // pinned staging
   char* pinned = nullptr;
   char* rb = nullptr;  // pinned read-back block (status, Cholesky state, eigensolver flags)
+  Ticket ticket = 0;       // of the last launch that announces its results in rb
+  static constexpr int kPollMs = 2;
   char* rb_dev = nullptr;  // the same block as the device addresses it
   double tick_ms = 0.0;    // one tick of the device's wall clock in ms
   size_t pinned_bytes = 0;
@@ -189,8 +191,23 @@ struct gcamps_ctx {
   }
   static_assert(sizeof(DevStatus) <= kRbPcState && kRbPcState + sizeof(PcState) <= kRbChol &&
                     kRbChol + sizeof(CholState) <= kRbEig &&
-                    kRbWeyl + sizeof(DevWeyl) <= kRbExpect && kRbExpect + sizeof(ExpectResult) <= kRbBytes,
+                    kRbWeyl + sizeof(DevWeyl) <= kRbExpect && kRbExpect + sizeof(ExpectResult) <= kRbCommit &&
+                    kRbCommit + sizeof(CommitResult) <= kRbBytes,
                 "read-back block layout");
+  // Waits until the launch with ticket `want` has announced its results (slot: in the read-back block).
+  // Polling returns 5 us earlier than a wait for the stream (an expectation of one launch: 53 against 58 us);
+  // after kPollMs the stream is waited for, which also reports a launch that failed.
+  void await(const Ticket& slot, Ticket want) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int i = 1; __atomic_load_n(&slot, __ATOMIC_ACQUIRE) != want; ++i) {
+      __builtin_ia32_pause();
+      if ((i & 63) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(kPollMs)) {
+        GC_HIP(hipStreamSynchronize(stream));
+        GC_CHECK(__atomic_load_n(&slot, __ATOMIC_ACQUIRE) == want, GCAMPS_EDEVICE, "a launch left no result");
+        return;
+      }
+    }
+  }
   void read_status(DevStatus& h) {  // through pinned memory: no staging copy
     GC_HIP(hipMemcpyAsync(rb + kRbStatus, st, sizeof(DevStatus), hipMemcpyDeviceToHost, stream));
     GC_HIP(hipStreamSynchronize(stream));
@@ -436,9 +453,9 @@ struct gcamps_ctx {
     int force_k, force_pass2;
     forced_decision(force_k, force_pass2);
     SplitArgs a{M, p, q, left_ortho, mode == 0 ? 1 : 0, force_pass2, {cfg.cutoff, cfg.chi_max, mode, force_k},
-                U, B, Lout, Rout, sig, perm, st, reinterpret_cast<DevStatus*>(rb_dev + kRbStatus)};
+                U, B, Lout, Rout, sig, perm, st, reinterpret_cast<DevStatus*>(rb_dev + kRbStatus), ++ticket};
     launch_split_small(stream, a);
-    GC_HIP(hipStreamSynchronize(stream));
+    await(reinterpret_cast<DevStatus*>(rb + kRbStatus)->ticket, a.ticket);
     DevStatus h;
     std::memcpy(&h, rb + kRbStatus, sizeof(DevStatus));
     GC_CHECK(h.converged, GCAMPS_ENUMERIC, "eigensolver did not converge");
@@ -546,8 +563,9 @@ struct gcamps_ctx {
       W.z[i] = (uint8_t)(((xzp[n + i] % d) + d) % d);
     }
     W.p = xzp[2 * n];
-    launch_weyl_extract(stream, n, d, tx, tz, tp, W, reinterpret_cast<DevWeyl*>(rb_dev + kRbWeyl));
-    GC_HIP(hipStreamSynchronize(stream));
+    ++ticket;
+    launch_weyl_extract(stream, n, d, tx, tz, tp, W, reinterpret_cast<DevWeyl*>(rb_dev + kRbWeyl), ticket);
+    await(reinterpret_cast<DevWeyl*>(rb + kRbWeyl)->ticket, ticket);
     DevWeyl P;
     std::memcpy(&P, rb + kRbWeyl, sizeof(DevWeyl));
     GC_CHECK(P.bad == 0, GCAMPS_ENUMERIC, "tableau decomposition failed");
@@ -825,7 +843,8 @@ struct gcamps_ctx {
         const int mm = std::min(cl * d, d * cr), kk = std::max(cl * d, d * cr);
         int gram_used = 0;
         bool shortcut = false;
-        CommitRule rule{-1, ncand, s2, nullptr, nullptr, cfg.tie_tol, st, reinterpret_cast<DevStatus*>(rb_dev + kRbStatus)};
+        CommitRule rule{-1, ncand, s2, nullptr, nullptr, cfg.tie_tol, st,
+                        reinterpret_cast<CommitResult*>(rb_dev + kRbCommit), ++ticket};
         if (frozen) {
           // replay: the recorded choice replaces scoring and selection
           GC_CHECK(choice_pos < choice_frz->size(), GCAMPS_EINVAL, "frozen replay ran past the recorded choices");
@@ -887,8 +906,9 @@ struct gcamps_ctx {
           // A_i otherwise), so Theta's Schmidt values are those of the centre tensor alone and the
           // split only needs the factorisation of that (smaller) tensor.
           if (mm > kSmallEig) {
-            GC_HIP(hipStreamSynchronize(stream));
-            shortcut = reinterpret_cast<const DevStatus*>(rb + kRbStatus)->cstar == 0;
+            CommitResult* made = reinterpret_cast<CommitResult*>(rb + kRbCommit);
+            await(made->ticket, rule.ticket);
+            shortcut = made->cstar == 0;
           }
         }
         DevStatus h;
@@ -933,6 +953,7 @@ struct gcamps_ctx {
         stats[14] += shortcut ? 1 : 0;
         if (!frozen) {
           float ms = 0.f;
+          GC_HIP(hipEventSynchronize(prec != GCAMPS_SCORE_FP64 && !rule.rank ? ev3 : ev1));
           GC_HIP(hipEventElapsedTime(&ms, ev0, ev1));
           stats[6] += ms;
           if (gram_used > 0) {  // Gram-purity kernel alone: algorithmic 4 m^2 k flop per candidate

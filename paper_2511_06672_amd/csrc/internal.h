@@ -103,6 +103,15 @@ constexpr int kReduceMaxM = 1024;
 constexpr double kDensityMinWork = 25000;
 constexpr int kBlk = 16;        // block size of the multi-workgroup block Jacobi
 
+// ----------------------------------------------------------------- results in host memory
+// A kernel that ends a host decision writes its result to pinned coherent host memory and then the ticket of its
+// launch beside it (announce); the host waits for the ticket instead of for the stream.
+using Ticket = uint32_t;
+__device__ __forceinline__ void announce(Ticket* slot, Ticket ticket) {
+  __threadfence_system();
+  __hip_atomic_store(slot, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ----------------------------------------------------------------- device status block
 // Written by the selection / truncation kernels, read back once per bond.
 struct DevStatus {
@@ -120,6 +129,7 @@ struct DevStatus {
   double norm2;        // |Theta|^2 of the scored tensor
   double lam_max;      // largest Gram eigenvalue
   int64_t ticks;       // small split: wall-clock ticks from the Gram to the truncation rule
+  Ticket ticket;       // small split: the launch that left this block
 };
 
 // Weyl string to be commuted through the tableau (exponents in [0, d)), passed to kernels by value.
@@ -136,6 +146,7 @@ struct DevWeyl {
   int32_t p;
   int32_t l, r;
   int32_t bad;  // nonzero: the rows did not multiply out to the target
+  Ticket ticket;
 };
 
 // ----------------------------------------------------------------- compiled words

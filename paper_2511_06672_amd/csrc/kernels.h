@@ -13,7 +13,7 @@ void launch_tableau_layer(hipStream_t s, int n, int d, int count, const int* sit
                           const uint32_t* luts, int* tx, int* tz, int* tp);
 // P = C^dagger W C for the target W; out may be host memory that the device addresses.
 void launch_weyl_extract(hipStream_t s, int n, int d, const int* tx, const int* tz, const int* tp,
-                         const WeylTarget& target, DevWeyl* out);
+                         const WeylTarget& target, DevWeyl* out, Ticket ticket);
 
 // ------------------------------------------------------------------ expectation (kernels_expect.hip)
 // A run of sites whose tensors have at most kExpectMaxSite entries and whose bonds at most kExpectMaxBond2
@@ -25,6 +25,7 @@ constexpr int kExpectMaxBond2 = 1600;
 struct ExpectResult {
   z64 value;  // without the phase of P
   int32_t p;  // tau exponent of P's phase
+  Ticket ticket;
 };
 struct ExpectArgs {
   int n, d, first, last;
@@ -33,6 +34,7 @@ struct ExpectArgs {
   DevWeyl* weyl;          // P, written when extract and not null
   const z64* e_in;        // left environment (chi x chi, row-major) at `first`; null: 1
   z64* e_out;             // environment at `last`, when not null
+  Ticket ticket;
   ExpectResult* result;   // at the end of the chain, when not null (host memory that the device addresses)
   WeylTarget target;
   int chi[kMaxN + 1];
@@ -86,7 +88,7 @@ inline JacobiCrit jacobi_crit(int m, int rel) {
 }
 // Offsets in a context's pinned read-back block: device status, pivoted and plain Cholesky
 // states, eigensolver slots, conjugated Weyl string and its error flag.
-constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbChol = 384, kRbEig = 512, kRbWeyl = 1024, kRbExpect = 2560, kRbBytes = 4096;
+constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbChol = 384, kRbEig = 512, kRbWeyl = 1024, kRbExpect = 2560, kRbCommit = 2816, kRbBytes = 4096;
 // precheck: test every pair against the rotation criterion first and return U = I, lam =
 // diag(G) without a sweep when none qualifies (for matrices expected to be diagonal already,
 // e.g. a Rayleigh-Ritz step; the result equals what one sweep that rotates nothing leaves).
@@ -120,6 +122,7 @@ struct SplitArgs {
   double* sig;
   int* perm;
   DevStatus *st, *host_st;
+  Ticket ticket;  // announced in *host_st
 };
 void launch_split_small(hipStream_t s, const SplitArgs& a);
 void launch_copy(hipStream_t s, z64* dst, const z64* src, size_t count);
@@ -197,7 +200,11 @@ void launch_score(hipStream_t s, int prec, int d, int chil, int chir, const z64*
 // ------------------------------------------------------------------ commit of a bond (kernels_commit.hip)
 // The choice: the lowest index with s2 <= min s2 + tol over the candidates 0..count, or over the
 // st->nwindow entries of list (s2 per entry); with ranks, over the candidates of the smallest rank and only
-// if that is below the identity's (else 0).  c* goes to st->cstar and host->cstar, the minimum to st->s2min.
+// if that is below the identity's (else 0).  c* goes to st->cstar and *host, the minimum to st->s2min.
+struct CommitResult {
+  int32_t cstar;
+  Ticket ticket;
+};
 struct CommitRule {
   int fixed;          // >= 0: this candidate, nothing is chosen and neither tableau nor status is written
   int count;
@@ -206,7 +213,8 @@ struct CommitRule {
   const int* rank;    // bond dimension per candidate, or null
   double tol;
   DevStatus* st;
-  DevStatus* host;    // host memory that the device addresses
+  CommitResult* host;  // host memory that the device addresses
+  Ticket ticket;
 };
 struct CommitTableau {
   int n, site;

@@ -110,6 +110,7 @@ __global__ __launch_bounds__(kThreads) void k_commit(CommitRule r, int chil, int
       r.st->cstar = c;
       r.st->s2min = smin;
       r.host->cstar = c;
+      announce(&r.host->ticket, r.ticket);
     }
     if (c == 0) return;
     // targets Z_a, Z_b, X_a, X_b (index ((xa d + za) d + xb) d + zb) of waves 0..3

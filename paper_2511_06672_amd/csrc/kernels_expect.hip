@@ -107,7 +107,11 @@ __global__ __launch_bounds__(kThreads) void k_expect_chain(ExpectArgs a, int e_e
     const int c1 = a.chi[a.last];
     for (int i = t; i < c1 * c1; i += kThreads) a.e_out[i] = E[(i % c1) * c1 + i / c1];
   }
-  if (a.result && t == 0) *a.result = ExpectResult{E[0], P.p};
+  if (a.result && t == 0) {
+    a.result->value = E[0];
+    a.result->p = P.p;
+    announce(&a.result->ticket, a.ticket);
+  }
 }
 
 // out[(al, t), b] = conj(omega^{z t}) A[(al, t + x), b] with the exponents of site `site` of *P.

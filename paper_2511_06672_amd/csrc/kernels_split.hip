@@ -283,7 +283,9 @@ __global__ __launch_bounds__(2 * HM * HM < 256 ? 256 : 2 * HM * HM) void k_split
     s.pass2 = pass2;
     s.ticks = t1 - t0;
     *a.st = s;
+    s.ticket = 0;
     *a.host_st = s;
+    announce(&a.host_st->ticket, a.ticket);
   }
 }
 

@@ -47,7 +47,7 @@ __global__ void k_tableau_layer(int n, int d, int count, const int* __restrict__
 
 __global__ __launch_bounds__(kMaxN) void k_weyl_extract(int n, int d, const int* __restrict__ tx,
                                                         const int* __restrict__ tz, const int* __restrict__ tp,
-                                                        WeylTarget target, DevWeyl* out) {
+                                                        WeylTarget target, DevWeyl* out, Ticket ticket) {
   __shared__ DevWeyl P;
   __shared__ WeylScratch ws;
   weyl_commute(n, d, tx, tz, tp, target, P, ws);
@@ -62,6 +62,9 @@ __global__ __launch_bounds__(kMaxN) void k_weyl_extract(int n, int d, const int*
     out->r = P.r;
     out->bad = P.bad;
   }
+  __threadfence_system();  // every thread's part before the ticket
+  __syncthreads();
+  if (t == 0) announce(&out->ticket, ticket);
 }
 
 }  // namespace
@@ -80,8 +83,8 @@ void launch_tableau_layer(hipStream_t s, int n, int d, int count, const int* sit
 }
 
 void launch_weyl_extract(hipStream_t s, int n, int d, const int* tx, const int* tz, const int* tp,
-                         const WeylTarget& target, DevWeyl* out) {
-  hipLaunchKernelGGL(k_weyl_extract, dim3(1), dim3(kMaxN), 0, s, n, d, tx, tz, tp, target, out);
+                         const WeylTarget& target, DevWeyl* out, Ticket ticket) {
+  hipLaunchKernelGGL(k_weyl_extract, dim3(1), dim3(kMaxN), 0, s, n, d, tx, tz, tp, target, out, ticket);
   GC_LAUNCH_CHECK();
 }
 
