@@ -107,7 +107,7 @@ struct gcamps_grad {
         GC_HIP(hipMemsetAsync(abar[i], 0, (size_t)c.chi[i] * d * c.chi[i + 1] * sizeof(z64), s()));
     const z64 one = {1.0, 0.0};
     std::vector<int> shift(n);
-    std::vector<z64> w((size_t)n * d);
+    std::vector<SitePhases> w(n);
     for (size_t j = 0; j < obs.size(); ++j) {
       const GateRec& P = obs[j];
       for (int herm = 0; herm < (adj ? 2 : 1); ++herm) {
@@ -118,42 +118,33 @@ struct gcamps_grad {
           for (int t = 0; t < d; ++t) {
             const int src = herm ? (t - x + d) % d : t;
             const double ang = 2.0 * M_PI * ((z * src) % d) / d;
-            w[(size_t)i * d + t] = z64{std::cos(ang), herm ? -std::sin(ang) : std::sin(ang)};
+            w[i].w[t] = z64{std::cos(ang), herm ? -std::sin(ang) : std::sin(ang)};
           }
         }
+        // the bra's tensor of site i with the site operator, rows (al, t), in T[2] where the operator acts
+        auto bra = [&](int i) -> const z64* {
+          if (P.x[i] == 0 && P.z[i] == 0) return c.site[i];
+          launch_site_gather(s(), d, c.chi[i], c.chi[i + 1], shift[i], w[i], c.site[i], T[2]);
+          return T[2];
+        };
         launch_copy(s(), E[0], dev_one, 1);
         for (int i = 0; i < n; ++i) {
           const int cl = c.chi[i], cr = c.chi[i + 1];
-          for (int t = 0; t < d; ++t) {
-            const z64* At = c.site[i] + (size_t)t * cr;
-            const z64* As = c.site[i] + (size_t)((t + shift[i]) % d) * cr;
-            launch_zgemm(s(), 0, 0, cl, cr, cl, E[i], cl, At, d * cr, T[0], cr, one, 0, 0);
-            launch_zgemm(s(), 1, 0, cr, cr, cl, As, d * cr, T[0], cr, E[i + 1], cr, w[(size_t)i * d + t], t > 0, 0);
-          }
+          const z64* B = bra(i);
+          launch_zgemm(s(), 0, 0, cl, d * cr, cl, E[i], cl, c.site[i], d * cr, T[0], d * cr, one, 0, 0);
+          launch_zgemm(s(), 1, 0, cr, cr, cl * d, B, cr, T[0], cr, E[i + 1], cr, one, 0, 0);
         }
         if (!herm) launch_copy(s(), res + j, E[n], 1);
         if (!adj) continue;
         launch_copy(s(), F[n], dev_one, 1);
+        const std::complex<double> ph = std::polar(0.5, (herm ? -1.0 : 1.0) * M_PI * P.p / d);
         for (int i = n - 1; i >= 0; --i) {
           const int cl = c.chi[i], cr = c.chi[i + 1];
-          for (int t = 0; t < d; ++t) {
-            const z64* At = c.site[i] + (size_t)t * cr;
-            const z64* As = c.site[i] + (size_t)((t + shift[i]) % d) * cr;
-            launch_zgemm(s(), 0, 0, cl, cr, cr, At, d * cr, F[i + 1], cr, T[0], cr, one, 0, 0);
-            launch_zgemm(s(), 0, 1, cl, cl, cr, T[0], cr, As, d * cr, F[i], cl, w[(size_t)i * d + t], t > 0, 0);
-          }
-        }
-        const std::complex<double> ph = std::polar(0.5, (herm ? -1.0 : 1.0) * M_PI * P.p / d);
-        for (int i = 0; i < n; ++i) {
-          const int cl = c.chi[i], cr = c.chi[i + 1];
-          for (int t = 0; t < d; ++t) {
-            const z64* At = c.site[i] + (size_t)t * cr;
-            const int so = (t + shift[i]) % d;
-            const std::complex<double> cf = ph * std::complex<double>(w[(size_t)i * d + t].re, w[(size_t)i * d + t].im);
-            launch_zgemm(s(), 0, 0, cl, cr, cl, E[i], cl, At, d * cr, T[0], cr, one, 0, 0);
-            launch_zgemm(s(), 0, 0, cl, cr, cr, T[0], cr, F[i + 1], cr, abar[i] + (size_t)so * cr, d * cr,
-                         z64{cf.real(), cf.imag()}, 1, 0);
-          }
+          // A_i F, then E A_i F onto the adjoint and (A_i F) B_i^H to the left
+          launch_zgemm(s(), 0, 0, cl * d, cr, cr, c.site[i], cr, F[i + 1], cr, T[0], cr, one, 0, 0);
+          launch_zgemm(s(), 0, 0, cl, d * cr, cl, E[i], cl, T[0], d * cr, T[1], d * cr, one, 0, 0);
+          launch_site_scatter(s(), d, cl, cr, shift[i], w[i], z64{ph.real(), ph.imag()}, T[1], abar[i]);
+          if (i > 0) launch_zgemm(s(), 0, 1, cl, cl, d * cr, T[0], d * cr, bra(i), d * cr, F[i], cl, one, 0, 0);
         }
       }
     }
@@ -170,55 +161,47 @@ struct gcamps_grad {
   // ------------------------------------------------------------ split adjoint
   // L (p x k), R (k x q) of the recorded split into T[0], T[1].
   void emit_factors(const FactRec& f) {
-    launch_emit(s(), f.wide, f.left, f.renorm, f.p, f.q, f.k, f.U, f.m, f.B, f.kW, f.perm, f.sig, T[0], T[1]);
+    launch_emit(s(), f.wide, f.left, f.renorm, f.p, f.q, f.k, f.U, f.m, f.B, f.kW, nullptr, f.sig, T[0], T[1]);
   }
 
   // Mbar (p x q) from Lbar (p x k), Rbar (k x q); L, R in T[0], T[1].  Uses T[2..11].
   void fact_bwd(const FactRec& f, const z64* Lbar, const z64* Rbar, z64* Mbar) {
     const int p = f.p, q = f.q, k = f.k, m = f.m, kW = f.kW;
-    const z64 one = {1.0, 0.0}, mone = {-1.0, 0.0};
+    const z64 one = {1.0, 0.0};
     const z64* L = T[0];
     const z64* R = T[1];
-    launch_kept_norm(s(), f.sig, k, f.renorm, dscal);
     z64* Nbar = T[4];
     if (f.left) {
       launch_zgemm(s(), 1, 0, k, k, p, L, k, Lbar, k, T[2], k, one, 0, 0);        // L^H Lbar
-      launch_copy(s(), T[3], Lbar, (size_t)p * k);
-      launch_zgemm(s(), 0, 0, p, k, k, L, k, T[2], k, T[3], k, mone, 1, 0);       // (1 - L L^H) Lbar
-      launch_inv_gram_scale(s(), T[3], p, k, 1, f.sig, dscal);                     // (R R^H)^{-1}
+      launch_zgemm(s(), 0, 0, p, k, k, L, k, T[2], k, T[3], k, one, 0, 0);        // L L^H Lbar
+      launch_gauge(s(), T[3], Lbar, p, k, 1, f.sig, k, f.renorm, dscal);          // (Lbar - .) (R R^H)^{-1}
       launch_zgemm(s(), 0, 0, p, q, k, T[3], k, R, q, Nbar, q, one, 0, 0);
       launch_zgemm(s(), 0, 0, p, q, k, L, k, Rbar, q, Nbar, q, one, 1, 0);
     } else {
       launch_zgemm(s(), 0, 1, k, k, q, Rbar, q, R, q, T[2], k, one, 0, 0);        // Rbar R^H
-      launch_copy(s(), T[3], Rbar, (size_t)k * q);
-      launch_zgemm(s(), 0, 0, k, q, k, T[2], k, R, q, T[3], q, mone, 1, 0);       // Rbar (1 - R^H R)
-      launch_inv_gram_scale(s(), T[3], k, q, 0, f.sig, dscal);                     // (L^H L)^{-1}
+      launch_zgemm(s(), 0, 0, k, q, k, T[2], k, R, q, T[3], q, one, 0, 0);        // Rbar R^H R
+      launch_gauge(s(), T[3], Rbar, k, q, 0, f.sig, k, f.renorm, dscal);          // (L^H L)^{-1} (Rbar - .)
       launch_zgemm(s(), 0, 0, p, q, k, Lbar, k, R, q, Nbar, q, one, 0, 0);
       launch_zgemm(s(), 0, 0, p, q, k, L, k, T[3], q, Nbar, q, one, 1, 0);
     }
     z64* Xbar = Nbar;
     if (f.renorm) {
       launch_zgemm(s(), 0, 0, p, q, k, L, k, R, q, T[5], q, one, 0, 0);           // N = L R
-      launch_dot_re(s(), T[5], Nbar, (size_t)p * q, dscal + 1);
-      launch_renorm_bwd(s(), Nbar, T[5], (size_t)p * q, dscal, dscal + 1, T[6]);
+      launch_renorm_bwd(s(), Nbar, T[5], (size_t)p * q, dscal, T[6]);
       Xbar = T[6];
     }
-    // Ybar = U^H Xbar_W (m x kW)
+    // Ybar = U^H Xbar_W (m x kW), rows in the sorted order as everything recorded
     if (f.wide)
       launch_zgemm(s(), 1, 0, m, kW, m, f.U, m, Xbar, kW, T[7], kW, one, 0, 0);
     else
       launch_zgemm(s(), 1, 1, m, kW, m, f.U, m, Xbar, m, T[7], kW, one, 0, 0);
-    launch_gather_rows(s(), T[7], f.perm, m, kW, m, T[8]);                         // Ybar sorted
-    launch_gather_rows(s(), f.B, f.perm, m, kW, m, T[9]);                          // B sorted
-    launch_zgemm(s(), 0, 1, m, m, kW, T[8], kW, T[9], kW, T[10], m, one, 0, 0);    // G1
-    launch_trunc_mix(s(), T[10], m, k, f.sig, T[11]);
-    launch_gather_rows(s(), T[7], f.perm, m, kW, k, T[4]);                         // Ybar_K
-    launch_zgemm(s(), 0, 0, m, kW, m, T[11], m, T[9], kW, T[4], kW, one, 1, 0);    // + Mix B
-    launch_gather_cols(s(), f.U, f.perm, m, T[10]);                                // U sorted
+    launch_zgemm(s(), 0, 1, m, m, kW, T[7], kW, f.B, kW, T[10], m, one, 0, 0);     // G1
+    launch_trunc_mix(s(), T[10], m, k, f.sig, T[11], T[7], kW);                    // T[7]: Ybar_K
+    launch_zgemm(s(), 0, 0, m, kW, m, T[11], m, f.B, kW, T[7], kW, one, 1, 0);     // + Mix B
     if (f.wide)
-      launch_zgemm(s(), 0, 0, m, kW, m, T[10], m, T[4], kW, Mbar, kW, one, 0, 0);
+      launch_zgemm(s(), 0, 0, m, kW, m, f.U, m, T[7], kW, Mbar, kW, one, 0, 0);
     else
-      launch_zgemm(s(), 1, 1, kW, m, m, T[4], kW, T[10], m, Mbar, m, one, 0, 0);
+      launch_zgemm(s(), 1, 1, kW, m, m, T[7], kW, f.U, m, Mbar, m, one, 0, 0);
   }
 
   // ------------------------------------------------------------ one tape step backwards

@@ -51,8 +51,7 @@ struct Arena {
 struct FactRec {
   z64* U = nullptr;
   z64* B = nullptr;
-  double* sig = nullptr;
-  int* perm = nullptr;
+  double* sig = nullptr;  // U's columns, B's rows and sig in descending order
   int m = 0, kW = 0, k = 0, p = 0, q = 0, wide = 0, left = 0, renorm = 0;
 };
 
@@ -440,11 +439,7 @@ struct gcamps_ctx {
     f.U = arena->take<z64>((size_t)m * m);
     f.B = arena->take<z64>((size_t)m * kW);
     f.sig = arena->take<double>(m);
-    f.perm = arena->take<int>(m);
-    launch_copy(stream, f.U, U, (size_t)m * m);
-    launch_copy(stream, f.B, B, (size_t)m * kW);
-    GC_HIP(hipMemcpyAsync(f.sig, sig, m * sizeof(double), hipMemcpyDeviceToDevice, stream));
-    GC_HIP(hipMemcpyAsync(f.perm, perm, m * sizeof(int), hipMemcpyDeviceToDevice, stream));
+    launch_record(stream, U, B, sig, perm, m, kW, f.U, f.B, f.sig);
   }
   // factorize() of a matrix whose smaller side fits one workgroup: one launch, which also leaves
   // the status in the pinned read-back block.

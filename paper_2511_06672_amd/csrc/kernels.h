@@ -280,22 +280,26 @@ void launch_clifford_dense(hipStream_t s, int n, int d, int D, const int* tx, co
                            z64* m, const z64* s0, const double* norm2, z64* out);
 
 // ------------------------------------------------------------------ reverse sweep (kernels_adjoint.hip)
-// out[0] = 1/sqrt(sum_{j<k} sig_j^2) when renorm, else 1.
-void launch_kept_norm(hipStream_t s, const double* sig, int k, int renorm, double* out);
-// X (rows x cols) scaled by 1/(sig_c^2 rn^2) per column (by_cols) or per row.
-void launch_inv_gram_scale(hipStream_t s, z64* X, int rows, int cols, int by_cols, const double* sig,
-                           const double* rn);
-// out[0] = Re sum conj(a) b.
-void launch_dot_re(hipStream_t s, const z64* a, const z64* b, size_t count, double* out);
-// Xbar = rn (Nbar - N dot).
-void launch_renorm_bwd(hipStream_t s, const z64* Nbar, const z64* N, size_t count, const double* rn,
-                       const double* dot, z64* Xbar);
-// dst[a] = src[perm[a]] for rows a < keep_rows, zero rows below (m x cols).
-void launch_gather_rows(hipStream_t s, const z64* src, const int* perm, int m, int cols, int keep_rows, z64* dst);
-// dst[:, a] = src[:, perm[a]] (m x m).
-void launch_gather_cols(hipStream_t s, const z64* src, const int* perm, int m, z64* dst);
-// Kept/discarded mixing matrix of the truncated-split adjoint (sorted basis, k kept).
-void launch_trunc_mix(hipStream_t s, const z64* G1, int m, int k, const double* sig, z64* Zc);
+struct SitePhases {
+  z64 w[kMaxD];
+};
+// Us, Bs, ss <- U (m x m), B (m x kW) and sig in the sorted order perm.
+void launch_record(hipStream_t s, const z64* U, const z64* B, const double* sig, const int* perm, int m, int kW, z64* Us,
+                   z64* Bs, double* ss);
+// X (rows x cols) <- (base - X) / (sig_c^2 rn^2) per column (by_cols) or per row; *rn = 1/sqrt(sum_{j<k} sig_j^2)
+// when renorm, else 1.
+void launch_gauge(hipStream_t s, z64* X, const z64* base, int rows, int cols, int by_cols, const double* sig, int k,
+                  int renorm, double* rn);
+// Xbar = rn (Nbar - N Re<N, Nbar>), rn = scal[0]; scal[1] is scratch.
+void launch_renorm_bwd(hipStream_t s, const z64* Nbar, const z64* N, size_t count, double* scal, z64* Xbar);
+// Kept/discarded mixing matrix of the truncated-split adjoint (sorted basis, k kept); rows >= k of Y (m x kW)
+// are cleared.
+void launch_trunc_mix(hipStream_t s, const z64* G1, int m, int k, const double* sig, z64* Zc, z64* Y, int kW);
+// abar[al, (t + shift) mod d, b] += cf w_t X[al, t, b] on site tensors (chil, d, chir).
+void launch_site_scatter(hipStream_t s, int d, int chil, int chir, int shift, const SitePhases& w, z64 cf, const z64* X,
+                         z64* abar);
+// out[al, t, b] = conj(w_t) in[al, (t + shift) mod d, b].
+void launch_site_gather(hipStream_t s, int d, int chil, int chir, int shift, const SitePhases& w, const z64* in, z64* out);
 // Transpose of the MPO site map and the gradient of its coefficients (kinds 0 and 3).
 void launch_mpo_site_bwd(hipStream_t s, int kind, int d, int chil, int chir, int dx, int dz, const MpoCoeff& co,
                          const z64* obar, z64* ibar);

@@ -3,8 +3,8 @@
 // Adjoint convention: for a real loss L and a complex array X, Xbar = dL/d conj(X), so that
 // dL = 2 Re sum conj(Xbar) dX.  The dense products of the reverse sweep use the GEMM of
 // kernels_linalg; the kernels here are the elementwise and reduction steps around them:
-// * factorisation adjoint helpers (kept-norm, gauge scalings, the renormalisation
-//   projection, row/column gathers by the sort order, the kept/discarded mixing matrix);
+// * factorisation adjoint helpers (the sorted basis, gauge scalings, the renormalisation
+//   projection, the kept/discarded mixing matrix);
 // * the transpose of the MPO site map and the gradient of its coefficients;
 // * Q^dagger applied to a two-site tensor.
 #include "kernels.h"
@@ -29,25 +29,27 @@ __device__ double block_sum(double v, double* red) {
   return r;
 }
 
-// out[0] = rn = 1/sqrt(sum_{j<k} sig_j^2) (1 when !renorm), out[1] = 1/(rn^2) factor base
-__global__ __launch_bounds__(1024) void k_kept_norm(const double* __restrict__ sig, int k, int renorm,
-                                                    double* __restrict__ out) {
-  __shared__ double red[1024];
+// X = (base - X) / (sig[c]^2 rn^2) (by_cols; sig[r] otherwise) with rn = 1 / sqrt(sum_{j<k} sig_j^2), or 1
+// when !renorm, also left in *rnp.  Every workgroup sums the k values itself: the sum, the copy of base and the scaling
+// were a launch each, of 2.6, 1.7 and 1.7 us with the gaps between them.
+__global__ __launch_bounds__(256) void k_gauge(z64* __restrict__ X, const z64* __restrict__ base, int rows, int cols,
+                                               int by_cols, const double* __restrict__ sig, int k, int renorm,
+                                               double* __restrict__ rnp) {
+  __shared__ double red[256];
+  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const bool mine = idx < (size_t)rows * cols;
+  z64 x = {0.0, 0.0};
+  double s = 1.0;
+  if (mine) {
+    x = csub(base[idx], X[idx]);
+    s = sig[by_cols ? idx % cols : idx / cols];
+  }
   double v = 0.0;
-  for (int j = threadIdx.x; j < k; j += blockDim.x) v += sig[j] * sig[j];
+  for (int j = threadIdx.x; j < k; j += 256) v += sig[j] * sig[j];
   const double tot = block_sum(v, red);
-  if (threadIdx.x == 0) out[0] = renorm ? 1.0 / sqrt(tot) : 1.0;
-}
-
-// X[r][c] *= 1 / (sig[c]^2 rn^2) (cols = true) or 1 / (sig[r]^2 rn^2) (cols = false).
-__global__ void k_inv_gram_scale(z64* __restrict__ X, int rows, int cols, int by_cols, const double* __restrict__ sig,
-                                 const double* __restrict__ rnp) {
-  size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)rows * cols) return;
-  const int r = (int)(idx / cols), c = (int)(idx % cols);
-  const double s = by_cols ? sig[c] : sig[r];
-  const double rn = rnp[0];
-  X[idx] = cscale(X[idx], 1.0 / (s * s * rn * rn));
+  const double rn = renorm ? 1.0 / sqrt(tot) : 1.0;
+  if (idx == 0) rnp[0] = rn;
+  if (mine) X[idx] = cscale(x, 1.0 / (s * s * rn * rn));
 }
 
 // out[0] = Re sum conj(a) b
@@ -69,30 +71,56 @@ __global__ void k_renorm_bwd(const z64* __restrict__ Nbar, const z64* __restrict
   Xbar[idx] = cscale(csub(Nbar[idx], cscale(N[idx], dt)), rn);
 }
 
-// dst[a][c] = src[perm[a]][c] for a < keep_rows, 0 for keep_rows <= a < m.
-__global__ void k_gather_rows(const z64* __restrict__ src, const int* __restrict__ perm, int m, int cols,
-                              int keep_rows, z64* __restrict__ dst) {
-  size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)m * cols) return;
-  const int a = (int)(idx / cols), c = (int)(idx % cols);
-  dst[idx] = (a < keep_rows) ? src[(size_t)perm[a] * cols + c] : z64{0.0, 0.0};
+// Both of the above in one workgroup, the entries in registers between them.
+constexpr int kRenormPer = 8;
+__global__ __launch_bounds__(1024) void k_renorm_bwd_small(const z64* __restrict__ Nbar, const z64* __restrict__ N,
+                                                           int count, const double* __restrict__ rnp,
+                                                           z64* __restrict__ Xbar) {
+  __shared__ double red[1024];
+  z64 a[kRenormPer], b[kRenormPer];
+  double v = 0.0;
+#pragma unroll
+  for (int u = 0; u < kRenormPer; ++u) {
+    const int i = threadIdx.x + u * 1024;
+    a[u] = b[u] = z64{0.0, 0.0};
+    if (i < count) {
+      a[u] = N[i];
+      b[u] = Nbar[i];
+    }
+    v += a[u].re * b[u].re + a[u].im * b[u].im;
+  }
+  const double dt = block_sum(v, red), rn = rnp[0];
+#pragma unroll
+  for (int u = 0; u < kRenormPer; ++u) {
+    const int i = threadIdx.x + u * 1024;
+    if (i < count) Xbar[i] = cscale(csub(b[u], cscale(a[u], dt)), rn);
+  }
 }
 
-// dst[r][a] = src[r][perm[a]] (m x m)
-__global__ void k_gather_cols(const z64* __restrict__ src, const int* __restrict__ perm, int m,
-                              z64* __restrict__ dst) {
+// A factorisation's basis as the reverse sweep wants it, in the sorted order: Us[r][a] = U[r][perm[a]] (m x m),
+// Bs[a][c] = B[perm[a]][c] (m x kW) and the values sig.
+__global__ void k_record(const z64* __restrict__ U, const z64* __restrict__ B, const double* __restrict__ sig,
+                         const int* __restrict__ perm, int m, int kW, z64* __restrict__ Us, z64* __restrict__ Bs,
+                         double* __restrict__ ss) {
   size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)m * m) return;
-  const int r = (int)(idx / m), a = (int)(idx % m);
-  dst[idx] = src[(size_t)r * m + perm[a]];
+  if (idx < (size_t)m) ss[idx] = sig[idx];
+  const size_t mm = (size_t)m * m;
+  if (idx < mm) {
+    Us[idx] = U[idx / m * m + perm[idx % m]];
+  } else if (idx < mm + (size_t)m * kW) {
+    idx -= mm;
+    Bs[idx] = B[(size_t)perm[idx / kW] * kW + idx % kW];
+  }
 }
 
 // Mixing of kept (index < k) and discarded rows in the sorted basis:
 //   Zc[a][b] = (G1[a][b] + conj(G1[b][a])) / (s_kept^2 - s_discarded^2)  when exactly one of a, b < k,
 // 0 otherwise (and 0 on an exact tie, where the derivative of the split does not exist).
+// The rows >= k of Y (m x kW) are cleared on the way: what stays of it is the kept part.
 __global__ void k_trunc_mix(const z64* __restrict__ G1, int m, int k, const double* __restrict__ sig,
-                            z64* __restrict__ Zc) {
+                            z64* __restrict__ Zc, z64* __restrict__ Y, int kW) {
   size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx < (size_t)(m - k) * kW) Y[(size_t)k * kW + idx] = z64{0.0, 0.0};
   if (idx >= (size_t)m * m) return;
   const int a = (int)(idx / m), b = (int)(idx % m);
   z64 v = {0.0, 0.0};
@@ -169,6 +197,24 @@ __global__ __launch_bounds__(1024) void k_mpo_coeff_bwd(int kind, int d, int chi
   }
 }
 
+// A site operator |t> -> w_t |t + shift> on a site tensor, from the bra's side and back onto it.
+__global__ void k_site_gather(int d, int chil, int chir, int shift, SitePhases w, const z64* __restrict__ in,
+                              z64* __restrict__ out) {
+  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (size_t)chil * d * chir) return;
+  const int b = (int)(idx % chir), t = (int)((idx / chir) % d);
+  const size_t al = idx / ((size_t)chir * d);
+  out[idx] = cmulc(w.w[t], in[(al * d + (t + shift) % d) * chir + b]);
+}
+__global__ void k_site_scatter(int d, int chil, int chir, int shift, SitePhases w, z64 cf, const z64* __restrict__ X,
+                               z64* __restrict__ abar) {
+  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (size_t)chil * d * chir) return;
+  const int b = (int)(idx % chir), t = (int)((idx / chir) % d);
+  const size_t al = idx / ((size_t)chir * d), o = (al * d + (t + shift) % d) * chir + b;
+  abar[o] = cadd(abar[o], cmul(cmul(cf, w.w[t]), X[idx]));
+}
+
 // theta <- Q_c^dagger theta on the physical pair of a (chil, d, d, chir) tensor.
 __global__ void k_apply_qh(int d, int chil, int chir, int c, const z64* __restrict__ qm, z64* __restrict__ theta) {
   size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -187,39 +233,31 @@ __global__ void k_apply_qh(int d, int chil, int chir, int c, const z64* __restri
 
 }  // namespace
 
-void launch_kept_norm(hipStream_t s, const double* sig, int k, int renorm, double* out) {
-  hipLaunchKernelGGL(k_kept_norm, dim3(1), dim3(1024), 0, s, sig, k, renorm, out);
+void launch_gauge(hipStream_t s, z64* X, const z64* base, int rows, int cols, int by_cols, const double* sig, int k,
+                  int renorm, double* rn) {
+  hipLaunchKernelGGL(k_gauge, dim3(nblocks((size_t)rows * cols, 256)), dim3(256), 0, s, X, base, rows, cols, by_cols,
+                     sig, k, renorm, rn);
   GC_LAUNCH_CHECK();
 }
-void launch_inv_gram_scale(hipStream_t s, z64* X, int rows, int cols, int by_cols, const double* sig,
-                           const double* rn) {
-  if (!rows || !cols) return;
-  hipLaunchKernelGGL(k_inv_gram_scale, dim3(nblocks((size_t)rows * cols, 256)), dim3(256), 0, s, X, rows, cols,
-                     by_cols, sig, rn);
+void launch_renorm_bwd(hipStream_t s, const z64* Nbar, const z64* N, size_t count, double* scal, z64* Xbar) {
+  // one workgroup reads its 8192 entries in one go; more of them are left to the whole chip after the sum
+  if (count <= (size_t)1024 * kRenormPer) {
+    hipLaunchKernelGGL(k_renorm_bwd_small, dim3(1), dim3(1024), 0, s, Nbar, N, (int)count, scal, Xbar);
+  } else {
+    hipLaunchKernelGGL(k_dot_re, dim3(1), dim3(1024), 0, s, N, Nbar, count, scal + 1);
+    hipLaunchKernelGGL(k_renorm_bwd, dim3(nblocks(count, 256)), dim3(256), 0, s, Nbar, N, count, scal, scal + 1, Xbar);
+  }
   GC_LAUNCH_CHECK();
 }
-void launch_dot_re(hipStream_t s, const z64* a, const z64* b, size_t count, double* out) {
-  hipLaunchKernelGGL(k_dot_re, dim3(1), dim3(1024), 0, s, a, b, count, out);
+void launch_record(hipStream_t s, const z64* U, const z64* B, const double* sig, const int* perm, int m, int kW, z64* Us,
+                   z64* Bs, double* ss) {
+  hipLaunchKernelGGL(k_record, dim3(nblocks((size_t)m * (m + kW), 256)), dim3(256), 0, s, U, B, sig, perm, m, kW, Us, Bs,
+                     ss);
   GC_LAUNCH_CHECK();
 }
-void launch_renorm_bwd(hipStream_t s, const z64* Nbar, const z64* N, size_t count, const double* rn,
-                       const double* dot, z64* Xbar) {
-  if (!count) return;
-  hipLaunchKernelGGL(k_renorm_bwd, dim3(nblocks(count, 256)), dim3(256), 0, s, Nbar, N, count, rn, dot, Xbar);
-  GC_LAUNCH_CHECK();
-}
-void launch_gather_rows(hipStream_t s, const z64* src, const int* perm, int m, int cols, int keep_rows, z64* dst) {
-  if (!m || !cols) return;
-  hipLaunchKernelGGL(k_gather_rows, dim3(nblocks((size_t)m * cols, 256)), dim3(256), 0, s, src, perm, m, cols,
-                     keep_rows, dst);
-  GC_LAUNCH_CHECK();
-}
-void launch_gather_cols(hipStream_t s, const z64* src, const int* perm, int m, z64* dst) {
-  hipLaunchKernelGGL(k_gather_cols, dim3(nblocks((size_t)m * m, 256)), dim3(256), 0, s, src, perm, m, dst);
-  GC_LAUNCH_CHECK();
-}
-void launch_trunc_mix(hipStream_t s, const z64* G1, int m, int k, const double* sig, z64* Zc) {
-  hipLaunchKernelGGL(k_trunc_mix, dim3(nblocks((size_t)m * m, 256)), dim3(256), 0, s, G1, m, k, sig, Zc);
+void launch_trunc_mix(hipStream_t s, const z64* G1, int m, int k, const double* sig, z64* Zc, z64* Y, int kW) {
+  const size_t total = std::max((size_t)m * m, (size_t)(m - k) * kW);
+  hipLaunchKernelGGL(k_trunc_mix, dim3(nblocks(total, 256)), dim3(256), 0, s, G1, m, k, sig, Zc, Y, kW);
   GC_LAUNCH_CHECK();
 }
 void launch_mpo_site_bwd(hipStream_t s, int kind, int d, int chil, int chir, int dx, int dz, const MpoCoeff& co,
@@ -232,6 +270,17 @@ void launch_mpo_site_bwd(hipStream_t s, int kind, int d, int chil, int chir, int
 void launch_mpo_coeff_bwd(hipStream_t s, int kind, int d, int chil, int chir, int dx, int dz, const MpoCoeff& co,
                           const z64* in, const z64* obar, z64* kbar) {
   hipLaunchKernelGGL(k_mpo_coeff_bwd, dim3(1), dim3(1024), 0, s, kind, d, chil, chir, dx, dz, co, in, obar, kbar);
+  GC_LAUNCH_CHECK();
+}
+void launch_site_gather(hipStream_t s, int d, int chil, int chir, int shift, const SitePhases& w, const z64* in, z64* out) {
+  const size_t total = (size_t)chil * d * chir;
+  hipLaunchKernelGGL(k_site_gather, dim3(nblocks(total, 256)), dim3(256), 0, s, d, chil, chir, shift, w, in, out);
+  GC_LAUNCH_CHECK();
+}
+void launch_site_scatter(hipStream_t s, int d, int chil, int chir, int shift, const SitePhases& w, z64 cf, const z64* X,
+                         z64* abar) {
+  const size_t total = (size_t)chil * d * chir;
+  hipLaunchKernelGGL(k_site_scatter, dim3(nblocks(total, 256)), dim3(256), 0, s, d, chil, chir, shift, w, cf, X, abar);
   GC_LAUNCH_CHECK();
 }
 void launch_apply_qh(hipStream_t s, int d, int chil, int chir, int c, const z64* qmats, z64* theta) {

@@ -746,7 +746,7 @@ __global__ __launch_bounds__(1024) void k_trunc(const double* __restrict__ sig2,
 
 // Factor emission.  W is the wide orientation of the split matrix M (p x q): wide = 1 when
 // W = M (p <= q, m = p, kW = q), wide = 0 when W = M^H (m = q, kW = p).  With U (m x m) the
-// eigenvectors of W W^H, B = U^H W (m x kW), perm the sorted order and sig the row norms of B:
+// eigenvectors of W W^H, B = U^H W (m x kW), perm the sorted order (null: sorted already) and sig the row norms of B:
 //   wide, left_ortho : L = U[:, perm],            R = B[perm, :] * rn
 //   wide, right_ortho: L = U[:, perm] * sig * rn, R = B[perm, :] / sig
 //   tall, left_ortho : L = B[perm, :]^H / sig,    R = sig * rn * U[:, perm]^H
@@ -767,7 +767,7 @@ __global__ void k_emit(int wide, int left_ortho, int renorm, int p, int q, int k
   size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < nl) {
     int i = (int)(idx / kept), j = (int)(idx % kept);
-    int pj = perm[j];
+    int pj = perm ? perm[j] : j;
     z64 v;
     if (wide) {
       v = U[(size_t)i * ldu + pj];
@@ -780,7 +780,7 @@ __global__ void k_emit(int wide, int left_ortho, int renorm, int p, int q, int k
   } else if (idx < nl + nr) {
     size_t e = idx - nl;
     int j = (int)(e / q), c = (int)(e % q);
-    int pj = perm[j];
+    int pj = perm ? perm[j] : j;
     z64 v;
     if (wide) {
       v = B[(size_t)pj * ldb + c];
