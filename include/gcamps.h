@@ -61,8 +61,9 @@ enum {
   GCAMPS_SCORE_FP64 = 0, /* complex128 scoring */
   GCAMPS_SCORE_FP32 = 1, /* complex64 scoring, FP64 re-score of the near-tie window */
   GCAMPS_SCORE_BF16 = 2, /* split-BF16 scoring (each real as hi + lo BF16, FP32 accumulation, relative
-                            error ~2^-16) for matrices above 96 rows, complex64 below; FP64 re-score
-                            of the near-tie window */
+                            error ~2^-16) for matrices above 96 rows, complex64 below and where
+                            the two-site density matrix is the faster form (d = 2 above 128
+                            candidates, d = 3 above 64); FP64 re-score of the near-tie window */
   GCAMPS_SCORE_REPLICA = 3 /* FP64 replica-tensor scoring (d = 2, 3 only): the purity of Q_c Theta (§3)
                               rewritten as sum W(Theta) o V_c, W from the Gram of Theta over its
                               larger bond and V_c a table built once per candidate set, so a bond

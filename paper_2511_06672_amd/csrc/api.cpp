@@ -100,7 +100,9 @@ void set_error(const std::string& msg) { g_last_error = msg; }
 namespace gc {
 // FP32 scoring takes the density form for qutrits; with d = 2 it stays with the rotated-matrix kernels, whose
 // per-shape launch choices (GCAMPS_TUNE_FILE) callers keep across runs.
-static bool density_fp32(const gcamps_config& c) { return c.d == 3 && c.score_prec == GCAMPS_SCORE_FP32; }
+static bool density_fp32(const gcamps_config& c) {
+  return c.d <= 3 && (c.score_prec == GCAMPS_SCORE_FP32 || c.score_prec == GCAMPS_SCORE_BF16);
+}
 
 Layout make_layout(const gcamps_config& c) {
   Layout L{};
@@ -150,7 +152,7 @@ Layout make_layout(const gcamps_config& c) {
   L.off_nbuf = take(L.nbuf_bytes);
   L.off_rtab = take(replica ? replica_table_elems(c.d, (int)L.ncand) * sizeof(z64) : 0);
   L.off_dtab = take(density_table_elems(c.d, (int)L.ncand) * sizeof(z64));
-  L.off_dtab32 = take(c.d == 3 ? density_table_elems(c.d, (int)L.ncand) * sizeof(c32) : 0);  // in every mode
+  L.off_dtab32 = take(density_table_elems(c.d, (int)L.ncand) * sizeof(c32));  // in every mode
   const size_t D4 = d * d * d * d;
   L.off_q64 = take(L.ncand * D4 * sizeof(z64));
   L.off_q32 = take(L.ncand * D4 * sizeof(c32));

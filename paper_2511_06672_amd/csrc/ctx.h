@@ -109,7 +109,7 @@ struct gcamps_ctx {
   c32* q32 = nullptr;
   z64* rtab = nullptr;  // replica-scoring tables of the candidate set (replica mode only)
   z64* dtab = nullptr;    // density-scoring rows of the candidate set (d <= 3)
-  c32* dtab32 = nullptr;  // the same in FP32 (FP32 scoring with d = 3)
+  c32* dtab32 = nullptr;  // the same in FP32 (FP32 and BF16 scoring)
   uint32_t* qinv = nullptr;
   EigWork eig{};
   // MPS
@@ -785,8 +785,19 @@ struct gcamps_ctx {
   // Scores of Theta (bonds cl, cr) in the arithmetic of prec: the full set, or (nlimit given) the window
   // list of an earlier pass.  f_ready: the scratch holds Theta's density matrix; it does after a pass
   // that used it.  evs, evcap and used as in launch_score.  Returns the algorithmic flops of the full set.
+  // Whether a score of this mode goes through the density matrix: in FP64 always, in the low-precision modes (then
+  // in FP32) where it is the faster form.  It pays its Gram product of Theta once, the rotated matrices pay theirs
+  // per candidate.  Qutrits, FP32: always.  Qutrits, BF16: 64 candidates at chi = 81 take 78 against 74 us, 128 89
+  // against 132, at chi = 243 16 take 291 against 213 and 128 426 against 990.  Qubits, chi = 256: 128
+  // candidates take 157 against 300 us (BF16) and 581 (FP32), 720 278 against 1565 and 3234; sets of up to 128
+  // keep the rotated matrices all the same, whose launch parameters are tuned and saved by shape.
+  bool density_mode(int prec) const {
+    if (prec == GCAMPS_SCORE_FP64) return true;
+    if (prec == GCAMPS_SCORE_REPLICA || !dtab32) return false;
+    return d == 2 ? ncand > 128 : prec == GCAMPS_SCORE_FP32 || ncand > 64;
+  }
   bool use_density(int prec, int cl, int cr) const {
-    return dtab && (prec == GCAMPS_SCORE_FP64 || (prec == GCAMPS_SCORE_FP32 && dtab32)) &&
+    return dtab && density_mode(prec) &&
            (double)std::min(cl, cr) * std::min(cl, cr) * std::max(cl, cr) * d * d * d >= kDensityMinWork && density_fits(d, cl, cr, ncand, lay.nbuf_bytes);
   }
   double density_flops(int cl, int cr) const {  // one candidate's product
@@ -800,7 +811,7 @@ struct gcamps_ctx {
       if (!f_ready) launch_density_gram(stream, d, cl, cr, theta, nbuf);
       f_ready = true;
       const bool ev = used && evcap >= 2;
-      launch_density_score(stream, d, prec == GCAMPS_SCORE_FP32, cl, cr, dtab, dtab32, ncand, list, ncand, nlimit, out,
+      launch_density_score(stream, d, prec != GCAMPS_SCORE_FP64, cl, cr, dtab, dtab32, ncand, list, ncand, nlimit, out,
                            nbuf, lay.nbuf_bytes, ev ? evs[0] : nullptr, ev ? evs[1] : nullptr);
       if (ev) *used = 1;
       return;

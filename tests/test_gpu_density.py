@@ -68,3 +68,24 @@ def test_density_window_choices(g, d, n, ncand):
         out.append((st.choice_log(), st.bond_dims(), st.fidelity()))
     assert np.array_equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
     assert out[0][2] == out[1][2]
+
+
+@pytest.mark.parametrize("prec_name,d,n,chi,ncand", [("bf16", 3, 8, 41, 64), ("bf16", 3, 8, 41, 65), ("fp32", 2, 12, 64, 128),
+                                                     ("fp32", 2, 12, 64, 129), ("bf16", 2, 12, 64, 128),
+                                                     ("bf16", 2, 12, 49, 129), ("bf16", 2, 12, 64, 300)])
+def test_low_precision_sets_on_both_sides_of_the_rule(g, prec_name, d, n, chi, ncand):
+    """Set sizes where BF16 (and, for qubits, FP32) scoring goes from rotated matrices to the density matrix in
+    FP32.  The rotated form is held to half of the smallest re-score window (1e-4), as the window assumes; the
+    density form to the FP32 bound above."""
+    print(f"[gpu-case] low-precision rule {prec_name} d={d} chi={chi} candidates={ncand}", flush=True)
+    st, mats = saturated(g, d, n, chi, g.SCORE_FP32 if prec_name == "fp32" else g.SCORE_BF16, ncand)
+    density = ncand > (128 if d == 2 else 64)
+    for i in range(n // 2 - 2, n // 2 + 2):
+        s = st.score_bond(i)
+        dims = [1] + st.bond_dims() + [1]
+        cl, cr = dims[i], dims[i + 2]
+        theta = np.tensordot(st.site(i), st.site(i + 1), axes=([2], [0]))
+        t = theta.reshape(cl, d * d, cr)
+        ref = np.array([renyi2(np.matmul(q, t).reshape(theta.shape)) for q in mats])
+        tol = 4 * d * d * (max(cl, cr) + d ** 4) * 2.0 ** -24 if density else 5e-5
+        assert np.max(np.abs(s - ref)) <= tol, (i, cl, cr, np.max(np.abs(s - ref)), tol)
