@@ -294,6 +294,9 @@ int32_t gcamps_init(const gcamps_config* cfg, void* dev_workspace, size_t bytes,
     GC_HIP(hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev));
     c->tick_ms = 1.0 / std::max(1, clock_khz);
     c->eig.host_rb = reinterpret_cast<double*>(c->rb + kRbEig);
+    c->eig.report = reinterpret_cast<SweepReport*>(c->rb + kRbSweep);
+    c->eig.report_dev = reinterpret_cast<SweepReport*>(c->rb_dev + kRbSweep);
+    c->eig.ticket = &c->ticket;
     GC_HIP(hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming));
     GC_HIP(hipEventCreate(&c->ev0));
     GC_HIP(hipEventCreate(&c->ev1));

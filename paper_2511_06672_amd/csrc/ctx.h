@@ -126,7 +126,6 @@ struct gcamps_ctx {
   char* pinned = nullptr;
   char* rb = nullptr;  // pinned read-back block (status, Cholesky state, eigensolver flags)
   Ticket ticket = 0;       // of the last launch that announces its results in rb
-  static constexpr int kPollMs = 2;
   char* rb_dev = nullptr;  // the same block as the device addresses it
   double tick_ms = 0.0;    // one tick of the device's wall clock in ms
   size_t pinned_bytes = 0;
@@ -191,22 +190,9 @@ struct gcamps_ctx {
   static_assert(sizeof(DevStatus) <= kRbPcState && kRbPcState + sizeof(PcState) <= kRbChol &&
                     kRbChol + sizeof(CholState) <= kRbEig &&
                     kRbWeyl + sizeof(DevWeyl) <= kRbExpect && kRbExpect + sizeof(ExpectResult) <= kRbCommit &&
-                    kRbCommit + sizeof(CommitResult) <= kRbBytes,
+                    kRbCommit + sizeof(CommitResult) <= kRbSweep && kRbSweep + sizeof(SweepReport) <= kRbBytes,
                 "read-back block layout");
-  // Waits until the launch with ticket `want` has announced its results (slot: in the read-back block).
-  // Polling returns 5 us earlier than a wait for the stream (an expectation of one launch: 53 against 58 us);
-  // after kPollMs the stream is waited for, which also reports a launch that failed.
-  void await(const Ticket& slot, Ticket want) {
-    const auto t0 = std::chrono::steady_clock::now();
-    for (int i = 1; __atomic_load_n(&slot, __ATOMIC_ACQUIRE) != want; ++i) {
-      __builtin_ia32_pause();
-      if ((i & 63) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(kPollMs)) {
-        GC_HIP(hipStreamSynchronize(stream));
-        GC_CHECK(__atomic_load_n(&slot, __ATOMIC_ACQUIRE) == want, GCAMPS_EDEVICE, "a launch left no result");
-        return;
-      }
-    }
-  }
+  void await(const Ticket& slot, Ticket want) const { await_ticket(stream, slot, want); }
   void read_status(DevStatus& h) {  // through pinned memory: no staging copy
     GC_HIP(hipMemcpyAsync(rb + kRbStatus, st, sizeof(DevStatus), hipMemcpyDeviceToHost, stream));
     GC_HIP(hipStreamSynchronize(stream));

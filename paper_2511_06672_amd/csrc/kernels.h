@@ -1,9 +1,27 @@
 // Launch wrappers of the HIP kernels (one definition per .hip translation unit).
 #pragma once
 
+#include <chrono>
+
 #include "internal.h"
 
 namespace gc {
+
+// Waits until the launch with ticket `want` has announced its results (slot: in pinned coherent memory).
+// Polling returns 5 us earlier than a wait for the stream (an expectation of one launch: 53 against 58 us);
+// after kPollMs the stream is waited for, which also reports a launch that failed.
+constexpr int kPollMs = 2;
+inline void await_ticket(hipStream_t s, const Ticket& slot, Ticket want) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int i = 1; __atomic_load_n(&slot, __ATOMIC_ACQUIRE) != want; ++i) {
+    __builtin_ia32_pause();
+    if ((i & 63) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(kPollMs)) {
+      GC_HIP(hipStreamSynchronize(s));
+      GC_CHECK(__atomic_load_n(&slot, __ATOMIC_ACQUIRE) == want, GCAMPS_EDEVICE, "a launch left no result");
+      return;
+    }
+  }
+}
 
 // ------------------------------------------------------------------ tableau (kernels_tableau.hip)
 // Device tableau: tx[2n*n], tz[2n*n], tp[2n] (row r, site i at r*n + i); exponents in [0,d),
@@ -55,13 +73,20 @@ void launch_zgemm(hipStream_t s, int opa, int opb, int M, int N, int K, const z6
 // Hermitian eigen-decomposition by two-sided Jacobi.  G (m x m, ld ldg) is destroyed (holds
 // the rotated matrix, padded to mp x mp with ld mp in the block variant); U (ld ldu) receives
 // eigenvectors, lam the eigenvalues (unsorted).  rel: relative-accuracy criterion.
+// What a sweep's rounds tell the host: whether the sweep before rotated anything, and the ticket of their launch.
+struct SweepReport {
+  int32_t rotated;
+  Ticket ticket;
+};
 struct EigWork {
   z64* G;      // three padded m_pad x m_pad planes: matrix, accumulator, second matrix buffer
   z64* V;      // block rotations (two rounds)
   z64* D;      // solved sub-problems (two rounds)
   int* flags;  // device flags
   int m_pad;
-  double* host_rb = nullptr;  // pinned host read-back slots (2 doubles); pageable locals when null
+  double* host_rb;            // pinned host read-back slots (2 doubles)
+  SweepReport *report, *report_dev;  // in pinned coherent host memory: what the host and the device address
+  Ticket* ticket;             // the context's ticket counter
 };
 // Criteria of the sweeps.  Absolute criterion 2e-15 of the trace: what stays off the diagonal tilts a
 // factor's columns by up to 2e-15 trace / lambda (1.1e-12 at 4e-15 on a Gaussian 300 x 97); half the
@@ -88,7 +113,7 @@ inline JacobiCrit jacobi_crit(int m, int rel) {
 }
 // Offsets in a context's pinned read-back block: device status, pivoted and plain Cholesky
 // states, eigensolver slots, conjugated Weyl string and its error flag.
-constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbChol = 384, kRbEig = 512, kRbWeyl = 1024, kRbExpect = 2560, kRbCommit = 2816, kRbBytes = 4096;
+constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbChol = 384, kRbEig = 512, kRbWeyl = 1024, kRbExpect = 2560, kRbCommit = 2816, kRbSweep = 2880, kRbBytes = 4096;
 // precheck: test every pair against the rotation criterion first and return U = I, lam =
 // diag(G) without a sweep when none qualifies (for matrices expected to be diagonal already,
 // e.g. a Rayleigh-Ritz step; the result equals what one sweep that rotates nothing leaves).

@@ -545,9 +545,6 @@ __device__ void solve_pair(int k, const z64* __restrict__ Gs, int mp, int nb, in
 // against 27.6 ms; m = 1536: 82.0 against 70.5 ms), where the rounds go without the pad.
 constexpr int kJroundPad = 36 * 1024;
 constexpr int kPadMaxM = 896;
-// Blocks up to which two sweeps are launched per read-back of their flags (m = 81: 1.07 against
-// 1.14 ms per decomposition; from about 256 rows on it makes no difference).
-constexpr int kChunkMaxNb = 16;
 template <bool REL>
 __global__ __launch_bounds__(512) void k_jround(const z64* __restrict__ Gs, z64* __restrict__ Gd,
                                                 z64* __restrict__ Up, int mp, int nb, int step, int ps,
@@ -555,11 +552,16 @@ __global__ __launch_bounds__(512) void k_jround(const z64* __restrict__ Gs, z64*
                                                 double floor_rel, z64* __restrict__ Vout, z64* __restrict__ Dout,
                                                 int* __restrict__ pair_flag, int* __restrict__ any_flag,
                                                 const int* __restrict__ prev_any, const z64* __restrict__ Vp,
-                                                const z64* __restrict__ Dp, const int* __restrict__ pfp) {
+                                                const z64* __restrict__ Dp, const int* __restrict__ pfp,
+                                                SweepReport* report, Ticket ticket) {
   __shared__ __align__(16) z64 pool[3 * BJ2 * BJ2];
   __shared__ int need;
   const int half = nb / 2, nsolve = step >= 0 ? half : 0, ngt = half * (half + 1) / 2;
   int b = blockIdx.x;
+  if (report && b == 0 && threadIdx.x == 0) {
+    report->rotated = *prev_any;
+    announce(&report->ticket, ticket);
+  }
   if (b < nsolve) {
     // thresholds from the trace on the device (read by no host sync)
     const JacobiThr jt = jacobi_thr(*trace, tol, skip_rel, REL, floor_rel);
@@ -878,7 +880,7 @@ void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu,
   GC_LAUNCH_CHECK();
   double* d_trace = reinterpret_cast<double*>(w.flags + 512);
   int* sweep_flags = w.flags + 300;  // rotation flag of each sweep, cleared by k_trace
-  GC_CHECK(max_sweeps <= kSweepFlags, GCAMPS_ECAPACITY, "more sweeps than rotation flags");
+  GC_CHECK(max_sweeps < kSweepFlags, GCAMPS_ECAPACITY, "more sweeps than rotation flags");
   hipLaunchKernelGGL(k_trace, dim3(1), dim3(256), 0, s, Gp, m, mp, d_trace, sweep_flags);
   GC_LAUNCH_CHECK();
   if (precheck) {
@@ -887,8 +889,7 @@ void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu,
     GC_LAUNCH_CHECK();
   }
   if (precheck) {  // the pre-check flag sits after the trace; the rounds read the trace themselves
-    double local[2] = {0.0, 0.0};
-    double* tr_flag = w.host_rb ? w.host_rb : local;  // pinned when the context gives a slot
+    double* tr_flag = w.host_rb;
     GC_HIP(hipMemcpyAsync(tr_flag, d_trace, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     GC_HIP(hipStreamSynchronize(s));
     int pre_hit = 1;
@@ -918,39 +919,37 @@ void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu,
   const int gtiles = tile_blocks(half * (half + 1) / 2), utiles = tile_blocks((mp / BJ2) * half);
   // a whole CU per block while the tile updates are few (see k_jround)
   const size_t pad = mp <= kPadMaxM ? kJroundPad : 0;
-  // The host reads the sweeps' flags back after `chunk` sweeps.  While a sweep is short, two are
-  // launched at a time: a sweep launched past convergence returns at once (prev_any), which costs
-  // less than a read-back per sweep.
-  const int chunk = nb <= kChunkMaxNb ? 2 : 1;
+  // A sweep is launched before the host knows whether the one before it rotated anything: its first round
+  // reports that, and if nothing was rotated it does nothing (prev_any).  So the queue never runs dry, where a
+  // read-back of the flags left it empty for 15 us after every one or two sweeps; the sweep too many
+  // costs 3 us a round.
   long round = 0;  // rounds launched so far
   int prev_step = -1;
-  while (!conv && sweeps < max_sweeps) {
-    for (int c = 0; c < chunk; ++c)
-      for (int step = 0; step < nb - 1; ++step, ++round) {
-        const bool upd = round > 0;
-        const int sw = sweeps + c;
+  auto sweep = [&](int sw) {
+    for (int step = 0; step < nb - 1; ++step, ++round) {
+      const bool upd = round > 0, tell = sw > 0 && step == 0;
+      if (tell) ++*w.ticket;
 #define GC_JROUND(REL)                                                                                               \
   hipLaunchKernelGGL((k_jround<REL>), dim3(half + (upd ? gtiles + utiles : 0)), dim3(kSolveThreads), pad, s,         \
                      upd ? gbuf(round - 1) : Gp, gbuf(round), Up, mp, nb, step, upd ? prev_step : -1, d_trace, tol,  \
                      skip, floor_rel, vbuf(round), dbuf(round), fbuf(round), sweep_flags + sw,                       \
-                     c > 0 ? sweep_flags + sw - 1 : nullptr, upd ? vbuf(round - 1) : nullptr,                        \
-                     upd ? dbuf(round - 1) : nullptr, upd ? fbuf(round - 1) : nullptr)
-        if (rel)
-          GC_JROUND(true);
-        else
-          GC_JROUND(false);
+                     sw > 0 ? sweep_flags + sw - 1 : nullptr, upd ? vbuf(round - 1) : nullptr,                       \
+                     upd ? dbuf(round - 1) : nullptr, upd ? fbuf(round - 1) : nullptr, tell ? w.report_dev : nullptr, \
+                     *w.ticket)
+      if (rel)
+        GC_JROUND(true);
+      else
+        GC_JROUND(false);
 #undef GC_JROUND
-        GC_LAUNCH_CHECK();
-        prev_step = step;
-      }
-    int local[2] = {0, 0};
-    int* hany = w.host_rb ? reinterpret_cast<int*>(w.host_rb) : local;  // pinned when given
-    GC_HIP(hipMemcpyAsync(hany, sweep_flags + sweeps, chunk * sizeof(int), hipMemcpyDeviceToHost, s));
-    GC_HIP(hipStreamSynchronize(s));
-    for (int c = 0; c < chunk && !conv; ++c) {
-      ++sweeps;
-      conv = hany[c] == 0;
+      GC_LAUNCH_CHECK();
+      prev_step = step;
     }
+  };
+  sweep(0);
+  while (!conv && sweeps < max_sweeps) {
+    sweep(++sweeps);
+    await_ticket(s, w.report->ticket, *w.ticket);
+    conv = w.report->rotated == 0;
   }
   // The last sweep rotated nothing, so its last round has nothing to apply: the matrix is what that
   // round's launch wrote.
