@@ -1,6 +1,6 @@
 // Dense FP64 complex linear algebra for the MPS factorisations (§2.4: truncation by SVD).
 //
-// * k_zgemm / k_zgemm_ks: C = alpha op(A) op(B) on 32x32 tiles with v_mfma_f64_16x16x4 (a
+// * k_zgemm_s / k_zgemm: C = alpha op(A) op(B) on 16x16 or 32x32 tiles with v_mfma_f64_16x16x4 (a
 //   complex product is four real MFMAs into a real and an imaginary accumulator).
 // * Hermitian eigen-decomposition by two-sided Jacobi rotations: a single-workgroup kernel that
 //   keeps the whole matrix in LDS (m <= kSmallEig) and a block-Jacobi scheme for larger m
@@ -138,74 +138,60 @@ __global__ __launch_bounds__(256) void k_zgemm(int M, int N, int K, const z64* _
                accumulate, herm);
 }
 
-// Eight waves for products with few tiles: wave group g (waves 4g..4g+3, one 16 x 16 quadrant
-// each) takes chunk 2p + g of every chunk pair p, and group 1 hands its sums to group 0 through
-// LDS at the end (two partial sums per element, added in a fixed order).
+// One 16 x 16 tile per workgroup: the eight waves take eight k values each in turn, straight from memory into
+// MFMA operands (the next ones while the current are multiplied), and their sums are added in a fixed
+// order through LDS.  Bound by the MFMA pipe of one CU per tile (K / 4 steps of four MFMAs on four SIMDs) where the
+// tiles are fewer than CUs, by the operands' L2 traffic (4 flop a byte) where they are many, and for small
+// products by the launch, one load latency and the reduction.  Against 32 x 32 tiles staged through LDS, the K range
+// split over two groups of four waves: 81 x 81 x 81 4.1 and 7.0 us (back to back, so mostly the launch), the Gram
+// of 243 x 729 12.4 and 38.6, 128 x 128 x 1152 18.0 and 58.2, 384^3 16.2 and 20.3, 768 x 256 x 768 28.2 and
+// 36.6, the Gram of 729 x 729 52 and 99 us.
+constexpr int ST = 16, SLD = ST + 1;
 template <int OPA, int OPB>
-__global__ __launch_bounds__(512) void k_zgemm_ks(int M, int N, int K, const z64* __restrict__ A, int lda,
-                                                  const z64* __restrict__ B, int ldb, z64* __restrict__ C, int ldc,
-                                                  z64 alpha, int accumulate, int herm) {
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-  if (herm && m0 >= n0 + GT) return;
-  __shared__ double As[2][2][2][GK][GLD];  // [stage][group][re, im][k][row]
-  __shared__ double Bs[2][2][2][GK][GLD];
-  __shared__ double Xr[4][4][64], Xi[4][4][64];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6, grp = w >> 2, wl = w & 3;
-  const int wr = (wl >> 1) * 16, wc = (wl & 1) * 16;
+__global__ __launch_bounds__(512) void k_zgemm_s(int M, int N, int K, const z64* __restrict__ A, int lda,
+                                                 const z64* __restrict__ B, int ldb, z64* __restrict__ C, int ldc,
+                                                 z64 alpha, int accumulate, int herm) {
+  const int m0 = blockIdx.y * ST, n0 = blockIdx.x * ST;
+  if (herm && m0 > n0) return;  // entirely below the diagonal
+  __shared__ z64 part[8][ST * SLD];
+  const int t = threadIdx.x, lane = t & 63, col = lane & 15, quad = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   d4 accr = {0, 0, 0, 0}, acci = {0, 0, 0, 0};
-  z64 ra[2], rb[2];
-  auto fetch = [&](int k0) {  // a chunk pair: 32 rows x 32 k values of each operand
+  z64 a[2], b[2];
+  auto fetch = [&](int k0) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      int r, kk;
-      tile_elem<OPA, 2 * GK>(t + 512 * i, r, kk);
-      ra[i] = load_a<OPA>(A, lda, M, K, m0 + r, k0 + kk);
-      tile_elem<OPB == 0 ? 1 : 0, 2 * GK>(t + 512 * i, r, kk);
-      rb[i] = load_b<OPB>(B, ldb, N, K, n0 + r, k0 + kk);
+    for (int j = 0; j < 2; ++j) {
+      a[j] = load_a<OPA>(A, lda, M, K, m0 + col, k0 + 4 * j + quad);
+      b[j] = load_b<OPB>(B, ldb, N, K, n0 + col, k0 + 4 * j + quad);
     }
   };
-  auto stash = [&](int s) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      int r, kk;
-      tile_elem<OPA, 2 * GK>(t + 512 * i, r, kk);
-      As[s][kk / GK][0][kk % GK][r] = ra[i].re;
-      As[s][kk / GK][1][kk % GK][r] = ra[i].im;
-      tile_elem<OPB == 0 ? 1 : 0, 2 * GK>(t + 512 * i, r, kk);
-      Bs[s][kk / GK][0][kk % GK][r] = rb[i].re;
-      Bs[s][kk / GK][1][kk % GK][r] = rb[i].im;
-    }
-  };
-  const int npair = (K + 2 * GK - 1) / (2 * GK);
-  fetch(0);
-  stash(0);
-  __syncthreads();
-  for (int c = 0; c < npair; ++c) {
-    const int s = c & 1;
-    if (c + 1 < npair) fetch((c + 1) * 2 * GK);
-#pragma unroll
-    for (int kk = 0; kk < GK; kk += 4) {
-      const int ka = kk + (lane >> 4);
-      const double ar = As[s][grp][0][ka][wr + (lane & 15)], ai = As[s][grp][1][ka][wr + (lane & 15)];
-      const double br = Bs[s][grp][0][ka][wc + (lane & 15)], bi = Bs[s][grp][1][ka][wc + (lane & 15)];
-      accr = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, accr, 0, 0, 0);
-      accr = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, bi, accr, 0, 0, 0);
-      acci = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, acci, 0, 0, 0);
-      acci = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, acci, 0, 0, 0);
-    }
-    if (c + 1 < npair) stash(s ^ 1);
-    __syncthreads();
+  fetch(w * 8);
+  for (int k0 = w * 8; k0 < K; k0 += 64) {
+    const z64 a0 = a[0], a1 = a[1], b0 = b[0], b1 = b[1];
+    if (k0 + 64 < K) fetch(k0 + 64);
+    mma4(a0, b0, accr, acci);
+    mma4(a1, b1, accr, acci);
   }
-  if (grp == 1)
-    for (int q = 0; q < 4; ++q) {
-      Xr[wl][q][lane] = accr[q];
-      Xi[wl][q][lane] = acci[q];
-    }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) part[w][mfma_row_f64(lane, q) * SLD + col] = z64{accr[q], acci[q]};
   __syncthreads();
-  if (grp == 0)
-    for (int q = 0; q < 4; ++q)
-      gemm_store(C, ldc, M, N, m0 + wr + mfma_row_f64(lane, q), n0 + wc + (lane & 15), accr[q] + Xr[wl][q][lane],
-                 acci[q] + Xi[wl][q][lane], alpha, accumulate, herm);
+  const bool act = t < ST * ST;
+  const int i = t / ST, j = t % ST, row = m0 + i, cc = n0 + j;
+  if (act) {
+    z64 s = part[0][i * SLD + j];
+    const int used = min(8, (K + 7) / 8);
+    for (int x = 1; x < used; ++x) s = cadd(s, part[x][i * SLD + j]);
+    s = z64{alpha.re * s.re - alpha.im * s.im, alpha.re * s.im + alpha.im * s.re};
+    const bool in = row < M && cc < N;
+    if (accumulate && in) s = cadd(s, C[(size_t)row * ldc + cc]);
+    if (in && !(herm && row > cc)) C[(size_t)row * ldc + cc] = s;
+    if (herm) part[0][i * SLD + j] = s;
+  }
+  if (!herm) return;
+  __syncthreads();
+  // the mirror of the tile, by rows of the mirror
+  const int mr = n0 + i, mc = m0 + j;
+  if (act && mr < M && mc < mr) C[(size_t)mr * ldc + mc] = cconj(part[0][j * SLD + i]);
 }
 
 // ===================================================================================== Jacobi
@@ -822,16 +808,15 @@ void linalg_set_attributes() {
 void launch_zgemm(hipStream_t s, int opa, int opb, int M, int N, int K, const z64* A, int lda, const z64* B,
                   int ldb, z64* C, int ldc, z64 alpha, int accumulate, int herm) {
   if (M <= 0 || N <= 0) return;
-  const dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
-  // Below 256 tiles (Hermitian: counting the upper ones) the K-split form with two waves per
-  // SIMD is faster (768 x 256 x 768: 39 against 54 us), above it the four-wave form (768^3:
-  // 108 against 112 us; both against 226 us on 64 x 64 single-stage tiles).
-  const long tiles = herm ? (long)grid.x * (grid.x + 1) / 2 : (long)grid.x * grid.y;
-  const bool ks = tiles < 256;
+  // Below 4096 16 x 16 tiles (Hermitian: counting the upper ones) the form without staging is the faster one
+  // (768^3: 74 against 98 us), above it the 32 x 32 tiles, which read half as much (1024^3: 172 us both;
+  // Hermitian 1536 x 512: 156 against 174 us).
+  const dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT), sgrid((N + ST - 1) / ST, (M + ST - 1) / ST);
+  const bool small = (herm ? (long)sgrid.x * (sgrid.x + 1) / 2 : (long)sgrid.x * sgrid.y) < 4096;
 #define GC_ZGEMM(OA, OB)                                                                                         \
   do {                                                                                                           \
-    if (ks)                                                                                                      \
-      hipLaunchKernelGGL((k_zgemm_ks<OA, OB>), grid, dim3(512), 0, s, M, N, K, A, lda, B, ldb, C, ldc, alpha,    \
+    if (small)                                                                                                   \
+      hipLaunchKernelGGL((k_zgemm_s<OA, OB>), sgrid, dim3(512), 0, s, M, N, K, A, lda, B, ldb, C, ldc, alpha,    \
                          accumulate, herm);                                                                      \
     else                                                                                                         \
       hipLaunchKernelGGL((k_zgemm<OA, OB>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, C, ldc, alpha,       \
