@@ -301,7 +301,7 @@ int32_t gcamps_get_site(gcamps_ctx* ctx, int32_t site, double* out, int64_t cap,
  * [4] algorithmic flops of full-set scoring (direct: N_c (4 m^2 k + 8 d^4 chi_l chi_r) per bond; through
  * the two-site density matrix, FP64 with d = 2, 3 and FP32 with d = 3 above a size:
  * 4 (X d^2)^2 Y + N_c 4 X (X + 1) d^6; replica mode: 4 (X d^2)^2 Y + 8 X (X + 1) / 2 d^8 + 2 N_c d^8 with X, Y the smaller and larger bond), [5] algorithmic flops of the Gram products of
- * the factorisations, [6] full-set scoring kernel time in ms (device events), [7] total time
+ * the factorisations, [6] full-set scoring kernel time in ms (device clock), [7] total time
  * inside gcamps_* calls in ms (host clock), [8] flops of the FP64 window re-score, [9] its
  * kernel time in ms, [10] scoring calls (bonds x passes), [11] launches of the scoring
  * MFMA kernel (full-set scoring; Gram purity or density product), [12] their summed kernel time in ms

@@ -791,7 +791,7 @@ struct gcamps_ctx {
     return 4.0 * X * (X + 1) * std::pow((double)d, 6);
   }
   void score(int prec, int cl, int cr, const int* list, const int* nlimit, double* out, bool& f_ready,
-             hipEvent_t* evs = nullptr, int evcap = 0, int* used = nullptr) {
+             hipEvent_t* evs = nullptr, int evcap = 0, int* used = nullptr, int64_t* tick = nullptr) {
     if (used) *used = 0;
     if (use_density(prec, cl, cr)) {
       if (!f_ready) launch_density_gram(stream, d, cl, cr, theta, nbuf);
@@ -804,7 +804,7 @@ struct gcamps_ctx {
     }
     f_ready = false;
     launch_score(stream, prec, d, cl, cr, theta, q64, q32, list, ncand, nlimit, out, partial, lay.ncand * lay.ntp * 2,
-                 nbuf, lay.nbuf_bytes, evs, evcap, used, rtab);
+                 nbuf, lay.nbuf_bytes, evs, evcap, used, rtab, tick);
   }
 
   // Full-set scores of bond (i, i+1) in the configured mode, to host memory; commits nothing.
@@ -835,7 +835,12 @@ struct gcamps_ctx {
         const int mm = std::min(cl * d, d * cr), kk = std::max(cl * d, d * cr);
         int gram_used = 0;
         bool shortcut = false;
-        CommitRule rule{-1, ncand, s2, nullptr, nullptr, cfg.tie_tol, st,
+        // the fused scoring launches are timed by the launches themselves (an event costs 3 us of a 100 us bond)
+        const bool batched_rank = mm <= kRankMaxM && (size_t)(mm + (mm & 1)) * kk <= kRankMaxElems;
+        const bool ticks = mm <= kScoreSmallM && !use_density(prec, cl, cr) && !use_density(GCAMPS_SCORE_FP64, cl, cr) &&
+                           (cfg.criterion != GCAMPS_CRITERION_BOND_DIM || (batched_rank && prec == GCAMPS_SCORE_FP64));
+        auto tick = [&](int k) { return ticks ? st->score_tick + k : nullptr; };
+        CommitRule rule{-1, ncand, s2, nullptr, nullptr, cfg.tie_tol, nullptr, st,
                         reinterpret_cast<CommitResult*>(rb_dev + kRbCommit), ++ticket};
         if (frozen) {
           // replay: the recorded choice replaces scoring and selection
@@ -855,13 +860,13 @@ struct gcamps_ctx {
           const bool density = use_density(prec, cl, cr);
           const double pflops = density ? density_flops(cl, cr)
                                         : 4.0 * mm * mm * kk + 8.0 * std::pow((double)d, 4) * cl * cr;
-          GC_HIP(hipEventRecord(ev0, stream));
+          if (!ticks) GC_HIP(hipEventRecord(ev0, stream));
           bool f_ready = false;
-          score(prec, cl, cr, nullptr, nullptr, s2, f_ready, gram_ev.data(), (int)gram_ev.size(), &gram_used);
-          GC_HIP(hipEventRecord(ev1, stream));
+          score(prec, cl, cr, nullptr, nullptr, s2, f_ready, gram_ev.data(), (int)gram_ev.size(), &gram_used, tick(0));
+          if (!ticks) GC_HIP(hipEventRecord(ev1, stream));
           if (cfg.criterion == GCAMPS_CRITERION_BOND_DIM) {
-            if (mm <= kRankMaxM && (size_t)(mm + (mm & 1)) * kk <= kRankMaxElems) {
-              launch_cand_rank(stream, d, cl, cr, theta, q64, ncand, cfg.cutoff, cfg.chi_max, wlist);
+            if (batched_rank) {
+              launch_cand_rank(stream, d, cl, cr, theta, q64, ncand, cfg.cutoff, cfg.chi_max, wlist, st->score_tick + 1);
             } else {
               // larger bonds: every candidate's rotated tensor through the split's own
               // factorisation (Lbuf holds Q_c Theta; the split of the bond comes later)
@@ -876,10 +881,10 @@ struct gcamps_ctx {
             }
             rule.rank = wlist;
           } else if (prec != GCAMPS_SCORE_FP64) {
-            launch_window(stream, ncand, s2, cfg.near_tie, wlist, st);
-            GC_HIP(hipEventRecord(ev2, stream));
-            score(GCAMPS_SCORE_FP64, cl, cr, wlist, &st->nwindow, s2w, f_ready);
-            GC_HIP(hipEventRecord(ev3, stream));
+            launch_window(stream, ncand, s2, cfg.near_tie, wlist, st, tick(1));
+            if (!ticks) GC_HIP(hipEventRecord(ev2, stream));
+            score(GCAMPS_SCORE_FP64, cl, cr, wlist, &st->nwindow, s2w, f_ready, nullptr, 0, nullptr, tick(2));
+            if (!ticks) GC_HIP(hipEventRecord(ev3, stream));
             rule.list = wlist;
             rule.s2 = s2w;
           }
@@ -892,6 +897,8 @@ struct gcamps_ctx {
             if (density) stats[4] += 4.0 * std::pow((double)std::min(cl, cr) * d * d, 2) * std::max(cl, cr);
           }
           stats[10] += 1;
+          rule.tick = tick(rule.list ? 3 : 1);
+          if (rule.rank) rule.tick = nullptr;
           launch_commit(stream, d, rule, cl, cr, q64, theta, CommitTableau{n, i, qinv, tx, tz, tp});
           // When the identity is kept, Theta = A_i A_{i+1} with the neighbour of the centre
           // orthonormal (right-orthonormal A_{i+1} when sweeping left to right, left-orthonormal
@@ -945,8 +952,12 @@ struct gcamps_ctx {
         stats[14] += shortcut ? 1 : 0;
         if (!frozen) {
           float ms = 0.f;
-          GC_HIP(hipEventSynchronize(prec != GCAMPS_SCORE_FP64 && !rule.rank ? ev3 : ev1));
-          GC_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+          if (!ticks) {
+            GC_HIP(hipEventSynchronize(prec != GCAMPS_SCORE_FP64 && !rule.rank ? ev3 : ev1));
+            GC_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+          } else {
+            ms = (float)((h.score_tick[1] - h.score_tick[0]) * tick_ms);
+          }
           stats[6] += ms;
           if (gram_used > 0) {  // Gram-purity kernel alone: algorithmic 4 m^2 k flop per candidate
             for (int e = 0; e < gram_used; ++e) {
@@ -971,7 +982,10 @@ struct gcamps_ctx {
                                       : 4.0 * mm * mm * kk + 8.0 * std::pow((double)d, 4) * cl * cr;
             stats[2] += h.nwindow;
             stats[8] += (double)h.nwindow * pflops;
-            GC_HIP(hipEventElapsedTime(&ms, ev2, ev3));
+            if (!ticks)
+              GC_HIP(hipEventElapsedTime(&ms, ev2, ev3));
+            else
+              ms = (float)((h.score_tick[3] - h.score_tick[2]) * tick_ms);
             stats[9] += ms;
           }
         }

@@ -129,6 +129,9 @@ struct DevStatus {
   double norm2;        // |Theta|^2 of the scored tensor
   double lam_max;      // largest Gram eigenvalue
   int64_t ticks;       // small split: wall-clock ticks from the Gram to the truncation rule
+  // wall clock around the fused scoring launches, each read by the first workgroup of the launch named: score,
+  // what follows it (window, ranks or commit), re-score, commit
+  int64_t score_tick[4];
   Ticket ticket;       // small split: the launch that left this block
 };
 

@@ -220,7 +220,7 @@ void launch_score(hipStream_t s, int prec, int d, int chil, int chir, const z64*
                   const z64* q64, const c32* q32, const int* cand_list, int count,
                   const int* nlimit, double* s2, double* partial, size_t partial_cap, void* nbuf,
                   size_t nbuf_bytes, hipEvent_t* evs = nullptr, int evcap = 0, int* evused = nullptr,
-                  const z64* replica_tables = nullptr);
+                  const z64* replica_tables = nullptr, int64_t* tick = nullptr);
 
 // ------------------------------------------------------------------ commit of a bond (kernels_commit.hip)
 // The choice: the lowest index with s2 <= min s2 + tol over the candidates 0..count, or over the
@@ -237,6 +237,7 @@ struct CommitRule {
   const int* list;    // window, or null
   const int* rank;    // bond dimension per candidate, or null
   double tol;
+  int64_t* tick;      // the wall clock at the start goes there, when not null
   DevStatus* st;
   CommitResult* host;  // host memory that the device addresses
   Ticket ticket;
@@ -256,7 +257,7 @@ constexpr int kRankMaxElems = 8192;  // entries of the two-site matrix (LDS of o
 // rank_out[c] = bond dimension left by candidate c (truncation rule of the split applied to the
 // singular values of reshape(Q_c Theta), one-sided Jacobi SVD per candidate).
 void launch_cand_rank(hipStream_t s, int d, int chil, int chir, const z64* theta, const z64* qmats, int count,
-                      double cutoff, int chi_max, int* rank_out);
+                      double cutoff, int chi_max, int* rank_out, int64_t* tick);
 void rank_set_attributes();
 void linalg_set_attributes();  // the block-Jacobi rounds' dynamic LDS limit
 
@@ -292,7 +293,7 @@ void launch_score_replica(hipStream_t s, int d, int chil, int chir, const z64* t
 // Low-precision window: list (ascending index) of candidates with s2lp <= min + window; the
 // list length goes to st->nwindow.
 void launch_window(hipStream_t s, int count, const double* s2lp, double window, int* list,
-                   DevStatus* st);
+                   DevStatus* st, int64_t* tick);
 
 // ------------------------------------------------------------------ dense state (kernels_dense.hip)
 // v <- C|0> for the tableau's Clifford C, not normalised (norm2 = its squared norm): the stabilizer

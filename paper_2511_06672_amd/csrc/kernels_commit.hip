@@ -93,6 +93,7 @@ template <int D>
 __global__ __launch_bounds__(kThreads) void k_commit(CommitRule r, int chil, int chir, const z64* __restrict__ qm,
                                                      z64* __restrict__ theta, CommitTableau tb) {
   constexpr int D2 = D * D;
+  const int64_t t0 = wall_clock64();
   __shared__ z64 q[D2 * D2];
   const int t = threadIdx.x;
   const bool last = r.fixed < 0 && blockIdx.x == gridDim.x - 1;
@@ -107,6 +108,7 @@ __global__ __launch_bounds__(kThreads) void k_commit(CommitRule r, int chil, int
   const int c = r.fixed >= 0 ? r.fixed : choose(r, count, smin);
   if (last) {
     if (t == 0) {
+      if (r.tick) *r.tick = t0;
       r.st->cstar = c;
       r.st->s2min = smin;
       r.host->cstar = c;

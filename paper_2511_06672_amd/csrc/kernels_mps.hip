@@ -191,8 +191,9 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_score_small(int d, int chil, 
                                                                const c32* __restrict__ q32,
                                                                const int* __restrict__ list,
                                                                const int* __restrict__ nlimit,
-                                                               double* __restrict__ s2) {
+                                                               double* __restrict__ s2, int64_t* tick) {
   const int slot = blockIdx.x;
+  if (tick && slot == 0 && threadIdx.x == 0) *tick = wall_clock64();
   if (nlimit && slot >= *nlimit) return;
   const int c = list ? list[slot] : slot;
   const bool rows_first = chil * d <= d * chir;
@@ -877,10 +878,11 @@ __global__ void k_score_reduce(int ntp, const int* __restrict__ nlimit, int coun
 
 // ===================================================================================== window
 __global__ __launch_bounds__(1024) void k_window(int count, const double* __restrict__ s2lp, double window,
-                                                 int* __restrict__ list, DevStatus* st) {
+                                                 int* __restrict__ list, DevStatus* st, int64_t* tick) {
   __shared__ double red[1024];
   __shared__ int cnt[16];
   const int t = threadIdx.x;
+  if (tick && t == 0) *tick = wall_clock64();
   double mn = DBL_MAX;
   for (int i = t; i < count; i += 1024) mn = fmin(mn, s2lp[i]);
   red[t] = mn;
@@ -958,7 +960,7 @@ int gen_cpt(hipStream_t s, int prec, int d, int chil, int chir, const int* nlimi
 
 void launch_score(hipStream_t s, int prec, int d, int chil, int chir, const z64* theta, const z64* q64, const c32* q32,
                   const int* list, int count, const int* nlimit, double* s2, double* partial, size_t partial_cap,
-                  void* nbuf, size_t nbuf_bytes, hipEvent_t* evs, int evcap, int* evused, const z64* replica_tables) {
+                  void* nbuf, size_t nbuf_bytes, hipEvent_t* evs, int evcap, int* evused, const z64* replica_tables, int64_t* tick) {
   if (evused) *evused = 0;
   if (count <= 0) return;
   if (prec == GCAMPS_SCORE_REPLICA) GC_CHECK(list == nullptr && nlimit == nullptr, GCAMPS_EINVAL,
@@ -969,10 +971,10 @@ void launch_score(hipStream_t s, int prec, int d, int chil, int chir, const z64*
   if (m <= SMALL_M) {
     if (prec == GCAMPS_SCORE_FP64 || prec == GCAMPS_SCORE_REPLICA)
       hipLaunchKernelGGL(k_score_small<double>, dim3(count), dim3(SMALL_THREADS), 0, s, d, chil, chir, theta, q64,
-                         q32, list, nlimit, s2);
+                         q32, list, nlimit, s2, tick);
     else
       hipLaunchKernelGGL(k_score_small<float>, dim3(count), dim3(SMALL_THREADS), 0, s, d, chil, chir, theta, q64, q32,
-                         list, nlimit, s2);
+                         list, nlimit, s2, tick);
     GC_LAUNCH_CHECK();
     return;
   }
@@ -1084,8 +1086,8 @@ void launch_score(hipStream_t s, int prec, int d, int chil, int chir, const z64*
   GC_LAUNCH_CHECK();
 }
 
-void launch_window(hipStream_t s, int count, const double* s2lp, double window, int* list, DevStatus* st) {
-  hipLaunchKernelGGL(k_window, dim3(1), dim3(1024), 0, s, count, s2lp, window, list, st);
+void launch_window(hipStream_t s, int count, const double* s2lp, double window, int* list, DevStatus* st, int64_t* tick) {
+  hipLaunchKernelGGL(k_window, dim3(1), dim3(1024), 0, s, count, s2lp, window, list, st, tick);
   GC_LAUNCH_CHECK();
 }
 

@@ -31,11 +31,13 @@ __device__ __forceinline__ void rr_rows(int k, int s, int mp, int& p, int& q) {
 
 __global__ __launch_bounds__(kRankThreads) void k_cand_rank(int d, int chil, int chir, const z64* __restrict__ theta,
                                                             const z64* __restrict__ qm, int count, double cutoff,
-                                                            int chi_max, int* __restrict__ rank_out) {
+                                                            int chi_max, int* __restrict__ rank_out,
+                                                            int64_t* tick) {
   extern __shared__ double lds[];
   __shared__ double s2v[32];
   __shared__ int rotated;
   const int c = blockIdx.x, t = threadIdx.x;
+  if (c == 0 && t == 0) *tick = wall_clock64();
   if (c >= count) return;
   const int D2 = d * d;
   const bool rows_first = chil * d <= d * chir;
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(kRankThreads) void k_cand_rank(int d, int chil, int
 }  // namespace
 
 void launch_cand_rank(hipStream_t s, int d, int chil, int chir, const z64* theta, const z64* qmats, int count,
-                      double cutoff, int chi_max, int* rank_out) {
+                      double cutoff, int chi_max, int* rank_out, int64_t* tick) {
   const int m = std::min(chil * d, d * chir), k = std::max(chil * d, d * chir);
   const int mp = m + (m & 1);
   GC_CHECK(m <= kRankMaxM && (size_t)mp * k <= kRankMaxElems, GCAMPS_EUNSUPPORTED,
@@ -185,7 +187,7 @@ void launch_cand_rank(hipStream_t s, int d, int chil, int chir, const z64* theta
   if (count <= 0) return;
   const size_t lds = 2 * (size_t)mp * k * sizeof(double);
   hipLaunchKernelGGL(k_cand_rank, dim3(count), dim3(kRankThreads), lds, s, d, chil, chir, theta, qmats, count, cutoff,
-                     chi_max, rank_out);
+                     chi_max, rank_out, tick);
   GC_LAUNCH_CHECK();
 }
 
