@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <functional>
 #include <cmath>
 #include <complex>
 #include <cstdio>
@@ -211,12 +212,12 @@ struct gcamps_ctx {
   // Cholesky factorisation of the Gram, which drops what the cutoff could never keep (rotated
   // two-site tensors often have rank far below m) and preconditions the Jacobi sweeps.
   DevStatus factorize(const z64* M, int p, int q, int mode, int left_ortho, z64* Lout, z64* Rout,
-                      bool reduce = false) {
+                      bool reduce = false, const std::function<void(int)>& ahead = {}) {
     const bool wide = p <= q;
     const int m = wide ? p : q, kW = wide ? q : p;
     GC_CHECK((size_t)m <= lay.mcap && (size_t)m * kW <= lay.slot_elems, GCAMPS_ECAPACITY,
              "factorisation exceeds workspace capacity");
-    if (m <= kSmallEig && kW <= kSplitSmallMaxK) return split_small(M, p, q, mode, left_ortho, Lout, Rout);
+    if (m <= kSmallEig && kW <= kSplitSmallMaxK) return split_small(M, p, q, mode, left_ortho, Lout, Rout, ahead);
     DevStatus mv{};
     if (mode == 1 && !tape && !rank_rec && !rank_frz && move_full_rank(M, p, q, left_ortho, Lout, Rout, mv)) return mv;
     const z64 one = {1.0, 0.0};
@@ -428,14 +429,16 @@ struct gcamps_ctx {
     launch_record(stream, U, B, sig, perm, m, kW, f.U, f.B, f.sig);
   }
   // factorize() of a matrix whose smaller side fits one workgroup: one launch, which also leaves
-  // the status in the pinned read-back block.
-  DevStatus split_small(const z64* M, int p, int q, int mode, int left_ortho, z64* Lout, z64* Rout) {
+  // the status in the pinned read-back block.  ahead: launches what follows for an assumed rank.
+  DevStatus split_small(const z64* M, int p, int q, int mode, int left_ortho, z64* Lout, z64* Rout,
+                        const std::function<void(int)>& ahead) {
     const int m = std::min(p, q), kW = std::max(p, q);
     int force_k, force_pass2;
     forced_decision(force_k, force_pass2);
     SplitArgs a{M, p, q, left_ortho, mode == 0 ? 1 : 0, force_pass2, {cfg.cutoff, cfg.chi_max, mode, force_k},
                 U, B, Lout, Rout, sig, perm, st, reinterpret_cast<DevStatus*>(rb_dev + kRbStatus), ++ticket};
     launch_split_small(stream, a);
+    if (ahead) ahead(force_k > 0 ? std::min(force_k, m) : m);
     await(reinterpret_cast<DevStatus*>(rb + kRbStatus)->ticket, a.ticket);
     DevStatus h;
     std::memcpy(&h, rb + kRbStatus, sizeof(DevStatus));
@@ -506,26 +509,37 @@ struct gcamps_ctx {
     tape->push_back(op);
   }
 
+  // A small split leaves its rank to the host, but an exact move nearly always keeps min(p, q): the product with the
+  // neighbour is launched behind the split for that rank (or the recorded one) before the host knows, and
+  // again only if the split kept another.  The queue then does not wait 6 us for the host.
   void move_right(int i) {  // centre i -> i+1
-    const int p = chi[i] * d, q = chi[i + 1];
-    DevStatus h = factorize(site[i], p, q, 1, 1, Lbuf, Rbuf);
+    const int p = chi[i] * d, q = chi[i + 1], ncols = d * chi[i + 2];
+    int made = 0;
+    auto absorb = [&](int k) {
+      launch_zgemm(stream, 0, 0, k, ncols, q, Rbuf, q, site[i + 1], ncols, spare, ncols, z64{1.0, 0.0}, 0, 0);
+      made = k;
+    };
+    DevStatus h = factorize(site[i], p, q, 1, 1, Lbuf, Rbuf, false, absorb);
     const int k = h.kept;
-    if (tape) tape_absorb(TAPE_ABSORB_R, i, site[i + 1], q, d * chi[i + 2]);
+    if (tape) tape_absorb(TAPE_ABSORB_R, i, site[i + 1], q, ncols);
+    if (made != k) absorb(k);
     std::swap(site[i], Lbuf);
-    const int ncols = d * chi[i + 2];
-    launch_zgemm(stream, 0, 0, k, ncols, q, Rbuf, q, site[i + 1], ncols, spare, ncols, z64{1.0, 0.0}, 0, 0);
     std::swap(site[i + 1], spare);
     chi[i + 1] = k;
     centre = i + 1;
   }
   void move_left(int i) {  // centre i -> i-1
-    const int p = chi[i], q = d * chi[i + 1];
-    DevStatus h = factorize(site[i], p, q, 1, 0, Lbuf, Rbuf);
+    const int p = chi[i], q = d * chi[i + 1], nrows = chi[i - 1] * d;
+    int made = 0;
+    auto absorb = [&](int k) {
+      launch_zgemm(stream, 0, 0, nrows, k, p, site[i - 1], p, Lbuf, k, spare, k, z64{1.0, 0.0}, 0, 0);
+      made = k;
+    };
+    DevStatus h = factorize(site[i], p, q, 1, 0, Lbuf, Rbuf, false, absorb);
     const int k = h.kept;
-    if (tape) tape_absorb(TAPE_ABSORB_L, i, site[i - 1], chi[i - 1] * d, p);
+    if (tape) tape_absorb(TAPE_ABSORB_L, i, site[i - 1], nrows, p);
+    if (made != k) absorb(k);
     std::swap(site[i], Rbuf);
-    const int nrows = chi[i - 1] * d;
-    launch_zgemm(stream, 0, 0, nrows, k, p, site[i - 1], p, Lbuf, k, spare, k, z64{1.0, 0.0}, 0, 0);
     std::swap(site[i - 1], spare);
     chi[i] = k;
     centre = i - 1;
