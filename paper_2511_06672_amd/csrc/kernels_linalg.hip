@@ -572,6 +572,7 @@ __global__ void k_pad_copy(const z64* __restrict__ G, int m, int ldg, z64* __res
   Up[idx] = (i == j) ? z64{1.0, 0.0} : z64{0.0, 0.0};
 }
 
+constexpr double kPrecheckTol = 2e-15;
 constexpr int kSweepFlags = 128;  // one rotation flag per sweep
 
 __global__ void k_trace(const z64* __restrict__ Gp, int m, int mp, double* out, int* __restrict__ sweep_flags) {
@@ -869,8 +870,10 @@ void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu,
   hipLaunchKernelGGL(k_trace, dim3(1), dim3(256), 0, s, Gp, m, mp, d_trace, sweep_flags);
   GC_LAUNCH_CHECK();
   if (precheck) {
-    hipLaunchKernelGGL(k_offdiag_check, dim3(blocks_for((size_t)m * m, 256)), dim3(256), 0, s, Gp, m, mp, d_trace, tol,
-                       skip, rel, floor_rel, reinterpret_cast<int*>(d_trace + 1));
+    // a Rayleigh-Ritz matrix is diagonal to the rounding of its products, a few 1e-16 of the trace; at the sweeps' own
+    // bound the check would call for a sweep each time (m = 600: 0.7 ms)
+    hipLaunchKernelGGL(k_offdiag_check, dim3(blocks_for((size_t)m * m, 256)), dim3(256), 0, s, Gp, m, mp, d_trace,
+                       kPrecheckTol, skip, rel, floor_rel, reinterpret_cast<int*>(d_trace + 1));
     GC_LAUNCH_CHECK();
   }
   if (precheck) {  // the pre-check flag sits after the trace; the rounds read the trace themselves
