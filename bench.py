@@ -46,7 +46,7 @@ N = 12 for 18 layers instead, past the transition (qutrit bonds reach 729):
     python bench.py --workload paper [--paper-layers 1.5]
 
 A plain device copy of known size calibrates the HBM counters (FETCH_SIZE, WRITE_SIZE)
-used for the roofline's traffic figure:
+of a profile:
 
     python bench.py --workload copy
 """
@@ -770,7 +770,7 @@ def main():
         sb = stb.stats()
         resbf = {"value": ngates / tb, "ms_per_step": 1e3 * tb, "fidelity": stb.fidelity(),
                  "choices_identical_to_timed_path": bool(np.array_equal(stb.choice_log(), st32.choice_log())),
-                 "gram_kernel": "k_gram_purity_bf16",
+                 "gram_kernel": "k_density<float, 3>",
                  "gram_tflops_algorithmic": (sb["tiled_flops"] / (sb["tiled_ms"] * 1e-3) / 1e12
                                              if sb["tiled_ms"] > 0 else None),
                  "rescored_candidates": int(sb["rescored"])}
@@ -808,7 +808,7 @@ def main():
                 "frac": achieved / peak, "traffic": None,
                 "traffic_unit": "HBM bytes per launch (FETCH_SIZE x 2 + WRITE_SIZE, copy-calibrated)",
                 "algorithmic_bytes": s32["tiled_bytes"] / s32["tiled_launches"],
-                "kernel": "k_gram_purity_bf16" if bf else "k_density<float, 3>",
+                "kernel": "k_density<float, 3>",
                 "launches": int(s32["tiled_launches"]), "avg_ms": per_launch_ms}
         if bf:
             roof["note"] = ("algorithmic flops (4 m^2 k per candidate); the split form issues three BF16 "
