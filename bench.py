@@ -64,7 +64,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 FP32_PEAK_TFLOPS = 157.3     # MI355X dense FP32 matrix peak
-BF16_PEAK_TFLOPS = 2500.0    # MI355X dense BF16 matrix peak
 FP64_PEAK_TFLOPS = 78.6      # MI355X dense FP64 matrix peak
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E bandwidth
 NEAR_TIE = 1e-4
@@ -802,17 +801,13 @@ def main():
         per_launch_flops = s32["tiled_flops"] / s32["tiled_launches"]
         per_launch_ms = tiled_ms / s32["tiled_launches"]
         achieved = per_launch_flops / (per_launch_ms * 1e-3) / 1e12
-        bf = prec == g.SCORE_BF16
-        peak = BF16_PEAK_TFLOPS if bf else FP32_PEAK_TFLOPS
+        peak = FP32_PEAK_TFLOPS
         roof = {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                 "frac": achieved / peak, "traffic": None,
                 "traffic_unit": "HBM bytes per launch (FETCH_SIZE x 2 + WRITE_SIZE, copy-calibrated)",
                 "algorithmic_bytes": s32["tiled_bytes"] / s32["tiled_launches"],
                 "kernel": "k_density<float, 3>",
                 "launches": int(s32["tiled_launches"]), "avg_ms": per_launch_ms}
-        if bf:
-            roof["note"] = ("algorithmic flops (4 m^2 k per candidate); the split form issues three BF16 "
-                            "products per real product, so 1/3 of the BF16 peak is its ceiling")
 
     # compression (factorisations) against the FP64 peak and the MPO apply against HBM, from the
     # library's event-timed counters of the same timed run
