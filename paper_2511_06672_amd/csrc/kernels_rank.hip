@@ -9,8 +9,6 @@
 // mutually orthogonal, and the singular values are the row norms.  One workgroup per candidate
 // holds M_c (smaller side <= 32) in LDS.
 #include <algorithm>
-#include <cfloat>
-#include <climits>
 
 #include "kernels.h"
 

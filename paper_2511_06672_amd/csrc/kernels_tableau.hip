@@ -1,5 +1,5 @@
-// Integer Z_d tableau kernels: Clifford layer update, disentangler right multiplication,
-// and commutation of a Weyl operator through C (§2.2, §2.3, §2.3.1, §3).
+// Integer Z_d tableau kernels: Clifford layer update and commutation of a Weyl operator through C (§2.2, §2.3,
+// §2.3.1, §3); the right multiplication by a disentangler is part of the bond's commit.
 //
 // Device layout: row r of the 2n-row tableau has exponents tx[r*n + i], tz[r*n + i] for site
 // i and phase tp[r] (power of tau, mod 2d).  Rows 0..n-1 are S_k = C Z_k C^dagger, rows

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,n,layers,nphase,ncand", [(2, 5, 4, 10, 6), (3, 9, 4, 10, 5), (3, 9, 6, 14, 4),
-                                                    (5, 4, 6, 12, 0), (7, 3, 3, 5, 0)])
+                                                    (5, 4, 6, 12, 0), (5, 4, 6, 12, 6), (7, 3, 3, 5, 0), (7, 3, 3, 5, 5)])
 def test_gradient_matches_dense_derivative(d, n, layers, nphase, ncand):
     from oracle.gradient import dense_gradient, dense_loss
     from paper_2511_06672_amd import gcamps as g
