@@ -299,7 +299,7 @@ int32_t gcamps_get_site(gcamps_ctx* ctx, int32_t site, double* out, int64_t cap,
 /* Statistics (16 doubles): [0] non-Clifford gates applied, [1] bonds scored,
  * [2] candidates re-scored in FP64 (FP32 mode), [3] degenerate cuts flagged,
  * [4] algorithmic flops of full-set scoring (direct: N_c (4 m^2 k + 8 d^4 chi_l chi_r) per bond; through
- * the two-site density matrix, FP64 with d = 2, 3 and FP32 with d = 3 above a size:
+ * the two-site density matrix, d = 2, 3 above a size (low-precision modes: by candidate count as well):
  * 4 (X d^2)^2 Y + N_c 4 X (X + 1) d^6; replica mode: 4 (X d^2)^2 Y + 8 X (X + 1) / 2 d^8 + 2 N_c d^8 with X, Y the smaller and larger bond), [5] algorithmic flops of the Gram products of
  * the factorisations, [6] full-set scoring kernel time in ms (device clock), [7] total time
  * inside gcamps_* calls in ms (host clock), [8] flops of the FP64 window re-score, [9] its
@@ -313,7 +313,8 @@ int32_t gcamps_get_stats(gcamps_ctx* ctx, double out[16]);
 /* Counters for the roofline of the compression and MPO steps (§2.4, §3), accumulated since
  * gcamps_init: [0] factorisations; [1] their algorithmic flops, 4 (6 p q^2 + 20 q^3) per p x q
  * SVD with p >= q (the R-SVD operation count, complex); [2] their device time in ms (Gram
- * product to truncation rule, second pass included; the emit of the factors excluded);
+ * product to truncation rule, second pass included; the emit of the factors excluded, except
+ * for exact moves by Cholesky factorisation, which form them on the way);
  * [3] MPO site launches; [4] their algorithmic bytes (each site tensor read once, its product
  * written once, complex128); [5] their device time in ms; [6] splits of rotated two-site
  * tensors whose eigen-decomposition ran on a rank-reduced basis (pivoted Cholesky of the Gram),
