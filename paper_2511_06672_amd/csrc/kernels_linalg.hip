@@ -635,7 +635,7 @@ __global__ void k_rownorm2(const z64* __restrict__ B, int m, int k, int ldb, dou
 }
 
 // Truncation rule on squared values sig2 (any order).  Sorted descending (ties by index).
-//   w_j = sig2_j / sum sig2;  tail[k] = sum_{j >= k} w_j  (accumulated from the smallest)
+//   w_j = sig2_j / sum sig2;  tail[k] = sum_{j >= k} w_j  (sums of values from k on alone, added from the end)
 //   k_cut = smallest k >= 1 with tail[k] <= cutoff; k_floor = #{sigma_j > 1e-13 sigma_0}
 //   k = min(k_cut, k_floor, chi_max); degeneracy guard as in the truncation rule.
 // mode 1 keeps k_floor (exact moves).  need_pass2 when a kept value is below 1e-12 sig2_0.
@@ -699,6 +699,8 @@ __global__ __launch_bounds__(1024) void k_trunc(const double* __restrict__ sig2,
     const double o = __shfl_down(after, off, 64);
     if (lane + off < 64) after += o;
   }
+  // of the later lanes alone: after - sum would lose them where this thread holds both sides of a gap
+  const double next = __shfl_down(after, 1, 64), later = lane < 63 ? next : 0.0;
   if (lane == 0) wsum[w] = after;
   if (t == 0) {
     above = over = below = 0;
@@ -708,7 +710,7 @@ __global__ __launch_bounds__(1024) void k_trunc(const double* __restrict__ sig2,
   const double ex = extra ? fmax(*extra, 0.0) : 0.0;
   double rest = ex;
   for (int x = nt / 64 - 1; x > w; --x) rest += wsum[x];
-  rest += after - sum;
+  rest += later;
   double total = ex;
   for (int x = nt / 64 - 1; x >= 0; --x) total += wsum[x];
   const double s0 = sqrt(key[0]);
