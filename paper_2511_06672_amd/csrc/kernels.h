@@ -179,7 +179,7 @@ void launch_scaled_copy(hipStream_t s, z64* dst, const z64* src, size_t count, d
 
 // ------------------------------------------------------------------ exact moves (kernels_chol.hip)
 // Pivots of a Cholesky factorisation (largest diagonal entry of the matrix, smallest pivot) and the
-// largest entry of |S - I| seen by launch_identity_gap.
+// largest row sum of |S - I| seen by launch_identity_gap, which bounds the spectral norm of a Hermitian S - I.
 struct CholState {
   double dmax, dmin, emax;
 };

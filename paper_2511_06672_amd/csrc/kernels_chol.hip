@@ -8,7 +8,8 @@
 //     G through the elimination (the panel solves divide them by K^H as they go), and two
 //     Newton-Schulz steps remove the rounding that the condition number has amplified.
 // The host falls back to the eigen-decomposition when a pivot is small (rank deficiency, or a
-// spectrum too wide for the Gram) or X K^-H is too far from orthonormal for those two steps.
+// spectrum too wide for the Gram) or X K^-H is too far from orthonormal for those two steps, by a bound of
+// the norm of its defect: its largest entry may be m times smaller.
 //
 // The eigen-decomposition that a move took before ran 5 to 10 sweeps: per move (averaged over a qutrit
 // circuit, device time) 0.63 ms at m = 81, 1.87 at 243 and 2.86 at 384, now 0.20, 0.43 and 0.72.  The
@@ -129,22 +130,24 @@ __global__ __launch_bounds__(512) void k_chol_panel(z64* __restrict__ A, int lda
     }
 }
 
-// Largest entry of |S - I| (S m x m) into st->emax.
+// Largest row sum of |S - I| (S m x m, Hermitian), a bound of its spectral norm, into st->emax; one workgroup
+// per row, and a maximum over them, so that the result does not depend on their order.
 __global__ __launch_bounds__(256) void k_identity_gap(const z64* __restrict__ S, int m, CholState* __restrict__ st) {
+  __shared__ double part[4];
+  const int i = blockIdx.x, t = threadIdx.x;
   double e = 0.0;
-  bool bad = false;
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < (size_t)m * m;
-       idx += (size_t)gridDim.x * blockDim.x) {
-    const z64 x = S[idx];
-    const double v = fabs(x.re - (idx / m == idx % m ? 1.0 : 0.0)) + fabs(x.im);
-    bad = bad || !(v < 1e30);
-    e = fmax(e, v);
+  for (int j = t; j < m; j += 256) {
+    const z64 x = S[(size_t)i * m + j];
+    e += fabs(x.re - (i == j ? 1.0 : 0.0)) + fabs(x.im);
   }
-  if (bad) e = 1e30;
-  for (int off = 32; off > 0; off >>= 1) e = fmax(e, __shfl_xor(e, off, 64));
+  for (int off = 32; off > 0; off >>= 1) e += __shfl_xor(e, off, 64);
+  if ((t & 63) == 0) part[t >> 6] = e;
+  __syncthreads();
+  if (t != 0) return;
+  e = part[0] + part[1] + part[2] + part[3];
+  if (!(e < 1e30)) e = 1e30;  // NaN as well
   // non-negative doubles order as their bit patterns
-  if ((threadIdx.x & 63) == 0)
-    atomicMax(reinterpret_cast<unsigned long long*>(&st->emax), (unsigned long long)__double_as_longlong(e));
+  atomicMax(reinterpret_cast<unsigned long long*>(&st->emax), (unsigned long long)__double_as_longlong(e));
 }
 
 // dst (q x p) = src^H (src p x q).
@@ -176,8 +179,7 @@ void launch_cholesky(hipStream_t s, z64* A, int m, int rows, CholState* st) {
 }
 
 void launch_identity_gap(hipStream_t s, const z64* S, int m, CholState* st) {
-  const int blocks = (int)std::min<size_t>(256, ((size_t)m * m + 1023) / 1024);
-  hipLaunchKernelGGL(k_identity_gap, dim3(blocks), dim3(256), 0, s, S, m, st);
+  hipLaunchKernelGGL(k_identity_gap, dim3(m), dim3(256), 0, s, S, m, st);
   GC_LAUNCH_CHECK();
 }
 
