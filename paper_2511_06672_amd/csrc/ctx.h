@@ -275,8 +275,11 @@ struct gcamps_ctx {
       // eigenvalues err by the square of the basis error where L L^H's err by tr S
       launch_zgemm(stream, 0, 1, nb, nb, kW, B, kW, B, kW, G, nb, one, 0, 1);
       // nearly diagonal already: the pre-check usually finds nothing to rotate, and then the
-      // eigenvectors are the identity and U and B stay as they are
-      eig_hermitian(stream, G, nb, nb, Z, nb, lam, 0, eig, st, &sw_main, true);
+      // eigenvectors are the identity and U and B stay as they are.  A direction dropped by the rank limit
+      // is below chi_max others, one dropped by the cutoff holds at most the cutoff (and with a degenerate group
+      // below the cut up to 1e-10 more of itself per member).
+      const double discardable = std::max(1.0 / (cfg.chi_max + 1.0), cfg.cutoff) * (1.0 + 1e-6);
+      eig_hermitian(stream, G, nb, nb, Z, nb, lam, 0, eig, st, &sw_main, discardable);
       if (sw_main != 0) {
         launch_zgemm(stream, 0, 0, m, nb, nb, U, ldu, Z, nb, Utmp, ldu, one, 0, 0);
         std::swap(U, Utmp);

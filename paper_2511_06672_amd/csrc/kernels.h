@@ -117,11 +117,12 @@ inline JacobiCrit jacobi_crit(int m, int rel) {
 // Offsets in a context's pinned read-back block: device status, pivoted and plain Cholesky
 // states, eigensolver slots, conjugated Weyl string and its error flag.
 constexpr size_t kRbStatus = 0, kRbPcState = 256, kRbChol = 384, kRbEig = 512, kRbWeyl = 1024, kRbExpect = 2560, kRbCommit = 2816, kRbSweep = 2880, kRbBytes = 4096;
-// precheck: test every pair against the rotation criterion first and return U = I, lam =
-// diag(G) without a sweep when none qualifies (for matrices expected to be diagonal already,
-// e.g. a Rayleigh-Ritz step; the result equals what one sweep that rotates nothing leaves).
+// discardable >= 0 (for matrices expected to be diagonal already, as of a Rayleigh-Ritz step; absolute criterion,
+// m > kSmallEig): every pair is tested first, and U = I, lam = diag(G) are returned without a sweep when no
+// entry exceeds kPrecheckTol and none that exceeds the sweeps' own bound turns a direction of at most
+// `discardable` of the trace, which the truncation rule may drop, by more than kPrecheckTilt (kernels_linalg.hip).
 void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu, double* lam,
-                   int rel, EigWork& w, DevStatus* st, int* host_sweeps, bool precheck = false);
+                   int rel, EigWork& w, DevStatus* st, int* host_sweeps, double discardable = -1.0);
 void launch_rownorm2(hipStream_t s, const z64* B, int m, int k, int ldb, double* out);
 // Sort, truncation rule, pass-2 decision.  mode 0 = truncate (cutoff, chi_max), 1 = floor only;
 // force_k > 0 keeps exactly that rank (frozen-decision replay).

@@ -572,7 +572,13 @@ __global__ void k_pad_copy(const z64* __restrict__ G, int m, int ldg, z64* __res
   Up[idx] = (i == j) ? z64{1.0, 0.0} : z64{0.0, 0.0};
 }
 
-constexpr double kPrecheckTol = 2e-15;
+// The pre-check's bounds.  A Rayleigh-Ritz matrix is diagonal to the rounding of its products, a few 1e-16 of the
+// trace, so the sweeps' bound of 3e-16 for every pair calls for a sweep each time (m = 600: 0.7 ms).  Between
+// directions that are all kept, or all dropped, entries up to kPrecheckTol may stay: they change neither space and
+// leave B's rows orthogonal to kPrecheckTol / discardable (5e-13 at 256 kept).  One that may be kept and one that may be
+// dropped are held to the sweeps' bound, unless what stays tilts them by no more than the rounding of the
+// rotations that made them (m 2^-53 = 8.5e-14 at m = 768).
+constexpr double kPrecheckTol = 2e-15, kPrecheckTilt = 1e-13;
 constexpr int kSweepFlags = 128;  // one rotation flag per sweep
 
 __global__ void k_trace(const z64* __restrict__ Gp, int m, int mp, double* out, int* __restrict__ sweep_flags) {
@@ -592,19 +598,22 @@ __global__ void k_trace(const z64* __restrict__ Gp, int m, int mp, double* out, 
   if (threadIdx.x < kSweepFlags) sweep_flags[threadIdx.x] = 0;
 }
 
-// Pre-check of a decomposition: sets *flag when some pair (i < j < m) of Gp passes the rotation
-// test, with the thresholds the sweeps would use (from the trace in out[0] of k_trace).
+// Pre-check of a decomposition: sets *flag when some pair (i < j < m) of Gp has an entry g above kPrecheckTol of the
+// trace (in *trace_in, from k_trace), or one above tol of it and above kPrecheckTilt of the difference of the
+// diagonal entries where the smaller of these is at most discardable of the trace.
 __global__ void k_offdiag_check(const z64* __restrict__ Gp, int m, int mp, const double* __restrict__ trace_in,
-                                double tol, double skip_rel, int rel, double floor_rel, int* __restrict__ flag) {
-  const JacobiThr jt = jacobi_thr(*trace_in, tol, skip_rel, rel, floor_rel);
+                                double tol, double discardable, int* __restrict__ flag) {
+  const JacobiThr strict = jacobi_thr(*trace_in, tol, 0.0, 0, 0.0), kept = jacobi_thr(*trace_in, kPrecheckTol, 0.0, 0, 0.0);
+  const double may_drop = discardable * *trace_in;
   const size_t total = (size_t)m * m;
   int hit = 0;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
     const int i = (int)(e / m), j = (int)(e % m);
     if (i < j) {
-      const z64 g = Gp[(size_t)i * mp + j];
+      const double h2 = cabs2(Gp[(size_t)i * mp + j]);
       const double a = Gp[(size_t)i * mp + i].re, b = Gp[(size_t)j * mp + j].re;
-      if (rel ? rot_needed<true>(a, b, cabs2(g), jt) : rot_needed<false>(a, b, cabs2(g), jt)) hit = 1;
+      const bool mixes = fmin(a, b) <= may_drop && h2 > kPrecheckTilt * kPrecheckTilt * (a - b) * (a - b);
+      if (rot_needed<false>(a, b, h2, mixes ? strict : kept)) hit = 1;
     }
   }
   if (hit) atomicOr(flag, 1);
@@ -863,7 +872,7 @@ void launch_zgemm(hipStream_t s, int opa, int opb, int M, int N, int K, const z6
 }
 
 void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu, double* lam, int rel, EigWork& w,
-                   DevStatus* st, int* host_sweeps, bool precheck) {
+                   DevStatus* st, int* host_sweeps, double discardable) {
   const JacobiCrit cr = jacobi_crit(m, rel);
   const double tol = cr.tol, skip = cr.skip_rel, floor_rel = cr.floor_rel;
   const int max_sweeps = cr.max_sweeps;
@@ -896,14 +905,12 @@ void eig_hermitian(hipStream_t s, const z64* G, int m, int ldg, z64* U, int ldu,
   GC_CHECK(max_sweeps < kSweepFlags, GCAMPS_ECAPACITY, "more sweeps than rotation flags");
   hipLaunchKernelGGL(k_trace, dim3(1), dim3(256), 0, s, Gp, m, mp, d_trace, sweep_flags);
   GC_LAUNCH_CHECK();
-  if (precheck) {
-    // a Rayleigh-Ritz matrix is diagonal to the rounding of its products, a few 1e-16 of the trace; at the sweeps' own
-    // bound the check would call for a sweep each time (m = 600: 0.7 ms)
-    hipLaunchKernelGGL(k_offdiag_check, dim3(blocks_for((size_t)m * m, 256)), dim3(256), 0, s, Gp, m, mp, d_trace,
-                       kPrecheckTol, skip, rel, floor_rel, reinterpret_cast<int*>(d_trace + 1));
+  if (discardable >= 0.0) {
+    GC_CHECK(!rel, GCAMPS_EINVAL, "eigensolver: the pre-check has the absolute criterion only");
+    hipLaunchKernelGGL(k_offdiag_check, dim3(blocks_for((size_t)m * m, 256)), dim3(256), 0, s, Gp, m, mp, d_trace, tol,
+                       discardable, reinterpret_cast<int*>(d_trace + 1));
     GC_LAUNCH_CHECK();
-  }
-  if (precheck) {  // the pre-check flag sits after the trace; the rounds read the trace themselves
+    // the flag sits after the trace; the rounds read the trace themselves
     double* tr_flag = w.host_rb;
     GC_HIP(hipMemcpyAsync(tr_flag, d_trace, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     GC_HIP(hipStreamSynchronize(s));
