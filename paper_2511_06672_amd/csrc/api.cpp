@@ -17,9 +17,6 @@
 
 using namespace gc;
 
-namespace gc {
-}
-
 namespace {
 
 thread_local std::string g_last_error;
@@ -98,10 +95,13 @@ void set_error(const std::string& msg) { g_last_error = msg; }
 }  // namespace gc
 
 namespace gc {
-// FP32 scoring takes the density form for qutrits; with d = 2 it stays with the rotated-matrix kernels, whose
-// per-shape launch choices (GCAMPS_TUNE_FILE) callers keep across runs.
+// Whether a bond of this configuration can be scored through the two-site density matrix at all, and whether it
+// may be in FP32 (of what size and number of candidates: gcamps_ctx::use_density).
+static bool density_reached(const gcamps_config& c) {
+  return c.d <= 3 && std::pow((double)c.chi_max * c.d, 3) >= kDensityMinWork;
+}
 static bool density_fp32(const gcamps_config& c) {
-  return c.d <= 3 && (c.score_prec == GCAMPS_SCORE_FP32 || c.score_prec == GCAMPS_SCORE_BF16);
+  return density_reached(c) && (c.score_prec == GCAMPS_SCORE_FP32 || c.score_prec == GCAMPS_SCORE_BF16);
 }
 
 Layout make_layout(const gcamps_config& c) {
@@ -151,8 +151,11 @@ Layout make_layout(const gcamps_config& c) {
   if (replica) L.nbuf_bytes = std::max(L.nbuf_bytes, replica_scratch_bytes(c.d, c.chi_max));
   L.off_nbuf = take(L.nbuf_bytes);
   L.off_rtab = take(replica ? replica_table_elems(c.d, (int)L.ncand) * sizeof(z64) : 0);
-  L.off_dtab = take(density_table_elems(c.d, (int)L.ncand) * sizeof(z64));
-  L.off_dtab32 = take(density_table_elems(c.d, (int)L.ncand) * sizeof(c32));  // in every mode
+  // the density form's rows (24 KB per qutrit candidate, 12 KB in FP32).  The replica mode's size stays that of the FP32
+  // mode plus its own tables, by which callers compare the two, so it holds the room of the FP32 rows too.
+  const size_t rows = density_reached(c) ? density_table_elems(c.d, (int)L.ncand) : 0;
+  L.off_dtab = take(rows * sizeof(z64));
+  L.off_dtab32 = take(density_fp32(c) || replica ? rows * sizeof(c32) : 0);
   const size_t D4 = d * d * d * d;
   L.off_q64 = take(L.ncand * D4 * sizeof(z64));
   L.off_q32 = take(L.ncand * D4 * sizeof(c32));
@@ -272,7 +275,7 @@ int32_t gcamps_init(const gcamps_config* cfg, void* dev_workspace, size_t bytes,
     c->q64 = reinterpret_cast<z64*>(w + lay.off_q64);
     c->rtab = cfg->score_prec == GCAMPS_SCORE_REPLICA ? reinterpret_cast<z64*>(w + lay.off_rtab) : nullptr;
     c->q32 = reinterpret_cast<c32*>(w + lay.off_q32);
-    c->dtab = cfg->d <= 3 ? reinterpret_cast<z64*>(w + lay.off_dtab) : nullptr;
+    c->dtab = density_reached(*cfg) ? reinterpret_cast<z64*>(w + lay.off_dtab) : nullptr;
     c->dtab32 = density_fp32(*cfg) ? reinterpret_cast<c32*>(w + lay.off_dtab32) : nullptr;
     c->qinv = reinterpret_cast<uint32_t*>(w + lay.off_qinv);
     int* tab = reinterpret_cast<int*>(w + lay.off_tab);
