@@ -785,32 +785,38 @@ struct gcamps_ctx {
   }
 
   // ---------------------------------------------------------------- scoring
-  // Scores of Theta (bonds cl, cr) in the arithmetic of prec: the full set, or (nlimit given) the window
-  // list of an earlier pass.  f_ready: the scratch holds Theta's density matrix; it does after a pass
-  // that used it.  evs, evcap and used as in launch_score.  Returns the algorithmic flops of the full set.
   // Whether a score of this mode goes through the density matrix: in FP64 always, in the low-precision modes (then
   // in FP32) where it is the faster form.  It pays its Gram product of Theta once, the rotated matrices pay theirs
-  // per candidate.  Qutrits, FP32: always.  Qutrits, BF16: 64 candidates at chi = 81 take 78 against 74 us, 128 89
-  // against 132, at chi = 243 16 take 291 against 213 and 128 426 against 990.  Qubits, chi = 256: 128
-  // candidates take 157 against 300 us (BF16) and 581 (FP32), 720 278 against 1565 and 3234; sets of up to 128
-  // keep the rotated matrices all the same, whose launch parameters are tuned and saved by shape.
+  // per candidate.  Qutrits, FP32: always in a sweep, whose FP64 re-score reuses the Gram; for a score alone (score_bond)
+  // of at most 8 candidates (one column group of the rotated form) the rotated matrices from m^2 k = 3e8 on: chi =
+  // 192 takes 162 us through the matrix and 167 rotated, 243 254 and 215, 495 1343 and 1076; 9 candidates at 243 257 and
+  // 361.  Qutrits, BF16: 64 candidates at chi = 81 take 78 against 74 us, 128 89
+  // against 132, at chi = 243 16 take 291 against 213 and 128 426 against 990.  Qubits: density is the faster form for
+  // 129 candidates at every size (chi = 64 40 us against 101 in FP32 and 72 in BF16, 512 593 against 4160 and 1947), and
+  // would be for fewer; sets of up to 128 keep the rotated matrices because their launch parameters are tuned and saved by
+  // shape (GCAMPS_TUNE_FILE) and sets of that size have saved ones.
   bool density_mode(int prec) const {
     if (prec == GCAMPS_SCORE_FP64) return true;
     if (prec == GCAMPS_SCORE_REPLICA || !dtab32) return false;
     return d == 2 ? ncand > 128 : prec == GCAMPS_SCORE_FP32 || ncand > 64;
   }
-  bool use_density(int prec, int cl, int cr) const {
-    return dtab && density_mode(prec) &&
-           (double)std::min(cl, cr) * std::min(cl, cr) * std::max(cl, cr) * d * d * d >= kDensityMinWork && density_fits(d, cl, cr, ncand, lay.nbuf_bytes);
+  // alone: no re-score of the same bond follows
+  bool use_density(int prec, int cl, int cr, bool alone = false) const {
+    const double work = (double)std::min(cl, cr) * std::min(cl, cr) * std::max(cl, cr) * d * d * d;
+    const bool few = alone && prec == GCAMPS_SCORE_FP32 && ncand <= kDensityFew && work >= kDensityFewWork;
+    return dtab && density_mode(prec) && work >= kDensityMinWork && !few && density_fits(d, cl, cr, ncand, lay.nbuf_bytes);
   }
   double density_flops(int cl, int cr) const {  // one candidate's product
     const double X = std::min(cl, cr);
     return 4.0 * X * (X + 1) * std::pow((double)d, 6);
   }
+  // Scores of Theta (bonds cl, cr) in the arithmetic of prec: the full set, or (nlimit given) the window
+  // list of an earlier pass.  f_ready: the scratch holds Theta's density matrix; it does after a pass
+  // that used it.  evs, evcap and used as in launch_score; alone as in use_density.
   void score(int prec, int cl, int cr, const int* list, const int* nlimit, double* out, bool& f_ready,
-             hipEvent_t* evs = nullptr, int evcap = 0, int* used = nullptr, int64_t* tick = nullptr) {
+             hipEvent_t* evs = nullptr, int evcap = 0, int* used = nullptr, int64_t* tick = nullptr, bool alone = false) {
     if (used) *used = 0;
-    if (use_density(prec, cl, cr)) {
+    if (use_density(prec, cl, cr, alone)) {
       if (!f_ready) launch_density_gram(stream, d, cl, cr, theta, nbuf);
       f_ready = true;
       const bool ev = used && evcap >= 2;
@@ -831,7 +837,7 @@ struct gcamps_ctx {
     launch_zgemm(stream, 0, 0, cl * d, d * cr, cm, site[i], cm, site[i + 1], d * cr, theta, d * cr, z64{1.0, 0.0},
                  0, 0);
     bool f_ready = false;
-    score(cfg.score_prec, cl, cr, nullptr, nullptr, s2, f_ready);
+    score(cfg.score_prec, cl, cr, nullptr, nullptr, s2, f_ready, nullptr, 0, nullptr, nullptr, true);
     GC_HIP(hipMemcpyAsync(out, s2, (size_t)ncand * sizeof(double), hipMemcpyDeviceToHost, stream));
     GC_HIP(hipStreamSynchronize(stream));
   }

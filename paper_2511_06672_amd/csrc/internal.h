@@ -101,6 +101,8 @@ constexpr int kReduceMaxM = 1024;
 // the two-site density matrix (kernels_density.hip): m = 32, k = 32 (d = 2) takes 40 us through it and 70
 // directly, m = 27, k = 27 (d = 3) 69 and 52, m = 27, k = 243 57 and 158.
 constexpr double kDensityMinWork = 25000;
+constexpr int kDensityFew = 8;  // see gcamps_ctx::density_mode
+constexpr double kDensityFewWork = 3e8;
 constexpr int kBlk = 16;        // block size of the multi-workgroup block Jacobi
 
 // ----------------------------------------------------------------- results in host memory
