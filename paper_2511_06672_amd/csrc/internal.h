@@ -91,10 +91,10 @@ constexpr double kNearTieLowp = 1e-4;  // smallest re-score window with FP32 / s
 constexpr size_t kDenseMax = size_t(1) << 16;  // largest d^n of the dense (validation) state
 constexpr int kSmallEig = 32;   // largest m handled by the single-workgroup eigensolver
 constexpr int kSplitSmallMaxK = 512;  // largest larger side of a one-launch split (kernels_split.hip)
-// Truncating splits with kReduceMinM < m <= kReduceMaxM take the pivoted-Cholesky path: below,
-// its fixed costs (panel launches, two more eigensolves) outweigh what it saves (measured on the
-// headline workload: m = 81 0.95 against 0.62 ms, m = 243 3.1 against 2.1 ms); above, it is
-// untested against the plain path's accuracy.
+// Truncating splits with kReduceMinM < m <= kReduceMaxM take the pivoted-Cholesky path; outside, it is
+// untested against the plain path's accuracy.  The lower line is not where the times cross: on graded matrices
+// (singular values over five decades) the plain path takes 0.80 ms at m = 48, 1.38 at 81, 2.67 at 144, 4.79 at 243 and
+// 6.40 at 320, this path 0.60, 0.65, 1.24, 2.06 and 2.82 (rank about 0.78 m; 0.96 at 81 and 2.70 at 243 with full rank).
 constexpr int kReduceMinM = 320;
 constexpr int kReduceMaxM = 1024;
 // m^2 k (m and k the smaller and larger side of the two-site matrix) from which a bond is scored through

@@ -93,7 +93,8 @@ struct EigWork {
 // that over the gap at a cut: over 24 gates of qutrit bonds up to 243 the fidelity estimate differed from the
 // oracle's by up to 1.9e-10 of itself at 2e-15 and by 1.2e-11 at 2e-16.  The convergence is quadratic, so the
 // tighter bound takes no further sweep (m = 48 to 243: equal times to 0.5%); rotations of degenerate
-// pairs leave about 1e-16 of the trace.
+// pairs leave about 1e-16 of the trace.  A Rayleigh-Ritz step that is skipped keeps to this bound only between
+// directions that the truncation may part (discardable, eig_hermitian).
 struct JacobiCrit {
   double tol, skip_rel, floor_rel;
   int max_sweeps;
@@ -284,8 +285,8 @@ void launch_density_score(hipStream_t s, int d, bool fp32, int chil, int chir, c
 // ------------------------------------------------------------------ replica scoring (kernels_replica.hip)
 // Full-set scores through the replica tensor of Theta (d = 2, 3): the Gram F of Theta over its
 // larger bond, the pair sum A, and one D^4 dot product per candidate with its table.
-constexpr int kReplicaMaxWg = 256;
-constexpr int kScoreSmallM = 96;    // matrices up to this many rows are scored directly (fused kernel)  // workgroups (partial sums) of the pair sum
+constexpr int kReplicaMaxWg = 256;  // workgroups (partial sums) of the pair sum
+constexpr int kScoreSmallM = 96;    // matrices up to this many rows are scored directly (fused kernel)
 // complex128 elements of the tables of `count` candidates (left-cut and right-cut tables).
 size_t replica_table_elems(int d, int count);
 // Scratch bytes for bonds up to chi_max (F, the transposed Theta, partial sums, A).

@@ -19,11 +19,11 @@ namespace gc {
 namespace {
 
 // ===================================================================================== GEMM
-// Two forms, both on 32 x 32 output tiles (a 768 x 768 product has 576 of them, so that every
-// CU gets work where 64 x 64 tiles left 40% of the chip idle).  K advances in chunks of 16;
-// each chunk is fetched into registers while the previous one is multiplied, then stored into
-// the other LDS stage (one barrier per chunk).  A complex product is four real MFMAs into a real
-// and an imaginary accumulator.  Hermitian products (herm: M == N and op(B) = op(A)^H) compute
+// Two forms: k_zgemm_s on 16 x 16 output tiles with operands straight from memory, and k_zgemm on 32 x 32 tiles
+// staged through LDS for products of many tiles (launch_zgemm has the line).  In k_zgemm, K advances in chunks
+// of 16; each chunk is fetched into registers while the previous one is multiplied, then stored into
+// the other LDS stage (one barrier per chunk).  In both a complex product is four real MFMAs into a real
+// and an imaginary accumulator, and Hermitian products (herm: M == N and op(B) = op(A)^H) compute
 // the upper triangle, diagonal included, and write its mirror.
 constexpr int GT = 32, GK = 16, GLD = GT + 4;
 
