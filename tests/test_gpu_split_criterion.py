@@ -69,6 +69,25 @@ def test_reduced_split_does_not_mix_kept_and_discarded(g, seed):
     assert np.max(tilt) <= (CRITERION + ROUNDING) / (lam[4] - lam[5])
 
 
+@pytest.mark.parametrize("m", [12, 24, 33, 48, 97, 243])
+def test_sweeps_stop_at_their_criterion(g, m):
+    """A Gram that is diagonal but for one entry of 1.2e-15 of the trace, above the criterion and below the looser one
+    that sweeps had before (2e-15), between the last kept direction and the first dropped one."""
+    print(f"[gpu-case] plain split, one entry off the diagonal, m={m}", flush=True)
+    lam = np.append(1.0 + 0.3 * np.arange(8)[::-1], 1e-2 * (1.0 - 0.003 * np.arange(m - 8)))
+    lam[5] = lam[4] * (1.0 - 1e-7)
+    lam /= lam.sum()
+    x = np.diag(np.sqrt(lam)).astype(complex)
+    x[5, 4] = 1.2e-15j / x[4, 4].real                   # G[5, 4] = 1.2e-15 i
+    theta = 0.5 * np.arctan2(2 * 1.2e-15, lam[4] - lam[5])
+    dropped = np.zeros(m, dtype=complex)
+    dropped[4], dropped[5] = 1j * np.sin(theta), np.cos(theta)
+    st = g.State(g.make_config(3, 2, 5, 1e-10, auto_disentangle=False, max_candidates=1, max_gate_terms=81))
+    sig, k, eps, left, _ = st.factorize(x, factors=True)
+    assert k == 5
+    assert np.max(np.abs(dropped.conj() @ left)) <= (CRITERION + ROUNDING) / (lam[4] - lam[5])
+
+
 @pytest.mark.parametrize("m,equal,reduce", [(20, 2, False), (32, 8, False), (33, 2, False), (48, 3, False), (81, 2, False),
                                             (81, 8, False), (97, 5, False), (243, 2, False), (243, 4, False),
                                             (333, 2, True), (333, 8, True)])
